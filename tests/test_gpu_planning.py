@@ -111,6 +111,30 @@ def test_multipliers_group_size_limits(wmb, orc):
     _check_mult(wmb, orc, T, m, off, train, "size limits")
 
 
+@pytest.mark.parametrize("kind", ["generic", "close", "equal", "extreme"])
+def test_multipliers_sorted_keys(wmb, orc, kind):
+    # pairs that share a wave's halves, its 64 lanes (63, 64 rows together) or
+    # not at all (65), an odd last group; ratios that agree in the bits the
+    # sort key keeps (m/T = k/k or (k + 1)/k, k near 2^24, next to k/(k + 1)'s
+    # neighbours), equal ratios, and float32's range ends
+    rng = np.random.default_rng(23)
+    sizes = [32, 32, 33, 31, 30, 34, 64, 0, 0, 64, 33, 32, 1, 1, 0, 0, 16, 48, 5, 60, 32, 0, 7]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(off[-1])
+    T = rng.uniform(1e-5, 1e-2, n)
+    m = T * rng.uniform(0.5, 2.0, n)
+    if kind == "close":
+        k = rng.integers(2 ** 24 - 64, 2 ** 24, n)
+        T, m = k.astype(float), k + rng.integers(-1, 2, n)
+    elif kind == "equal":
+        m = 2.0 * T
+    elif kind == "extreme":
+        T = rng.choice([1e-44, 1e-38, 1.0, 3e38], n)
+        m = rng.choice([1e-44, 1e-38, 1.0, 3e38], n)
+    train = (rng.random(n) < 0.8).astype(np.uint8)
+    _check_mult(wmb, orc, T, m, off, train, f"sorted keys, {kind}")
+
+
 # plan totals and all-singles sums: float32 run costs (the model's prediction
 # tolerance), summed in float64
 PLAN_RTOL = 1e-5
