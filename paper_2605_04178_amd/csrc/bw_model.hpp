@@ -102,7 +102,7 @@ struct BwEval {
     int32_t dt, pair, comp, nbar, nr;
     bool compute_bound;
     bool near_kink;        // |T_compute - T_io| within 1e-5 relative
-    R Kt, MA, MB, Dread, Dacc, Tmma, ta_tb, Tde, Dab, io_raw, ob_bytes;
+    R Kt, MA, MB, Dread, Dacc, Tmma, inv_rtc, ta_tb, Tde, Dab, io_raw, ob_bytes;
 };
 
 __device__ inline bool bw_desc_valid(const BwDesc& d)
@@ -123,14 +123,15 @@ __device__ inline double bw_div(double a, double b) { return a / b; }
 // rounding: relative error below 2^-21) is within one of floor(a / b)
 // whenever that quotient is below 2^20, and at or above cap + 1 whenever the
 // quotient is larger than cap + 1; so after clamping the estimate to cap + 1
-// one correction by the exact 64-bit remainder gives the quotient or a value
-// above cap, which the final min clamps.
+// one correction by the remainder gives the quotient or a value above cap,
+// which the final min clamps.  The remainder lies in [-b, a], within 32 bits
+// (its low 32 bits are exact whatever the product).
 __device__ inline uint32_t udiv_capped(uint32_t a, uint32_t b, uint32_t cap)
 {
     const float qf = (float)a * __builtin_amdgcn_rcpf((float)b);
     uint32_t q = qf >= (float)(cap + 1u) ? cap + 1u : (uint32_t)qf;
-    const uint64_t prod = (uint64_t)q * b;
-    q = prod > a ? q - 1u : (a - prod >= b ? q + 1u : q);
+    const int32_t r = (int32_t)(a - q * b);
+    q = r < 0 ? q - 1u : (r >= (int32_t)b ? q + 1u : q);
     return q < cap ? q : cap;
 }
 
@@ -179,14 +180,14 @@ __device__ inline void evaluate_bw(const BwStruct& st, const BwConst<R>& c, cons
     E.nr = (int32_t)nr;
 
     // element bytes 8, 4, 2, 1, 1/2 for dtypes 0..4 (exact powers of two)
-    const R e = (R)__builtin_ldexp(1.0, 3 - dt);
+    const R e = (R)__builtin_ldexpf(1.0f, 3 - dt);
     const R Kt = (R)d.Kt;
     E.Kt = Kt;
     const R MA = (R)d.bM * (R)d.bK * e;
     const R MB = (R)d.bN * (R)d.bK * e;
     E.MA = MA;
     E.MB = MB;
-    const R Dacc = (R)acc;
+    const R Dacc = (R)(uint32_t)acc;   // it fits in TMEM: below 2^30
     E.Dacc = Dacc;
 
     // Eq. (2), Eq. (3)
@@ -195,11 +196,12 @@ __device__ inline void evaluate_bw(const BwStruct& st, const BwConst<R>& c, cons
     const R Ttmem = Dread * c.inv_tr + c.lmma + Dacc * c.inv_tw;
     const R Tmgmt = bw_div(c.ltmgmt, Kt);
     const R fl = (R)2 * (R)d.bM * (R)d.bN * (R)d.bK;
-    R inv_rtc = c.inv_rtc[0];
-    inv_rtc = dt == 1 ? c.inv_rtc[1] : inv_rtc;
-    inv_rtc = dt == 2 ? c.inv_rtc[2] : inv_rtc;
-    inv_rtc = dt == 3 ? c.inv_rtc[3] : inv_rtc;
-    inv_rtc = dt == 4 ? c.inv_rtc[4] : inv_rtc;
+    R inv_rtc = vreg(c.inv_rtc[0]);   // register selects, not an indexed load
+    inv_rtc = dt == 1 ? vreg(c.inv_rtc[1]) : inv_rtc;
+    inv_rtc = dt == 2 ? vreg(c.inv_rtc[2]) : inv_rtc;
+    inv_rtc = dt == 3 ? vreg(c.inv_rtc[3]) : inv_rtc;
+    inv_rtc = dt == 4 ? vreg(c.inv_rtc[4]) : inv_rtc;
+    E.inv_rtc = inv_rtc;
     const R Tmma = fl * inv_rtc * (pair ? c.inv_s2sm : (R)1);
     E.Tmma = Tmma;
     const R Tcomp = Tmma + Ttmem + Tmgmt;
@@ -258,7 +260,7 @@ __device__ inline void bw_accumulate(const BwConst<R>& c, const BwEval<R>& E, A 
     // once per round, not per K step: wc inv_f / Kt with the K steps cancelled
     g[20] += E.compute_bound ? w * nr * inv_f : (A)0;
     // d/dR_TC[dt] of Tmma = -Tmma / R_TC[dt]
-    const A dR = -wc * (A)E.Tmma * (A)c.inv_rtc[E.dt];
+    const A dR = -wc * (A)E.Tmma * (A)E.inv_rtc;
     g[3] += E.dt == 0 ? dR : (A)0;
     g[4] += E.dt == 1 ? dR : (A)0;
     g[5] += E.dt == 2 ? dR : (A)0;

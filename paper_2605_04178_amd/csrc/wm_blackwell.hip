@@ -11,6 +11,21 @@
 
 namespace wm {
 
+// row base + k (base wave-uniform, off = lane_offset(k))
+__device__ inline BwDesc load_bw_desc(const BwDescPtrs& d, int64_t base, uint32_t off)
+{
+    BwDesc x;
+    x.bM = ntload_at(d.bM + base, off);
+    x.bN = ntload_at(d.bN + base, off);
+    x.bK = ntload_at(d.bK + base, off);
+    x.G = ntload_at(d.G + base, off);
+    x.fl = ntload_at(d.flags + base, off);
+    x.Kt = ntload_at(d.Kt + base, off);
+    x.CR = ntload_at(d.CR + base, off);
+    x.ob = ntload_at(d.ob + base, off);
+    return x;
+}
+
 __device__ inline BwDesc load_bw_desc(const BwDescPtrs& d, int64_t i)
 {
     BwDesc x;
@@ -96,6 +111,11 @@ __device__ inline void bw_grad_exact(const BwSet& S, const BwDesc& x, float wi, 
 
 // Phase 1: wave-aligned groups of 64 descriptors, one ballot word of redo
 // flags per group (written exactly once).
+// Bound: VALU issue (about 235 per 64 descriptors at 0.8 per CU-cycle, 63 % of
+// HBM peak on 36 B each).  At 2^24 descriptors the sweep takes 121 us; 168
+// when the tensor rate of the dtype was an indexed load from the kernel
+// arguments (twice per descriptor, its latency inside the evaluation) and
+// every array's address a 64-bit vector add.
 template <int MODE, bool PTR, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, const float* __restrict__ wv,
                                                   BwSet sv, const BwSet* __restrict__ sp,
@@ -107,12 +127,15 @@ __global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, cons
     float acc[kAcc];   // the lane's partial sums; float64 from the wave reduction on
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0f;
-    const int lane = threadIdx.x & 63;
+    const uint32_t lane = threadIdx.x & 63u;
+    // a wave's group of 64 descriptors starts at a wave-uniform row, so that
+    // its loads take a scalar base and one 32-bit lane offset
+    const int64_t first = (int64_t)blockIdx.x * BLOCK + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK + (threadIdx.x & ~63); base < n; base += stride) {
-        const int64_t i = base + lane;
+    for (int64_t base = first; base < n; base += stride) {
         bool redo = false;
-        if (i < n) redo = bw_grad_fast<MODE>(S, load_bw_desc(d, i), ntload(wv + i), acc);
+        const uint32_t off = lane_offset(lane);
+        if (lane < n - base) redo = bw_grad_fast<MODE>(S, load_bw_desc(d, base, off), ntload_at(wv + base, off), acc);
         const uint64_t m = __ballot(redo);
         if (lane == 0) flags[base >> 6] = m;
     }

@@ -10,6 +10,23 @@ namespace wm {
 template <typename T>
 __device__ inline T ntload(const T* p) { return __builtin_nontemporal_load(p); }
 
+// Element k of the array at p (wave-uniform) with k < 2^30, as a load from a
+// scalar base and a 32-bit lane offset.  off = lane_offset(k) has to be formed
+// in the loop body that loads: hoisted out as a 64-bit value, it costs a 64-bit
+// vector add per array.
+__device__ inline uint32_t lane_offset(uint32_t k)
+{
+    uint32_t off = k * 4u;
+    asm volatile("" : "+v"(off));
+    return off;
+}
+
+template <typename T>
+__device__ inline T ntload_at(const T* p, uint32_t off)
+{
+    return ntload((const T*)((const char*)p + off));
+}
+
 // Parameters read through a pointer into memory that stays constant while
 // the kernel runs (a by-value kernel argument in the kernel-argument
 // segment, or a set in device memory), laundered so that the optimiser cannot
