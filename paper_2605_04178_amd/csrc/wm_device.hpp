@@ -82,18 +82,50 @@ __device__ inline Desc<double> widen(const Desc<float>& x)
 // ---------------------------------------------------------------------------
 // block reduction of the 26 FP64 accumulators (fixed order)
 // ---------------------------------------------------------------------------
-// One step of the wave's recursive halving over lane bit m: a lane keeps the
-// upper half of its H x 2 remaining columns if its bit m is set, else the
-// lower half, and adds the partner lane's copy of the half it keeps.
-template <int H>
-__device__ inline void halve_columns(double* v, int lane, int m)
+// One step of the wave's recursive halving over lane bit M: a lane keeps the
+// upper half of its H x 2 remaining columns if its bit M is set, else the
+// lower half, and adds the partner lane's copy of the half it keeps.  Bits 32
+// and 16 swap half the lane rows of column j with the other half of column j +
+// H (v_permlane*_swap), after which the two registers hold exactly the two
+// addends; bits 8, 4 and 2 fetch the partner's copy by DPP moves inside the row
+// of 16 (i ^ 4 as the mirrors i ^ 3 and i ^ 7).
+template <int CTRL>
+__device__ inline double row_move(double x)
 {
-    const bool hi = (lane & m) != 0;
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+template <int M, int H>
+__device__ inline void halve_columns(double* v, int lane)
+{
 #pragma unroll
     for (int j = 0; j < H; ++j) {
-        const double send = hi ? v[j] : v[j + H];
-        const double keep = hi ? v[j + H] : v[j];
-        v[j] = keep + __shfl_xor(send, m, 64);
+        if constexpr (M == 32 || M == 16) {
+            const uint64_t a = __builtin_bit_cast(uint64_t, v[j]), b = __builtin_bit_cast(uint64_t, v[j + H]);
+            uint32_t al, ah, bl, bh;
+            if constexpr (M == 32) {
+                const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+                const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+                al = lo[0]; bl = lo[1]; ah = hi[0]; bh = hi[1];
+            } else {
+                const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+                al = lo[0]; bl = lo[1]; ah = hi[0]; bh = hi[1];
+            }
+            v[j] = __builtin_bit_cast(double, ((uint64_t)ah << 32) | al) +
+                   __builtin_bit_cast(double, ((uint64_t)bh << 32) | bl);
+        } else {
+            static_assert(M == 8 || M == 4 || M == 2, "lane bits 32 .. 2");
+            const bool up = (lane & M) != 0;
+            const double send = up ? v[j] : v[j + H];
+            const double keep = up ? v[j + H] : v[j];
+            if constexpr (M == 8) v[j] = keep + row_move<0x128>(send);
+            else if constexpr (M == 4) v[j] = keep + row_move<0x141>(row_move<0x1B>(send));
+            else v[j] = keep + row_move<0x4E>(send);
+        }
     }
 }
 
@@ -101,6 +133,8 @@ __device__ inline void halve_columns(double* v, int lane, int m)
 // the columns are halved over lane bits 5..1 (32 doubles cross lanes, not
 // 26 x 6 for one butterfly per column), after which lanes 2c and 2c + 1
 // hold column c over 32 lanes each; then the waves' rows are added in LDS.
+// Exchanging the doubles by 64 ds_bpermute per wave instead held the tail of
+// a sweep of few rows per lane to the LDS pipe.
 // Must be called by every thread of the block.  acc is clobbered.
 __device__ inline void block_reduce_acc(double* acc, double* lds /* [waves][26] */, double* out)
 {
@@ -110,12 +144,12 @@ __device__ inline void block_reduce_acc(double* acc, double* lds /* [waves][26] 
     double v[32];
 #pragma unroll
     for (int j = 0; j < 32; ++j) v[j] = j < kAcc ? acc[j] : 0.0;
-    halve_columns<16>(v, lane, 32);
-    halve_columns<8>(v, lane, 16);
-    halve_columns<4>(v, lane, 8);
-    halve_columns<2>(v, lane, 4);
-    halve_columns<1>(v, lane, 2);
-    const double s = v[0] + __shfl_xor(v[0], 1, 64);
+    halve_columns<32, 16>(v, lane);
+    halve_columns<16, 8>(v, lane);
+    halve_columns<8, 4>(v, lane);
+    halve_columns<4, 2>(v, lane);
+    halve_columns<2, 1>(v, lane);
+    const double s = v[0] + row_move<0xB1>(v[0]);
     const int col = lane >> 1;
     if ((lane & 1) == 0 && col < kAcc) lds[wid * kAcc + col] = s;
     __syncthreads();
