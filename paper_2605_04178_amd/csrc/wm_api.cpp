@@ -540,8 +540,8 @@ int32_t capture_stream(void* user, hipStream_t* out)
 // Device images of a multi-set calibration in a workspace: the per-set
 // parameter images, Adam states, options, descriptor and measurement pointer
 // tables, and each set's first item (items of `chunk` descriptors, set by
-// set).  step() enqueues the sweep, the float64 pass and one
-// reduce-and-Adam launch.
+// set).  step() enqueues the sweep and the float64 pass that ends in the
+// sets' Adam steps.
 struct BatchRun {
     int n_sets = 0, steps = 0, n_items = 0, nb = 0, nb2 = 0;
     int64_t chunk = 0;
@@ -556,15 +556,13 @@ struct BatchRun {
     double* hist_dev = nullptr;
     double* part_dev = nullptr;
     uint64_t* flags_dev = nullptr;
+    uint32_t* tickets_dev = nullptr;
     hipStream_t s = nullptr;
 
     hipError_t step() const
     {
-        hipError_t e = launch_grad_batched(d_dev, m_dev, S_dev, io_dev, n_items, chunk, n_sets,
-                                           n_dev, fo_dev, flags_dev, part_dev, nb, nb2, s);
-        if (e != hipSuccess) return e;
-        return launch_adam_batched(part_dev + (int64_t)nb * n_sets * kAcc, nb2, n_sets, st_dev,
-                                   o_dev, S_dev, steps, hist_dev, s);
+        return launch_batched_step(d_dev, m_dev, S_dev, io_dev, n_items, chunk, n_sets, n_dev, fo_dev, flags_dev,
+                                   part_dev, nb, nb2, tickets_dev, st_dev, o_dev, steps, hist_dev, s);
     }
 };
 
@@ -617,6 +615,13 @@ int32_t batch_prepare(int32_t n_sets, const wm_desc_t* sets, const float* const*
     run->hist_dev = (double*)(base + L.hist);
     run->part_dev = (double*)(base + L.partials);
     run->flags_dev = (uint64_t*)(base + L.flags);
+    // the sets' counts of finished blocks take a row slot behind the rows in
+    // use (one block less per set when every slot is taken)
+    static_assert(kMaxSets * sizeof(uint32_t) <= kAcc * sizeof(double), "the counts fit in a row");
+    const int room = L.nb + L.nb2 - run->nb - 1;
+    if (run->nb2 > 1 && room < run->nb2) run->nb2 = room;
+    if (run->nb2 > 1)
+        run->tickets_dev = (uint32_t*)(run->part_dev + (int64_t)(run->nb + run->nb2) * n_sets * kAcc);
     run->s = s;
     WM_HIP(hipMemcpyAsync(run->S_dev, Sh.data(), sizeof(Set) * n_sets, hipMemcpyHostToDevice, s));
     WM_HIP(hipMemcpyAsync(run->st_dev, sth.data(), sizeof(CalibState) * n_sets, hipMemcpyHostToDevice, s));
@@ -843,7 +848,7 @@ static int32_t bw_grad_common(int mode, const wm_bw_desc_t* desc, const float* w
     const BwSet S = make_bw_set(params);
     char* base = (char*)ws;
     const LaunchCfg cfg = launch_cfg(mode == 1 ? kOpLossGrad : kOpVjp, desc->n);
-    WM_HIP(launch_bw_grad(mode, bw_ptrs_of(desc), desc->n, w, S, nullptr, (double*)(base + W.partials),
+    WM_HIP(launch_bw_grad(mode, bw_ptrs_of(desc), desc->n, w, S, (double*)(base + W.partials),
                           (uint64_t*)(base + W.flags), W.g, cfg, out, (hipStream_t)stream));
     return WM_OK;
 }
@@ -901,12 +906,8 @@ int32_t wm_bw_calibrate(const wm_bw_desc_t* desc, const float* measured, const w
     const int64_t n = desc->n;
     const GradLayout G = L.g.g;
     const LaunchCfg cfg = launch_cfg(kOpLossGrad, n);
-    double* rows2_dev = part_dev + (int64_t)bw_grad_grid(1, true, n, cfg) * kAcc;
     auto step = [&]() -> hipError_t {
-        hipError_t e = launch_bw_grad(1, dp, n, measured, S, S_dev, part_dev, flags_dev, G, cfg,
-                                      nullptr, s);
-        if (e != hipSuccess) return e;
-        return launch_bw_adam(rows2_dev, G.nb2, st_dev, ao, S_dev, hist_dev, s);
+        return launch_bw_grad_adam(dp, n, measured, G, cfg, part_dev, flags_dev, st_dev, ao, S_dev, hist_dev, s);
     };
     rc = run_steps(s, opts->steps, step);
     if (rc != WM_OK) return rc;
@@ -1009,7 +1010,7 @@ static int32_t grad_common(int mode, const wm_desc_t* desc, const float* w, cons
         WM_HIP(launch_grad_exact(mode, ptrs_of(desc), desc->n, w, S, (double*)(base + W.partials),
                                  (uint64_t*)(base + W.flags), W.g, cfg.grid_mult, out, (hipStream_t)stream));
     else
-        WM_HIP(launch_grad(mode, ptrs_of(desc), desc->n, w, S, nullptr, (double*)(base + W.partials),
+        WM_HIP(launch_grad(mode, ptrs_of(desc), desc->n, w, S, (double*)(base + W.partials),
                            (uint64_t*)(base + W.flags), W.g, cfg, out, (hipStream_t)stream));
     return WM_OK;
 }
@@ -1187,13 +1188,8 @@ int32_t wm_calibrate_resume(const wm_desc_t* desc, const float* measured, const 
     const int64_t n = desc->n;
     const GradLayout G = L.g.g;
     const LaunchCfg cfg = launch_cfg(kOpLossGrad, n);
-    // the float64 pass folds the sweep's rows: Adam reduces its nb2 rows
-    double* rows2_dev = part_dev + (int64_t)grad_grid(1, true, n, cfg) * kAcc;
     auto step = [&]() -> hipError_t {
-        hipError_t e = launch_grad(1, dp, n, measured, S, S_dev, part_dev, flags_dev, G, cfg,
-                                   nullptr, s);
-        if (e != hipSuccess) return e;
-        return launch_adam(rows2_dev, G.nb2, st_dev, ao, S_dev, hist_dev, s);
+        return launch_grad_adam(dp, n, measured, G, cfg, part_dev, flags_dev, st_dev, ao, S_dev, hist_dev, s);
     };
     rc = run_steps(s, run, step);
     if (rc != WM_OK) return rc;
@@ -1321,7 +1317,7 @@ int32_t wm_autotune_grad(int32_t op, const wm_desc_t* desc, const float* w,
     hipStream_t s = (hipStream_t)stream;
     return tune_over(op, n, candidates(op), s, 10,
                      [&](const LaunchCfg& c) {
-                         return launch_grad(mode, dp, n, w, S, nullptr, (double*)(base + W.partials),
+                         return launch_grad(mode, dp, n, w, S, (double*)(base + W.partials),
                                             (uint64_t*)(base + W.flags), W.g, c, out, s);
                      },
                      best, best_us);
@@ -1402,7 +1398,7 @@ int32_t wm_autotune_batched(int32_t n_sets, const wm_desc_t* sets, const float* 
     hipStream_t s = nullptr;
     int32_t rc = capture_stream(stream, &s);
     if (rc != WM_OK) return rc;
-    // every candidate times one calibration step (sweep + reduce-and-Adam)
+    // every candidate times one calibration step (sweep, float64 pass and Adam)
     // from freshly uploaded images, so the Adam state it perturbs is private
     // to the workspace
     std::vector<LaunchCfg> cands = candidates(kOpCalibrateBatched);

@@ -120,9 +120,10 @@ template <int MODE, bool PTR, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, const float* __restrict__ wv,
                                                   BwSet sv, const BwSet* __restrict__ sp,
                                                   double* __restrict__ partials,
-                                                  uint64_t* __restrict__ flags)
+                                                  uint64_t* __restrict__ flags, uint32_t* __restrict__ ticket)
 {
     __shared__ double red[16 * kAcc];
+    if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;   // counted by the float64 pass
     const BwSet& S = PTR ? *sp : sv;
     float acc[kAcc];   // the lane's partial sums; float64 from the wave reduction on
 #pragma unroll
@@ -145,53 +146,48 @@ __global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, cons
     block_reduce_acc(a64, red, partials + (int64_t)blockIdx.x * kAcc);
 }
 
-// Phase 2: fold the phase-1 rows (fixed order) and redo flagged descriptors
-// in float64.
-template <int MODE, bool PTR>
+// One Adam step on log(theta); thread 0 rebuilds the set's constants.
+struct BwFinishAdam {
+    CalibState* st;
+    AdamOpts o;
+    BwSet* S;
+    double* loss_hist;
+    typedef AdamLane Ahead;
+    __device__ Ahead ahead() const { return AdamLane(st, o); }
+    __device__ void operator()(const double* tot, const Ahead& a) const
+    {
+        __shared__ double th[kTheta];
+        if (threadIdx.x >= 64) return;
+        if (adam_theta_step(st, a, tot, o, loss_hist, th) && threadIdx.x == 0) {
+            make_bw_const<float>(th, S->st, S->cf);
+            make_bw_const<double>(th, S->st, S->cd);
+        }
+    }
+};
+
+// Phase 2: fold the phase-1 rows (fixed order), redo flagged descriptors in
+// float64; the last block to finish sums the rows and ends the call.
+template <int MODE, bool PTR, typename FIN>
 __global__ __launch_bounds__(256) void k_bw_grad_redo(BwDescPtrs d, int64_t n,
                                                        const float* __restrict__ wv, BwSet sv,
-                                                       const BwSet* __restrict__ sp,
+                                                       const BwSet* sp,
                                                        const uint64_t* __restrict__ flags,
                                                        const double* __restrict__ rows1, int nrows1,
-                                                       double* __restrict__ rows2)
+                                                       double* rows2, uint32_t* ticket, FIN fin)
 {
-    __shared__ double red[16 * kAcc];
+    __shared__ double red[4 * kAcc], part[kRowGroups * kAcc], tot[kAcc];
+    __shared__ int64_t queue[4][kFlagQueue];
     const BwSet& S = PTR ? *sp : sv;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const typename FIN::Ahead ahead = fin.ahead();
+    const FlagWalk walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
+    column_parts<false, 4>(rows1, nrows1, (int)blockIdx.x, (int)gridDim.x, kAcc, part);
     double acc[kAcc];
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    for (int r = blockIdx.x + gridDim.x * threadIdx.x; r < nrows1; r += gridDim.x * blockDim.x) {
-#pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] += rows1[(int64_t)r * kAcc + j];
-    }
-    const int64_t nwords = (n + 63) >> 6;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t wi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; wi < nwords; wi += stride) {
-        uint64_t m = flags[wi];
-        while (m) {
-            const int bit = __builtin_ctzll(m);
-            m &= m - 1;
-            const int64_t i = (wi << 6) + bit;
-            bw_grad_exact<MODE>(S, load_bw_desc(d, i), wv[i], acc);
-        }
-    }
-    block_reduce_acc(acc, red, rows2 + (int64_t)blockIdx.x * kAcc);
-}
-
-// reduce the phase-2 rows and take one Adam step; rebuild the constants
-__global__ __launch_bounds__(256) void k_bw_adam(const double* __restrict__ partials, int rows,
-                                                  CalibState* st, AdamOpts o, BwSet* S,
-                                                  double* loss_hist)
-{
-    __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
-    reduce_partials(partials, rows, kAcc, red, tot);
-    __shared__ double th[kTheta];
-    if (threadIdx.x >= 64) return;
-    if (adam_theta_step(st, tot, o, loss_hist, th) && threadIdx.x == 0) {
-        make_bw_const<float>(th, S->st, S->cf);
-        make_bw_const<double>(th, S->st, S->cd);
-    }
+    for_flagged(walk, queue[wid], [&](int64_t i) { bw_grad_exact<MODE>(S, load_bw_desc(d, i), wv[i], acc); });
+    const double t = block_reduce_value(acc, red);
+    if (finish_rows(t, part, rows2, kAcc, ticket, tot)) fin(tot, ahead);
 }
 
 template <int BLOCK>
@@ -227,45 +223,32 @@ static int bw_grid_t(int64_t n, int grid_mult)
     return (int)(r < 1 ? 1 : r);
 }
 
-int bw_grad_grid(int mode, bool ptr, int64_t n, const LaunchCfg& c)
+template <int MODE, bool PTR, typename FIN>
+static hipError_t bw_grad_t(const BwDescPtrs& d, int64_t n, const float* w, const BwSet& S, const BwSet* S_dev,
+                            double* partials, uint64_t* flags, const GradLayout& L, const LaunchCfg& c,
+                            const FIN& fin, hipStream_t s)
 {
-    if (mode == 1) return ptr ? bw_grid_t<1, true>(n, c.grid_mult) : bw_grid_t<1, false>(n, c.grid_mult);
-    return ptr ? bw_grid_t<0, true>(n, c.grid_mult) : bw_grid_t<0, false>(n, c.grid_mult);
-}
-
-template <int MODE, bool PTR>
-static void bw_grad_t(const BwDescPtrs& d, int64_t n, const float* w, const BwSet& S,
-                      const BwSet* S_dev, double* partials, uint64_t* flags, int nb,
-                      const GradLayout& L, hipStream_t s)
-{
-    k_bw_grad<MODE, PTR, 256><<<nb, 256, 0, s>>>(d, n, w, S, S_dev, partials, flags);
-    k_bw_grad_redo<MODE, PTR><<<L.nb2, 256, 0, s>>>(d, n, w, S, S_dev, flags, partials, nb,
-                                                     partials + (int64_t)nb * kAcc);
+    const int nb = bw_grid_t<MODE, PTR>(n, c.grid_mult);
+    const RedoLayout r = redo_layout(L, nb, partials);
+    k_bw_grad<MODE, PTR, 256><<<nb, 256, 0, s>>>(d, n, w, S, S_dev, partials, flags, r.ticket);
+    k_bw_grad_redo<MODE, PTR><<<r.nb2, 256, 0, s>>>(d, n, w, S, S_dev, flags, partials, nb,
+                                                    partials + (int64_t)nb * kAcc, r.ticket, fin);
+    return hipGetLastError();
 }
 
 hipError_t launch_bw_grad(int mode, const BwDescPtrs& d, int64_t n, const float* w, const BwSet& S,
-                          const BwSet* S_dev, double* partials, uint64_t* flags, const GradLayout& L,
-                          const LaunchCfg& c, double* out, hipStream_t s)
+                          double* partials, uint64_t* flags, const GradLayout& L, const LaunchCfg& c,
+                          double* out, hipStream_t s)
 {
-    const int nb = bw_grad_grid(mode, S_dev != nullptr, n, c);
-    if (mode == 1) {
-        if (S_dev) bw_grad_t<1, true>(d, n, w, S, S_dev, partials, flags, nb, L, s);
-        else bw_grad_t<1, false>(d, n, w, S, S_dev, partials, flags, nb, L, s);
-    } else {
-        if (S_dev) bw_grad_t<0, true>(d, n, w, S, S_dev, partials, flags, nb, L, s);
-        else bw_grad_t<0, false>(d, n, w, S, S_dev, partials, flags, nb, L, s);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !out) return e;
-    return launch_reduce(mode, partials + (int64_t)nb * kAcc, L.nb2, out, s);
+    if (mode == 1) return bw_grad_t<1, false>(d, n, w, S, nullptr, partials, flags, L, c, FinishOut<1>{out}, s);
+    return bw_grad_t<0, false>(d, n, w, S, nullptr, partials, flags, L, c, FinishOut<0>{out}, s);
 }
 
-hipError_t launch_bw_adam(const double* partials, int rows, CalibState* st, const AdamOpts& o,
-                          BwSet* S, double* loss_hist, hipStream_t s)
+hipError_t launch_bw_grad_adam(const BwDescPtrs& d, int64_t n, const float* meas, const GradLayout& L,
+                               const LaunchCfg& c, double* partials, uint64_t* flags, CalibState* st,
+                               const AdamOpts& o, BwSet* S, double* loss_hist, hipStream_t s)
 {
-    // one wave when it holds every row (no cross-wave steps in the reduction)
-    k_bw_adam<<<1, rows <= 64 ? 64 : 256, 0, s>>>(partials, rows, st, o, S, loss_hist);
-    return hipGetLastError();
+    return bw_grad_t<1, true>(d, n, meas, BwSet{}, S, partials, flags, L, c, BwFinishAdam{st, o, S, loss_hist}, s);
 }
 
 }  // namespace wm

@@ -135,8 +135,9 @@ __device__ inline void halve_columns(double* v, int lane)
 // hold column c over 32 lanes each; then the waves' rows are added in LDS.
 // Exchanging the doubles by 64 ds_bpermute per wave instead held the tail of
 // a sweep of few rows per lane to the LDS pipe.
-// Must be called by every thread of the block.  acc is clobbered.
-__device__ inline void block_reduce_acc(double* acc, double* lds /* [waves][26] */, double* out)
+// Must be called by every thread of the block; thread j < 26 returns column
+// j's sum (other threads 0).  acc is clobbered.
+__device__ inline double block_reduce_value(double* acc, double* lds /* [waves][26] */)
 {
     const int lane = threadIdx.x & 63;
     const int wid = threadIdx.x >> 6;
@@ -153,30 +154,207 @@ __device__ inline void block_reduce_acc(double* acc, double* lds /* [waves][26] 
     const int col = lane >> 1;
     if ((lane & 1) == 0 && col < kAcc) lds[wid * kAcc + col] = s;
     __syncthreads();
+    double t = 0.0;
     if (threadIdx.x < kAcc) {
         const int nw = blockDim.x >> 6;
-        double s = 0.0;
-        for (int w = 0; w < nw; ++w) s += lds[w * kAcc + threadIdx.x];
-        out[threadIdx.x] = s;
+        for (int w = 0; w < nw; ++w) t += lds[w * kAcc + threadIdx.x];
     }
     __syncthreads();
+    return t;
 }
 
-// Fixed-order sum of partial rows: thread t adds rows t, t+256, ... of all 26
-// columns, then the block tree of block_reduce_acc.
-__device__ inline void reduce_partials(const double* __restrict__ partials, int rows, int stride,
-                                       double* red /* [waves][26] */, double* tot /* [26] */)
+__device__ inline void block_reduce_acc(double* acc, double* lds /* [waves][26] */, double* out)
 {
-    double acc[kAcc];
-#pragma unroll
-    for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    for (int r = threadIdx.x; r < rows; r += blockDim.x) {
-        const double* row = partials + (int64_t)r * stride;
-#pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] += row[j];
-    }
-    block_reduce_acc(acc, red, tot);
+    const double t = block_reduce_value(acc, lds);
+    if (threadIdx.x < kAcc) out[threadIdx.x] = t;
 }
+
+// ---------------------------------------------------------------------------
+// rows handed to the last block of a grid
+// ---------------------------------------------------------------------------
+// A block's row of column sums stored where every other block can read it
+// within the launch: the eight XCDs' L2 caches are not coherent with one
+// another, so the values go by agent-scope atomic stores (written through) and
+// come back by agent-scope atomic loads.
+__device__ inline void store_shared(double* p, double v)
+{
+    __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline double load_shared(const double* p)
+{
+    return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// True on every thread of the block that finishes last, after wave 0 of each
+// block has stored its row by store_shared.  *ticket counts finished blocks (0
+// before the launch).  The wait makes the row's stores complete before the
+// count shows the block as finished, so the last block's load_shared see
+// every row.  An agent-scope release and acquire around the count would write
+// back and invalidate whole L2 caches for the same guarantee: measured slower
+// than a separate launch for the final reduction.
+__device__ inline bool last_block(uint32_t* ticket, uint32_t nblocks)
+{
+    __shared__ uint32_t last;
+    if (threadIdx.x < 64) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0)
+            last = nblocks <= 1u || __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT) == nblocks - 1u;
+    }
+    __syncthreads();
+    return last != 0u;
+}
+
+// Column sums of rows first, first + step, ... below nrows (`stride` doubles
+// apart), by a block of 256: thread 26 g + c adds column c of every ninth row
+// from the g-th, LOADS of them in flight, so that consecutive threads read
+// consecutive doubles (one row per thread would spread each load over 64 rows);
+// its sum goes to part[26 g + c].  SHARED: rows stored by store_shared in this
+// launch.
+constexpr int kRowGroups = 9;   // 9 x 26 of the 256 threads
+template <bool SHARED, int LOADS>
+__device__ inline void column_parts(const double* rows, int nrows, int first, int step, int64_t stride, double* part)
+{
+    const int g = (int)threadIdx.x / kAcc, c = (int)threadIdx.x - g * kAcc;
+    if (g >= kRowGroups) return;
+    double v = 0.0;
+    const int64_t hop = (int64_t)step * kRowGroups;
+    for (int64_t r0 = first + (int64_t)step * g; r0 < nrows; r0 += hop * LOADS) {
+        double x[LOADS];
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) {
+            const int64_t r = r0 + hop * k;
+            x[k] = 0.0;
+            if (r < nrows) x[k] = SHARED ? load_shared(rows + r * stride + c) : rows[r * stride + c];
+        }
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) v += x[k];
+    }
+    part[threadIdx.x] = v;
+}
+
+__device__ inline double add_parts(const double* part)   // threads 0 .. 25, after a barrier
+{
+    double v = 0.0;
+#pragma unroll
+    for (int g = 0; g < kRowGroups; ++g) v += part[g * kAcc + threadIdx.x];
+    return v;
+}
+
+// The end of a float64 pass: this block's row of column sums (thread j < 26:
+// t, plus the parts of the sweep's rows) goes to rows2, and the last block to
+// finish sums the rows.  True on the threads of that block, with tot[j] in LDS.
+__device__ inline bool finish_rows(double t, double* part /* [9 * 26] */, double* rows2, int64_t stride, uint32_t* ticket,
+                                   double* tot)
+{
+    if (threadIdx.x < kAcc) store_shared(rows2 + (int64_t)blockIdx.x * stride + threadIdx.x, t + add_parts(part));
+    if (!last_block(ticket, gridDim.x)) return false;
+    column_parts<true, 15>(rows2, (int)gridDim.x, 0, 1, stride, part);
+    __syncthreads();
+    if (threadIdx.x < kAcc) tot[threadIdx.x] = add_parts(part);
+    __syncthreads();
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// flagged rows of a bit-per-row flag array, packed over a wave's lanes
+// ---------------------------------------------------------------------------
+// Orders this wave's LDS stores before its later LDS loads from other lanes
+// (the LDS executes one wave's operations in issue order; the fences keep
+// the compiler from moving accesses across this point).
+__device__ inline void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline uint32_t lanes_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+constexpr int kFlagQueue = 128;   // row indices queued per wave
+
+// This lane's first two words of a walk over the flag words w0 .. w0 + 63, w0 +
+// stride ..., up to nwords (w0 and stride multiples of 64, wave-uniform),
+// loaded ahead of other work.
+struct FlagWalk {
+    const uint64_t* flags;
+    int64_t nwords, base, stride;
+    uint64_t m, next;
+    __device__ inline uint64_t word(int64_t b) const
+    {
+        const int64_t w = b + (threadIdx.x & 63);
+        return w < nwords ? flags[w] : 0ull;
+    }
+    __device__ inline FlagWalk(const uint64_t* f, int64_t nw, int64_t w0, int64_t st)
+        : flags(f), nwords(nw), base(w0), stride(st), m(word(w0)), next(word(w0 + st))
+    {
+    }
+};
+
+// f(row) for every set bit of the walk's words (every lane active).
+// Flags are sparse (a few per thousand rows) and f is a long float64 chain,
+// so rows are queued in LDS, lowest bit of each lane's word first, and f runs
+// with a row on every lane; called on the words' own lanes it would run once
+// for nearly every word, a lane or two at a time.
+template <typename F>
+__device__ inline void for_flagged(FlagWalk w, int64_t* queue /* [kFlagQueue], the wave's own */, F f)
+{
+    const int lane = threadIdx.x & 63;
+    int qn = 0;
+    for (;;) {
+        uint64_t any = __ballot(w.m != 0ull);
+        while (qn < 64 && (any != 0ull || w.base + w.stride < w.nwords)) {
+            if (any != 0ull) {
+                if (w.m != 0ull) {
+                    queue[qn + (int)lanes_below(any)] = ((w.base + lane) << 6) + __builtin_ctzll(w.m);
+                    w.m &= w.m - 1;
+                }
+                qn += __builtin_popcountll(any);
+            } else {
+                w.base += w.stride;
+                w.m = w.next;
+                w.next = w.word(w.base + w.stride);
+            }
+            any = __ballot(w.m != 0ull);
+        }
+        if (qn == 0) return;
+        wave_lds_sync();
+        if (lane < qn) f(queue[lane]);
+        const int left = qn > 64 ? qn - 64 : 0;   // at most 63
+        const int64_t moved = lane < left ? queue[64 + lane] : 0;
+        wave_lds_sync();
+        if (lane < left) queue[lane] = moved;
+        qn = left;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the end of a gradient call: what the last block of the float64 pass does
+// with the 26 totals in LDS; ahead() is loaded at the pass's start
+// ---------------------------------------------------------------------------
+template <int MODE>
+struct FinishOut {   // mode 0: the 24 gradient sums; mode 1: loss, count and gradient over the count
+    double* out;
+    struct Ahead {};
+    __device__ Ahead ahead() const { return Ahead(); }
+    __device__ void operator()(const double* tot, const Ahead&) const
+    {
+        if (threadIdx.x >= kAcc) return;
+        const double v = tot[threadIdx.x];
+        if (MODE == 1) {
+            const double c = tot[1];
+            out[threadIdx.x] = (threadIdx.x == 1 || c == 0.0) ? v : v / c;
+        } else if (threadIdx.x >= 2) {
+            out[threadIdx.x - 2] = v;
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------
 // device Adam on log(theta)
@@ -208,7 +386,38 @@ __device__ inline double isotonic4(double v, int lane, int base)
     return best;
 }
 
-__device__ inline bool adam_theta_step(CalibState* st, const double* tot, const AdamOpts& o,
+// What lane j < 24 of a wave needs of the step, loaded ahead of the totals (at
+// the start of the kernel that ends in the step, where the loads cost nothing;
+// after the totals they were 2 us of its chain).
+struct AdamLane {
+    int32_t step_index, was_diverged;
+    double theta, phi, m, v, lo_log, hi_log;
+    double lr, c1, c2;   // the step's schedule
+    __device__ inline AdamLane(const CalibState* st, const AdamOpts& o)
+    {
+        const int lane = threadIdx.x & 63;
+        const int j = lane < kTheta ? lane : 0;
+        step_index = st->t;
+        was_diverged = st->diverged;
+        theta = st->theta[j];
+        phi = st->phi[j];
+        m = st->m[j];
+        v = st->v[j];
+        lo_log = o.lo_log[j];
+        hi_log = o.hi_log[j];
+        // from the host's table where there is one, else formed here (three
+        // pow calls on the wave's critical path)
+        if (o.sched && step_index < o.steps) {
+            lr = o.sched[3 * step_index];
+            c1 = o.sched[3 * step_index + 1];
+            c2 = o.sched[3 * step_index + 2];
+        } else {
+            adam_schedule(o, step_index, &lr, &c1, &c2);
+        }
+    }
+};
+
+__device__ inline bool adam_theta_step(CalibState* st, const AdamLane& a, const double* tot, const AdamOpts& o,
                                        double* loss_hist, double* th_out /* LDS [kTheta] */)
 {
     // Called by the 64 lanes of one wave, converged; lane j < 24 updates
@@ -217,42 +426,31 @@ __device__ inline bool adam_theta_step(CalibState* st, const double* tot, const 
     // changed; th_out then holds the new theta, visible to the whole wave,
     // and the caller rebuilds its constants from it.
     const int lane = threadIdx.x & 63;
-    const int step_index = st->t;
-    const int was_diverged = st->diverged;
     const double cnt = tot[1];
     const double loss = cnt > 0.0 ? tot[0] / cnt : 0.0;
     if (lane == 0) {
-        st->t = step_index + 1;
-        if (loss_hist && step_index < o.steps)
-            loss_hist[step_index] = was_diverged ? __builtin_nan("") : loss;
+        st->t = a.step_index + 1;
+        if (loss_hist && a.step_index < o.steps)
+            loss_hist[a.step_index] = a.was_diverged ? __builtin_nan("") : loss;
     }
-    if (was_diverged) return false;
+    if (a.was_diverged) return false;
     const bool mine = lane < kTheta;
     const double g = mine && cnt > 0.0 ? tot[2 + lane] / cnt : 0.0;
     if (!__builtin_isfinite(loss) || __ballot(!__builtin_isfinite(g)) != 0) {
         if (lane == 0) st->diverged = 1;
         return false;
     }
-    const double th = mine ? st->theta[lane] : 1.0;
+    const double th = mine ? a.theta : 1.0;
     if (mine) st->theta_ok[lane] = th;
-    // the step's schedule: from the host's table (three loads) where there is
-    // one, else formed here (three pow calls on the wave's critical path)
-    double lr, c1, c2;
-    if (o.sched && step_index < o.steps) {
-        lr = o.sched[3 * step_index];
-        c1 = o.sched[3 * step_index + 1];
-        c2 = o.sched[3 * step_index + 2];
-    } else {
-        adam_schedule(o, step_index, &lr, &c1, &c2);
-    }
+    const double lr = a.lr, c1 = a.c1, c2 = a.c2;
     double th_new = th;
     bool ok = true;
     const bool fit = mine && ((o.free_mask >> lane) & 1u);
-    double phi = fit ? st->phi[lane] : 0.0;
+    double phi = fit ? a.phi : 0.0;
     if (fit) {
         const double gp = th * g;
-        const double m = o.beta1 * st->m[lane] + (1.0 - o.beta1) * gp;
-        const double v = o.beta2 * st->v[lane] + (1.0 - o.beta2) * gp * gp;
+        const double m = o.beta1 * a.m + (1.0 - o.beta1) * gp;
+        const double v = o.beta2 * a.v + (1.0 - o.beta2) * gp * gp;
         st->m[lane] = m;
         st->v[lane] = v;
         const double mh = m / c1;
@@ -264,7 +462,7 @@ __device__ inline bool adam_theta_step(CalibState* st, const double* tot, const 
     if (o.order & 1) phi = isotonic4<false>(phi, lane, 0);
     if (o.order & 2) phi = isotonic4<true>(phi, lane, 4);
     if (fit) {
-        phi = fmin(fmax(phi, o.lo_log[lane]), o.hi_log[lane]);
+        phi = fmin(fmax(phi, a.lo_log), a.hi_log);
         st->phi[lane] = phi;
         th_new = exp(phi);
         ok = __builtin_isfinite(th_new) && th_new > 0.0;

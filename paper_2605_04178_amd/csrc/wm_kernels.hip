@@ -219,9 +219,10 @@ template <int MODE, bool PTR, int BLOCK, bool X64 = false>
 __global__ __launch_bounds__(BLOCK) void k_grad(DescPtrs d, int64_t n, const float* __restrict__ wv,
                                                Set sv, const Set* __restrict__ sp,
                                                double* __restrict__ partials,
-                                               uint64_t* __restrict__ flags)
+                                               uint64_t* __restrict__ flags, uint32_t* __restrict__ ticket)
 {
     __shared__ double red[16 * kAcc];
+    if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;   // counted by the float64 pass
     const Set& S = PTR ? *sp : sv;
     struct Args { DescPtrs d; int64_t n; const float* wv; Set sv; };
     const Set* sc = PTR ? sp : WM_KERNARG_PTR(Args, sv);   // the set, read in place
@@ -252,67 +253,61 @@ __global__ __launch_bounds__(BLOCK) void k_grad(DescPtrs d, int64_t n, const flo
     block_reduce_acc(a64, red, partials + (int64_t)blockIdx.x * kAcc);
 }
 
+__device__ inline void adam_update(CalibState* st, const AdamLane& a, const double* tot, const AdamOpts& o, Set* S,
+                                   double* loss_hist)
+{
+    __shared__ double th[kTheta];
+    if (threadIdx.x >= 64) return;
+    // one group of constants per lane, from the new theta in LDS
+    if (adam_theta_step(st, a, tot, o, loss_hist, th) && threadIdx.x < kConstFields) {
+        const_field<float>(th, S->st, S->cf, threadIdx.x);
+        const_field<double>(th, S->st, S->cd, threadIdx.x);
+    }
+}
+
+struct FinishAdam {   // one Adam step on log(theta); the set's constants rebuilt
+    CalibState* st;
+    AdamOpts o;
+    Set* S;
+    double* loss_hist;
+    typedef AdamLane Ahead;
+    __device__ Ahead ahead() const { return AdamLane(st, o); }
+    __device__ void operator()(const double* tot, const Ahead& a) const { adam_update(st, a, tot, o, S, loss_hist); }
+};
+
 // Phase 2: (a) block b first folds the phase-1 partial rows b, b + nb2, ...
-// (fixed order), so the final single-block reduction only sees nb2 rows;
-// (b) it re-evaluates in float64 every descriptor flagged in its flag words.
-template <int MODE, bool PTR>
+// (fixed order), so the final reduction only sees nb2 rows; (b) it
+// re-evaluates in float64 every descriptor flagged in its flag words; (c) the
+// last block to finish sums the blocks' rows in row order and ends the call
+// (fin).  Latency only: one chain of loads, a float64 evaluation, the block
+// reduction, the count and the rows' read-back.  At 2^20 descriptors with the
+// Adam step as the end 12.0 us where the pass (8.0) and a launch of its own
+// for the end (7.7) took 15.7 and a gap; at 2^24 10.6 us against 12.9 + 5.8.
+template <int MODE, bool PTR, typename FIN>
 __global__ __launch_bounds__(256) void k_grad_redo(DescPtrs d, int64_t n,
                                                     const float* __restrict__ wv, Set sv,
-                                                    const Set* __restrict__ sp,
+                                                    const Set* sp,
                                                     const uint64_t* __restrict__ flags,
                                                     const double* __restrict__ rows1, int nrows1,
-                                                    double* __restrict__ rows2)
+                                                    double* rows2, uint32_t* ticket, FIN fin)
 {
-    __shared__ double red[16 * kAcc];
+    __shared__ double red[4 * kAcc], part[kRowGroups * kAcc], tot[kAcc];
+    __shared__ int64_t queue[4][kFlagQueue];
     const Set& S = PTR ? *sp : sv;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const typename FIN::Ahead ahead = fin.ahead();
+    const FlagWalk walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
+    column_parts<false, 4>(rows1, nrows1, (int)blockIdx.x, (int)gridDim.x, kAcc, part);
     double acc[kAcc];
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    for (int r = blockIdx.x + gridDim.x * threadIdx.x; r < nrows1; r += gridDim.x * blockDim.x) {
-#pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] += rows1[(int64_t)r * kAcc + j];
-    }
-    const int64_t nwords = (n + 63) >> 6;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t wi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; wi < nwords; wi += stride) {
-        uint64_t m = flags[wi];
-        while (m) {
-            const int bit = __builtin_ctzll(m);
-            m &= m - 1;
-            const int64_t i = (wi << 6) + bit;
-            grad_exact<MODE>(S, load_desc(d, i), wv[i], acc);
-        }
-    }
-    block_reduce_acc(acc, red, rows2 + (int64_t)blockIdx.x * kAcc);
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ partials, int rows,
-                                                 double* __restrict__ out)
-{
-    __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
-    reduce_partials(partials, rows, kAcc, red, tot);
-    if (threadIdx.x < kAcc) {
-        if (MODE == 1) {
-            const double c = tot[1];
-            const double v = tot[threadIdx.x];
-            out[threadIdx.x] = (threadIdx.x == 1 || c == 0.0) ? v : v / c;
-        } else if (threadIdx.x >= 2) {
-            out[threadIdx.x - 2] = tot[threadIdx.x];
-        }
-    }
-}
-
-hipError_t launch_reduce(int mode, const double* partials, int rows, double* out, hipStream_t stream)
-{
-    if (mode == 1) k_reduce<1><<<1, 256, 0, stream>>>(partials, rows, out);
-    else k_reduce<0><<<1, 256, 0, stream>>>(partials, rows, out);
-    return hipGetLastError();
+    for_flagged(walk, queue[wid], [&](int64_t i) { grad_exact<MODE>(S, load_desc(d, i), wv[i], acc); });
+    const double t = block_reduce_value(acc, red);
+    if (finish_rows(t, part, rows2, kAcc, ticket, tot)) fin(tot, ahead);
 }
 
 // The exact variant: float64 sweep (k_grad<MODE, false, 256, true>), the
-// row fold of the float64 pass (no flags are set), the fixed-order reduce.
+// row fold of the float64 pass (no flags are set) and its end.
 template <int MODE>
 static void launch_grad_exact_t(const DescPtrs& d, int64_t n, const float* w, const Set& S, double* partials,
                                 uint64_t* flags, const GradLayout& L, int grid_mult, double* out,
@@ -324,10 +319,10 @@ static void launch_grad_exact_t(const DescPtrs& d, int64_t n, const float* w, co
     nb = nb < want ? nb : want;
     nb = nb < L.nb ? nb : L.nb;
     nb = nb < 1 ? 1 : nb;
-    k_grad<MODE, false, 256, true><<<(int)nb, 256, 0, stream>>>(d, n, w, S, nullptr, partials, flags);
-    k_grad_redo<MODE, false><<<L.nb2, 256, 0, stream>>>(d, n, w, S, nullptr, flags, partials, (int)nb,
-                                                        partials + nb * kAcc);
-    if (out) k_reduce<MODE><<<1, 256, 0, stream>>>(partials + nb * kAcc, L.nb2, out);
+    const RedoLayout r = redo_layout(L, (int)nb, partials);
+    k_grad<MODE, false, 256, true><<<(int)nb, 256, 0, stream>>>(d, n, w, S, nullptr, partials, flags, r.ticket);
+    k_grad_redo<MODE, false><<<r.nb2, 256, 0, stream>>>(d, n, w, S, nullptr, flags, partials, (int)nb,
+                                                        partials + nb * kAcc, r.ticket, FinishOut<MODE>{out});
 }
 
 hipError_t launch_grad_exact(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S,
@@ -402,76 +397,47 @@ int grad_grid(int mode, bool ptr, int64_t n, const LaunchCfg& c)
     return ptr ? grad_grid_b<0, true>(n, c) : grad_grid_b<0, false>(n, c);
 }
 
-template <int MODE, bool PTR>
-static bool launch_grad_t(const DescPtrs& d, int64_t n, const float* w, const Set& S,
-                          const Set* S_dev, double* partials, uint64_t* flags, int nb,
-                          const GradLayout& L, const LaunchCfg& c, hipStream_t stream)
+template <int MODE, bool PTR, typename FIN>
+static bool launch_grad_t(const DescPtrs& d, int64_t n, const float* w, const Set& S, const Set* S_dev,
+                          double* partials, uint64_t* flags, const GradLayout& L, const LaunchCfg& c,
+                          const FIN& fin, hipStream_t stream)
 {
+    const int nb = grad_grid(MODE, PTR, n, c);
+    const RedoLayout r = redo_layout(L, nb, partials);
+#define WM_GRAD_CASE(B)                                                                                   \
+    case B:                                                                                               \
+        k_grad<MODE, PTR, B><<<nb, B, 0, stream>>>(d, n, w, S, S_dev, partials, flags, r.ticket);         \
+        break;
     switch (c.block) {
-    case 64: k_grad<MODE, PTR, 64><<<nb, 64, 0, stream>>>(d, n, w, S, S_dev, partials, flags); break;
-    case 128: k_grad<MODE, PTR, 128><<<nb, 128, 0, stream>>>(d, n, w, S, S_dev, partials, flags); break;
-    case 256: k_grad<MODE, PTR, 256><<<nb, 256, 0, stream>>>(d, n, w, S, S_dev, partials, flags); break;
-    case 512: k_grad<MODE, PTR, 512><<<nb, 512, 0, stream>>>(d, n, w, S, S_dev, partials, flags); break;
+        WM_GRAD_CASE(64)
+        WM_GRAD_CASE(128)
+        WM_GRAD_CASE(256)
+        WM_GRAD_CASE(512)
     default: return false;
     }
-    k_grad_redo<MODE, PTR><<<L.nb2, 256, 0, stream>>>(d, n, w, S, S_dev, flags, partials, nb,
-                                                       partials + (int64_t)nb * kAcc);
+#undef WM_GRAD_CASE
+    k_grad_redo<MODE, PTR><<<r.nb2, 256, 0, stream>>>(d, n, w, S, S_dev, flags, partials, nb,
+                                                      partials + (int64_t)nb * kAcc, r.ticket, fin);
     return true;
 }
 
-hipError_t launch_grad(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S,
-                       const Set* S_dev, double* partials, uint64_t* flags, const GradLayout& L,
-                       const LaunchCfg& c, double* out, hipStream_t stream)
+hipError_t launch_grad(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S, double* partials,
+                       uint64_t* flags, const GradLayout& L, const LaunchCfg& c, double* out, hipStream_t stream)
 {
-    const int nb = grad_grid(mode, S_dev != nullptr, n, c);
-    bool ok;
-    if (mode == 1)
-        ok = S_dev ? launch_grad_t<1, true>(d, n, w, S, S_dev, partials, flags, nb, L, c, stream)
-                   : launch_grad_t<1, false>(d, n, w, S, S_dev, partials, flags, nb, L, c, stream);
-    else
-        ok = S_dev ? launch_grad_t<0, true>(d, n, w, S, S_dev, partials, flags, nb, L, c, stream)
-                   : launch_grad_t<0, false>(d, n, w, S, S_dev, partials, flags, nb, L, c, stream);
-    if (!ok) return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !out) return e;
-    if (mode == 1)
-        k_reduce<1><<<1, 256, 0, stream>>>(partials + (int64_t)nb * kAcc, L.nb2, out);
-    else
-        k_reduce<0><<<1, 256, 0, stream>>>(partials + (int64_t)nb * kAcc, L.nb2, out);
-    return hipGetLastError();
+    const bool ok = mode == 1 ? launch_grad_t<1, false>(d, n, w, S, nullptr, partials, flags, L, c,
+                                                        FinishOut<1>{out}, stream)
+                              : launch_grad_t<0, false>(d, n, w, S, nullptr, partials, flags, L, c,
+                                                        FinishOut<0>{out}, stream);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-// ---------------------------------------------------------------------------
-// device Adam on log(theta)
-// ---------------------------------------------------------------------------
-__device__ inline void adam_update(CalibState* st, const double* tot, const AdamOpts& o, Set* S,
-                                   double* loss_hist)
+hipError_t launch_grad_adam(const DescPtrs& d, int64_t n, const float* meas, const GradLayout& L, const LaunchCfg& c,
+                            double* partials, uint64_t* flags, CalibState* st, const AdamOpts& o, Set* S,
+                            double* loss_hist, hipStream_t stream)
 {
-    __shared__ double th[kTheta];
-    if (threadIdx.x >= 64) return;
-    // one group of constants per lane, from the new theta in LDS
-    if (adam_theta_step(st, tot, o, loss_hist, th) && threadIdx.x < kConstFields) {
-        const_field<float>(th, S->st, S->cf, threadIdx.x);
-        const_field<double>(th, S->st, S->cd, threadIdx.x);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_adam(const double* __restrict__ partials, int rows,
-                                               CalibState* st, AdamOpts o, Set* S,
-                                               double* loss_hist)
-{
-    __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
-    reduce_partials(partials, rows, kAcc, red, tot);
-    adam_update(st, tot, o, S, loss_hist);
-}
-
-hipError_t launch_adam(const double* partials, int rows, CalibState* st, const AdamOpts& o, Set* S,
-                       double* loss_hist, hipStream_t stream)
-{
-    // one wave when it holds every row (no cross-wave steps in the reduction)
-    k_adam<<<1, rows <= 64 ? 64 : 256, 0, stream>>>(partials, rows, st, o, S, loss_hist);
-    return hipGetLastError();
+    const bool ok = launch_grad_t<1, true>(d, n, meas, Set{}, S, partials, flags, L, c,
+                                           FinishAdam{st, o, S, loss_hist}, stream);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
@@ -485,11 +451,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const Set* __restrict__ S_all, const int32_t* __restrict__ item_off, int n_items,
     int64_t chunk, int n_sets, const int64_t* __restrict__ set_n,
     const int64_t* __restrict__ flag_off, uint64_t* __restrict__ flags,
-    double* __restrict__ partials)
+    double* __restrict__ partials, uint32_t* __restrict__ tickets)
 {
     __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
     __shared__ double per_set[kMaxSets * kAcc];
+    if (tickets && blockIdx.x == 0 && (int)threadIdx.x < n_sets) tickets[threadIdx.x] = 0u;
     for (int j = threadIdx.x; j < n_sets * kAcc; j += blockDim.x) per_set[j] = 0.0;
     __syncthreads();
     const int b = blockIdx.x, nb = gridDim.x;
@@ -522,8 +488,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         double a64[kAcc];
 #pragma unroll
         for (int j = 0; j < kAcc; ++j) a64[j] = (double)acc[j];
-        block_reduce_acc(a64, red, tot);
-        if (threadIdx.x < kAcc) per_set[k * kAcc + threadIdx.x] = tot[threadIdx.x];
+        const double t = block_reduce_value(a64, red);
+        if (threadIdx.x < kAcc) per_set[k * kAcc + threadIdx.x] = t;
     }
     __syncthreads();
     for (int j = threadIdx.x; j < n_sets * kAcc; j += blockDim.x)
@@ -532,62 +498,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // Phase 2, block (b, s) for set s = blockIdx.y, so the sets' float64
 // re-evaluations run side by side: fold the phase-1 rows b, b + nb2, ... of
-// the set (fixed order), then re-evaluate its flagged descriptors in the
-// block's share of the flag words.
+// the set (fixed order), re-evaluate its flagged descriptors in the block's
+// share of the flag words; the set's last block sums its rows and takes its
+// Adam step.
 __global__ __launch_bounds__(256) void k_grad_redo_batched(const DescPtrs* __restrict__ sets,
                                                             const float* const* __restrict__ meas,
-                                                            const Set* __restrict__ S_all,
+                                                            Set* S_all,
                                                             const int64_t* __restrict__ set_n,
                                                             const int64_t* __restrict__ flag_off,
                                                             const uint64_t* __restrict__ flags,
                                                             int n_sets,
                                                             const double* __restrict__ rows1,
-                                                            int nrows1,
-                                                            double* __restrict__ partials)
+                                                            int nrows1, double* rows2, uint32_t* tickets,
+                                                            CalibState* st, const AdamOpts* __restrict__ opts,
+                                                            int steps, double* loss_hist)
 {
-    __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    __shared__ double red[4 * kAcc], part[kRowGroups * kAcc], tot[kAcc];
+    __shared__ int64_t queue[4][kFlagQueue];
     const int s = blockIdx.y;
-    if (s >= n_sets) return;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const AdamLane ahead(st + s, opts[s]);
+    const FlagWalk walk(flags + flag_off[s], (set_n[s] + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64,
+                        (int64_t)gridDim.x * 256);
+    const int64_t stride = (int64_t)n_sets * kAcc;   // between a set's rows
+    column_parts<false, 4>(rows1 + (int64_t)s * kAcc, nrows1, (int)blockIdx.x, (int)gridDim.x, stride, part);
     double acc[kAcc];
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    for (int r = blockIdx.x + gridDim.x * threadIdx.x; r < nrows1; r += gridDim.x * blockDim.x) {
-        const double* row = rows1 + ((int64_t)r * n_sets + s) * kAcc;
-#pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] += row[j];
-    }
     const DescPtrs d = sets[s];
     const float* m = meas[s];
     const Set& S = S_all[s];
-    const uint64_t* fl = flags + flag_off[s];
-    const int64_t nwords = (set_n[s] + 63) >> 6;
-    for (int64_t wi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; wi < nwords; wi += stride) {
-        uint64_t mk = fl[wi];
-        while (mk) {
-            const int bit = __builtin_ctzll(mk);
-            mk &= mk - 1;
-            const int64_t i = (wi << 6) + bit;
-            grad_exact<1>(S, load_desc(d, i), m[i], acc);
-        }
-    }
-    block_reduce_acc(acc, red, tot);
-    if (threadIdx.x < kAcc)
-        partials[((int64_t)blockIdx.x * n_sets + s) * kAcc + threadIdx.x] = tot[threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void k_adam_batched(const double* __restrict__ partials, int rows,
-                                                       int n_sets, CalibState* st,
-                                                       const AdamOpts* __restrict__ opts,
-                                                       Set* S_all, int steps, double* loss_hist)
-{
-    __shared__ double red[16 * kAcc];
-    __shared__ double tot[kAcc];
-    const int s = blockIdx.x;
-    reduce_partials(partials + s * kAcc, rows, n_sets * kAcc, red, tot);
-    adam_update(st + s, tot, opts[s], S_all + s,
-                loss_hist ? loss_hist + (int64_t)s * steps : nullptr);
+    for_flagged(walk, queue[wid], [&](int64_t i) { grad_exact<1>(S, load_desc(d, i), m[i], acc); });
+    const double t = block_reduce_value(acc, red);
+    if (!finish_rows(t, part, rows2 + (int64_t)s * kAcc, stride, tickets + s, tot)) return;
+    adam_update(st + s, ahead, tot, opts[s], S_all + s, loss_hist ? loss_hist + (int64_t)s * steps : nullptr);
 }
 
 int batched_grid(int n_items, int grid_mult)
@@ -611,25 +555,17 @@ int batched_redo_grid(int n_sets, int64_t max_set_words, int cap)
     return per < 1 ? 1 : per;
 }
 
-hipError_t launch_grad_batched(const DescPtrs* sets, const float* const* meas, const Set* S_all,
+hipError_t launch_batched_step(const DescPtrs* sets, const float* const* meas, Set* S_all,
                                const int32_t* item_off, int n_items, int64_t chunk, int n_sets,
                                const int64_t* set_n, const int64_t* flag_off, uint64_t* flags,
-                               double* partials, int nb, int nb2, hipStream_t stream)
+                               double* partials, int nb, int nb2, uint32_t* tickets, CalibState* st,
+                               const AdamOpts* opts, int steps, double* loss_hist, hipStream_t stream)
 {
     k_grad_batched<<<nb, 256, 0, stream>>>(sets, meas, S_all, item_off, n_items, chunk, n_sets,
-                                           set_n, flag_off, flags, partials);
-    k_grad_redo_batched<<<dim3(nb2, n_sets), 256, 0, stream>>>(sets, meas, S_all, set_n, flag_off, flags, n_sets,
-                                                 partials, nb,
-                                                 partials + (int64_t)nb * n_sets * kAcc);
-    return hipGetLastError();
-}
-
-hipError_t launch_adam_batched(const double* partials, int rows, int n_sets, CalibState* st,
-                               const AdamOpts* opts, Set* S_all, int steps, double* loss_hist,
-                               hipStream_t stream)
-{
-    k_adam_batched<<<n_sets, 256, 0, stream>>>(partials, rows, n_sets, st, opts, S_all, steps,
-                                                loss_hist);
+                                           set_n, flag_off, flags, partials, tickets);
+    k_grad_redo_batched<<<dim3(nb2, n_sets), 256, 0, stream>>>(
+        sets, meas, S_all, set_n, flag_off, flags, n_sets, partials, nb, partials + (int64_t)nb * n_sets * kAcc,
+        tickets, st, opts, steps, loss_hist);
     return hipGetLastError();
 }
 

@@ -122,6 +122,22 @@ int32_t record_hip_error(hipError_t e);
 // argument check of the gradient calls (wm_predict_vjp, wm_loss_grad): a
 // valid descriptor set and parameter set, an output, weights unless n = 0
 bool grad_args_ok(const wm_desc_t* desc, const float* w, const wm_params_t* params, const double* out);
+// The float64 pass of a gradient call whose sweep launched nb of its L.nb
+// blocks: its blocks, and the row slot behind its rows where the count of
+// finished blocks is kept (cleared by the sweep).  With every row slot taken
+// the pass runs one block less; a single block needs no count.
+struct RedoLayout {
+    int nb2;
+    uint32_t* ticket;
+};
+inline RedoLayout redo_layout(const GradLayout& L, int nb, double* partials)
+{
+    RedoLayout r;
+    const int room = L.nb + L.nb2 - nb - 1;
+    r.nb2 = L.nb2 > 1 && room < L.nb2 ? room : L.nb2;
+    r.ticket = r.nb2 > 1 ? (uint32_t*)(partials + (int64_t)(nb + r.nb2) * kAcc) : nullptr;
+    return r;
+}
 // phase-1 blocks actually launched (<= grad_layout(n).nb): the blocks
 // resident at once on the current device times cfg.grid_mult, so partial
 // rows = that + nb2
@@ -139,32 +155,31 @@ hipError_t launch_predict(const DescPtrs& d, int64_t n, const Set& S, float* T, 
 hipError_t launch_roofline(const DescPtrs& d, int64_t n, const Set& S, float* T,
                            hipStream_t stream);
 // mode 0: weights are dL/dT, out = dL/dtheta[24]; mode 1: weights are measured
-// times, out = [loss, count, grad[24]].  S_dev != nullptr reads the set from
-// device memory (graph replay with a changing theta).  out == nullptr skips
-// the final reduction.
-hipError_t launch_grad(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S,
-                       const Set* S_dev, double* partials, uint64_t* flags, const GradLayout& L,
-                       const LaunchCfg& cfg, double* out, hipStream_t stream);
+// times, out = [loss, count, grad[24]].  Two launches: the sweep, and the
+// float64 pass whose last block forms the result.
+hipError_t launch_grad(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S, double* partials,
+                       uint64_t* flags, const GradLayout& L, const LaunchCfg& cfg, double* out,
+                       hipStream_t stream);
+// One calibration step: launch_grad's mode 1 over the device-resident set S
+// (graph replay with a changing theta), ending in the Adam update of st and S.
+hipError_t launch_grad_adam(const DescPtrs& d, int64_t n, const float* meas, const GradLayout& L, const LaunchCfg& cfg,
+                            double* partials, uint64_t* flags, CalibState* st, const AdamOpts& o, Set* S,
+                            double* loss_hist, hipStream_t stream);
 // The exact variant of launch_grad: every descriptor evaluated and
 // differentiated in float64 (persistent grid of resident blocks x grid_mult).
 hipError_t launch_grad_exact(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S,
                              double* partials, uint64_t* flags, const GradLayout& L, int grid_mult,
                              double* out, hipStream_t stream);
-// Fixed-order reduction of `rows` partial rows of 26 doubles: mode 0 writes
-// the 24 gradient sums, mode 1 [loss, count, grad[24]] divided by the count.
-hipError_t launch_reduce(int mode, const double* partials, int rows, double* out, hipStream_t stream);
-hipError_t launch_adam(const double* partials, int rows, CalibState* st, const AdamOpts& o, Set* S,
-                       double* loss_hist, hipStream_t stream);
 // Multi-set step: the work is n_items items of `chunk` descriptors (the
 // last item of a set may be short); set k owns items item_off[k] ..
-// item_off[k + 1] - 1 (device int32 [n_sets + 1]).
-hipError_t launch_grad_batched(const DescPtrs* sets, const float* const* meas, const Set* S_all,
+// item_off[k + 1] - 1 (device int32 [n_sets + 1]).  The sweep, then the sets'
+// float64 passes (nb2 <= 256 blocks each), each ending in its Adam step.
+// tickets: n_sets counts of finished blocks (nullptr when nb2 is 1).
+hipError_t launch_batched_step(const DescPtrs* sets, const float* const* meas, Set* S_all,
                                const int32_t* item_off, int n_items, int64_t chunk, int n_sets,
                                const int64_t* set_n, const int64_t* flag_off, uint64_t* flags,
-                               double* partials, int nb, int nb2, hipStream_t stream);
-hipError_t launch_adam_batched(const double* partials, int rows, int n_sets, CalibState* st,
-                               const AdamOpts* opts, Set* S_all, int steps, double* loss_hist,
-                               hipStream_t stream);
+                               double* partials, int nb, int nb2, uint32_t* tickets, CalibState* st,
+                               const AdamOpts* opts, int steps, double* loss_hist, hipStream_t stream);
 // Application totals (and, if T_seg != nullptr, segment times) in float32.
 hipError_t launch_predict_apps(const DescPtrs& d, const SegPtrs& sg, int64_t n_seg, int64_t n_apps,
                                const Set& S, const SegSet& Q, float* T_app, float* T_seg,

@@ -80,16 +80,6 @@ __device__ inline uint64_t shfl_xor_u64(uint64_t v, int m)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Orders this wave's LDS stores before its later LDS loads from other lanes
-// (the LDS executes one wave's operations in issue order; the fences keep
-// the compiler from moving accesses across this point).
-__device__ inline void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // float64 minimum, its lowest local index and the second-smallest value of
 // a multiset, accumulated in candidate order (exact ties keep the first)
 struct Best2 {
@@ -145,11 +135,6 @@ struct TileQueue {
     double cost[kTileQueue];
     unsigned long long bmin[kTileBatch];   // packed float32 minimum per batch shape
 };
-
-__device__ inline uint32_t lanes_below(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 // first entry in [0, qn) whose slot is >= sl
 __device__ inline int first_entry(const TileQueue& q, int qn, uint32_t sl)

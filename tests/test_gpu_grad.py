@@ -179,3 +179,36 @@ def test_exact_variants_match_the_oracle_slot_by_slot(wmb, orc, L, combine):
     gv = wmb.vjp(dd, ps, torch.from_numpy(w).cuda(), exact=True).cpu().numpy()
     check_grad(gv, orc.vjp(ps, d, w), ps.theta, f"exact vjp, L={L} combine={combine}", 1e-9,
                names=synth.THETA_NAMES)
+
+
+@pytest.mark.parametrize("n,block", [(1, 256), (64, 256), (960, 64), (16384, 64), (16448, 64), (20037, 128),
+                                     (70001, 256), (131072, 64)])
+def test_float64_pass_flags_and_row_slots(wmb, orc, n, block):
+    """Every descriptor flagged (measured = the float64 time rounded to
+    float32), so that the float64 pass's row queues overflow and refill, at
+    its block-count edges (one block up to 16384 descriptors; block 64 with 960
+    and 131072 leaves no row slot unused); nothing is written past the
+    workspace.  All terms are float64: 1e-11 of each slot's absolute sum
+    (a few thousand float64 roundings), and the loss, |T - m| / m ~ 1e-8
+    formed from T to 1e-15, to 1e-13 absolute."""
+    p = synth.param_set(6)
+    d = synth.descriptors(n, 105)
+    T, _ = orc.predict(p, d)
+    m = np.where(np.isfinite(T), T, 1.0).astype(np.float32)
+    loss, cnt, g = orc.loss_grad(p, d, m)
+    absum = loss_grad_absum(orc, p, d, m)
+    dd = wmb.DeviceDescriptors.from_host(d)
+    need = wmb.workspace_bytes(wmb.OP_LOSS_GRAD, n)
+    raw = torch.full((need + 512,), 0xAB, dtype=torch.uint8, device="cuda")
+    off = (-raw.data_ptr()) % 256
+    default = wmb.get_launch(wmb.OP_LOSS_GRAD, n)
+    wmb.set_launch(wmb.OP_LOSS_GRAD, n, block, default["per_thread"], 8)
+    try:
+        say("float64 pass", n, block)
+        out = wmb.loss_grad(dd, torch.from_numpy(m).cuda(), p, ws=raw[off:off + need]).cpu().numpy()
+    finally:
+        wmb.set_launch(wmb.OP_LOSS_GRAD, n, default["block"], default["per_thread"], default["grid_mult"])
+    assert np.all(raw[off + need:].cpu().numpy() == 0xAB)
+    assert int(out[1]) == cnt
+    assert abs(out[0] - loss) <= 1e-13
+    assert np.all(np.abs(out[2:] - g) * np.abs(p.theta) <= 1e-11 * absum + 1e-300)
