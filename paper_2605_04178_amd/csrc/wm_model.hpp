@@ -237,16 +237,25 @@ struct Eval {
     bool near_kink;    // within 1e-5 relative of a max/min switch
 };
 
-// TILE: the descriptor comes from derive_tile, so it is valid by
-// construction and has r1 = r3 = 0, W = 0, u = 1 and no concurrency, device,
-// fusion or sync counts; the terms those zeros and ones cancel are skipped.
-template <typename R, bool FULL, bool TILE = false>
+// What is known of a descriptor before it is evaluated.  kTile: it comes from
+// derive_tile, so it is valid by construction and has r1 = r3 = 0, W = 0, u = 1
+// and no concurrency, device, fusion or sync counts; the terms those zeros and
+// ones cancel are skipped.  kFused: it combines valid rows, so its integers
+// and hit rates are in range and only sums and quotients can leave theirs.
+enum Known { kNothing, kTile, kFused };
+template <typename R, bool FULL, Known KNOWN = kNothing>
 __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<R>& d, Eval<R>& E)
 {
     typedef Ar<R> A;
+    constexpr bool TILE = KNOWN == kTile;
     E.T = (R)__builtin_nan("");
     E.occ = -1;
-    if (!TILE && !desc_valid(d)) return;
+    if (KNOWN == kNothing && !desc_valid(d)) return;
+    if (KNOWN == kFused) {
+        const bool fF = finite_nonneg(d.F), fB = finite_nonneg(d.B), fK = finite_nonneg(d.K), fW = finite_nonneg(d.W);
+        const bool ok = fF & fB & fK & fW & (d.u > (R)0);
+        if (!ok) return;
+    }
     const int32_t g = d.gp & 2047;
     const int32_t dt = (d.gp >> 11) & 7;
     E.dt = dt;

@@ -12,9 +12,9 @@
 // and bytes plus tau_fusion): a chain of kernels is cut into runs of at most
 // R consecutive kernels.  One thread per row extends the fusion sums of the
 // runs starting there one row at a time (float64 sums) and evaluates each
-// run's combined descriptor in float32; one thread per chain runs the prefix
-// dynamic programme over those costs in float64.  Chains where float32 could
-// decide differently from float64 (a decision within a small relative
+// run's combined descriptor in float32; a group of lanes per chain runs the
+// prefix dynamic programme over those costs in float64.  Chains where float32
+// could decide differently from float64 (a decision within a small relative
 // margin, or a run float32 cannot represent) are redone in float64, one wave
 // per chain, so plans match a float64 evaluation except at its own ties.
 #include "wm_device.hpp"
@@ -30,10 +30,10 @@ __device__ inline bool mult_ok(float T, float m)
     return __builtin_amdgcn_classf(T, 0x180) & __builtin_amdgcn_classf(m, 0x180);
 }
 
-// 1 / d for a positive double in float32's range, two Newton steps from the
-// hardware estimate, and n / d from it with one remainder step: the sequence
-// of an IEEE division without its scaling and special cases, which quotients
-// of two float32 values (2^-278 .. 2^278) do not need.
+// 1 / d for a positive double, two Newton steps from the hardware estimate,
+// and n / d from it with one remainder step: the sequence of an IEEE division
+// without its scaling and special cases, which operands and quotients made of
+// a few float32 values (2^-278 .. 2^278) do not need.  d = 0 or infinity: NaN.
 __device__ inline double recip_f32range(double d)
 {
     double y = __builtin_amdgcn_rcp(d);
@@ -644,20 +644,63 @@ __device__ inline Desc<float> load_row(const DescPtrs& d, int64_t i)
     return x;
 }
 
-// The combined descriptor of rows a .. a+len-1 (len >= 2), float64:
+// The float64 sums and integer maxima of a run of rows.
+struct FuseSum {
+    double F = 0.0, Bs = 0.0, E = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0, K = 0.0, Ws = 0.0, tc = 0.0, Fmax = -1.0;
+    int32_t v = 0, s = 0, g = 0, G = 0, nc = 0, nd = 0, ns = 0, dt = 0;
+};
+
+__device__ inline void fuse_ints(FuseSum& a, double F, int32_t v, int32_t s, int32_t gp, int32_t G)
+{
+    if (F > a.Fmax) {
+        a.Fmax = F;
+        a.dt = (gp >> 11) & 7;
+    }
+    a.v = v > a.v ? v : a.v;
+    a.s = s > a.s ? s : a.s;
+    a.g = (gp & 2047) > a.g ? (gp & 2047) : a.g;
+    a.G = G > a.G ? G : a.G;
+    a.nc = ((gp >> 14) & 7) > a.nc ? ((gp >> 14) & 7) : a.nc;
+    a.nd = ((gp >> 17) & 7) > a.nd ? ((gp >> 17) & 7) : a.nd;
+    a.ns += (gp >> 21) & 15;
+}
+
+// The combined descriptor of a run (two or more rows) from its sums, float64:
 //   F = sum F;  B = max(sum B - 2 sum edges, 0);  r_l byte-weighted;
 //   K = sum K;  W = max(sum W - sum edges, 0);  dtype of the first row with
 //   the largest F;  u keeps the summed compute time F_k / (u_k P_k) (capped
 //   at 1, 1 when F = 0);  VGPRs, LDS, workgroup size, grid, concurrent
 //   kernels and devices the largest;  host syncs summed (<= 15);  fused.
-// Returns false if a row or an edge is invalid.
+__device__ inline void fuse_form(const FuseSum& a, const double* peak, Desc<double>& o)
+{
+#pragma clang fp contract(off)
+    o.F = a.F;
+    o.B = a.Bs - 2.0 * a.E > 0.0 ? a.Bs - 2.0 * a.E : 0.0;
+    o.r1 = a.Bs > 0.0 ? a.r1 / a.Bs : 0.0;
+    o.r2 = a.Bs > 0.0 ? a.r2 / a.Bs : 0.0;
+    o.r3 = a.Bs > 0.0 ? a.r3 / a.Bs : 0.0;
+    o.K = a.K;
+    o.W = a.Ws - a.E > 0.0 ? a.Ws - a.E : 0.0;
+    if (a.F > 0.0) {
+        const double u = a.F / (peak[a.dt] * a.tc);
+        o.u = u < 1.0 ? u : 1.0;
+    } else {
+        o.u = 1.0;
+    }
+    o.v = a.v;
+    o.s = a.s;
+    o.G = a.G;
+    const int32_t ns = a.ns < 15 ? a.ns : 15;
+    o.gp = a.g | (a.dt << 11) | (a.nc << 14) | (a.nd << 17) | (1 << 20) | (ns << 21);
+}
+
+// The combined descriptor of rows a .. a+len-1 (len >= 2).  Returns false if a
+// row or an edge is invalid.
 __device__ inline bool fuse_rows(const DescPtrs& d, const float* __restrict__ edge,
                                  const double* peak, int64_t a, int32_t len, Desc<double>& o)
 {
 #pragma clang fp contract(off)
-    double F = 0.0, Bs = 0.0, E = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0, K = 0.0, Ws = 0.0, tc = 0.0,
-           Fmax = -1.0;
-    int32_t v = 0, s = 0, g = 0, G = 0, nc = 0, nd = 0, ns = 0, dt = 0;
+    FuseSum f;
     for (int32_t q = 0; q < len; ++q) {
         const int64_t k = a + q;
         const Desc<float> x = load_row(d, k);
@@ -665,127 +708,26 @@ __device__ inline bool fuse_rows(const DescPtrs& d, const float* __restrict__ ed
         if (q < len - 1) {
             const float ek = edge[k];
             if (!(ek >= 0.0f && ek < __builtin_huge_valf())) return false;
-            E += (double)ek;
+            f.E += (double)ek;
         }
         const double Fk = x.F, Bk = x.B;
-        const int32_t dtk = (x.gp >> 11) & 7;
-        F += Fk;
-        Bs += Bk;
-        r1 += (double)x.r1 * Bk;
-        r2 += (double)x.r2 * Bk;
-        r3 += (double)x.r3 * Bk;
-        K += (double)x.K;
-        Ws += (double)x.W;
-        if (Fk > 0.0) tc += Fk / ((double)x.u * peak[dtk]);
-        if (Fk > Fmax) {
-            Fmax = Fk;
-            dt = dtk;
-        }
-        v = x.v > v ? x.v : v;
-        s = x.s > s ? x.s : s;
-        g = (x.gp & 2047) > g ? (x.gp & 2047) : g;
-        G = x.G > G ? x.G : G;
-        nc = ((x.gp >> 14) & 7) > nc ? ((x.gp >> 14) & 7) : nc;
-        nd = ((x.gp >> 17) & 7) > nd ? ((x.gp >> 17) & 7) : nd;
-        ns += (x.gp >> 21) & 15;
+        f.F += Fk;
+        f.Bs += Bk;
+        f.r1 += (double)x.r1 * Bk;
+        f.r2 += (double)x.r2 * Bk;
+        f.r3 += (double)x.r3 * Bk;
+        f.K += (double)x.K;
+        f.Ws += (double)x.W;
+        if (Fk > 0.0) f.tc += Fk / ((double)x.u * peak[(x.gp >> 11) & 7]);
+        fuse_ints(f, Fk, x.v, x.s, x.gp, x.G);
     }
-    o.F = F;
-    o.B = Bs - 2.0 * E > 0.0 ? Bs - 2.0 * E : 0.0;
-    o.r1 = Bs > 0.0 ? r1 / Bs : 0.0;
-    o.r2 = Bs > 0.0 ? r2 / Bs : 0.0;
-    o.r3 = Bs > 0.0 ? r3 / Bs : 0.0;
-    o.K = K;
-    o.W = Ws - E > 0.0 ? Ws - E : 0.0;
-    if (F > 0.0) {
-        const double u = F / (peak[dt] * tc);
-        o.u = u < 1.0 ? u : 1.0;
-    } else {
-        o.u = 1.0;
-    }
-    o.v = v;
-    o.s = s;
-    o.G = G;
-    ns = ns < 15 ? ns : 15;
-    o.gp = g | (dt << 11) | (nc << 14) | (nd << 17) | (1 << 20) | (ns << 21);
+    fuse_form(f, peak, o);
     return true;
 }
 
 struct Peaks {
     double p[5];
 };
-
-// Running float64 sums of a run of rows, extended one row at a time in row
-// order (the order fuse_rows adds them in, so a run's sums are the same).
-struct FuseSum {
-    double F, Bs, E, r1, r2, r3, K, Ws, tc;
-    float Fmax;
-    int32_t v, s, g, G, nc, nd, ns, dt;
-};
-
-__device__ inline void fuse_begin(FuseSum& a)
-{
-    a.F = a.Bs = a.E = a.r1 = a.r2 = a.r3 = a.K = a.Ws = a.tc = 0.0;
-    a.Fmax = -1.0f;
-    a.v = a.s = a.g = a.G = a.nc = a.nd = a.ns = a.dt = 0;
-}
-
-// Adds row x; tk = its compute time F / (u P_dtype) (float32, only summed).
-__device__ inline void fuse_add(FuseSum& a, const Desc<float>& x, float tk)
-{
-#pragma clang fp contract(off)
-    const double Bk = x.B;
-    const int32_t gp = x.gp;
-    const int32_t dtk = (gp >> 11) & 7;
-    a.F += (double)x.F;
-    a.Bs += Bk;
-    a.r1 += (double)x.r1 * Bk;
-    a.r2 += (double)x.r2 * Bk;
-    a.r3 += (double)x.r3 * Bk;
-    a.K += (double)x.K;
-    a.Ws += (double)x.W;
-    if (x.F > 0.0f) a.tc += (double)tk;
-    if (x.F > a.Fmax) {
-        a.Fmax = x.F;
-        a.dt = dtk;
-    }
-    a.v = x.v > a.v ? x.v : a.v;
-    a.s = x.s > a.s ? x.s : a.s;
-    a.g = (gp & 2047) > a.g ? (gp & 2047) : a.g;
-    a.G = x.G > a.G ? x.G : a.G;
-    a.nc = ((gp >> 14) & 7) > a.nc ? ((gp >> 14) & 7) : a.nc;
-    a.nd = ((gp >> 17) & 7) > a.nd ? ((gp >> 17) & 7) : a.nd;
-    a.ns += (gp >> 21) & 15;
-}
-
-// The fused descriptor of the run so far (two or more rows), formed in
-// float64 as fuse_rows does and rounded to float32; Wd gets the float64
-// working set.
-__device__ inline Desc<float> fuse_narrow(const FuseSum& a, double peak_dt, double& Wd)
-{
-#pragma clang fp contract(off)
-    Desc<float> o;
-    o.F = (float)a.F;
-    o.B = (float)(a.Bs - 2.0 * a.E > 0.0 ? a.Bs - 2.0 * a.E : 0.0);
-    const double iB = a.Bs > 0.0 ? 1.0 / a.Bs : 0.0;
-    o.r1 = (float)(a.r1 * iB);
-    o.r2 = (float)(a.r2 * iB);
-    o.r3 = (float)(a.r3 * iB);
-    o.K = (float)a.K;
-    Wd = a.Ws - a.E > 0.0 ? a.Ws - a.E : 0.0;
-    o.W = (float)Wd;
-    if (a.F > 0.0) {
-        const double u = a.F / (peak_dt * a.tc);
-        o.u = (float)(u < 1.0 ? u : 1.0);
-    } else {
-        o.u = 1.0f;
-    }
-    o.v = a.v;
-    o.s = a.s;
-    o.G = a.G;
-    const int32_t ns = a.ns < 15 ? a.ns : 15;
-    o.gp = a.g | (a.dt << 11) | (a.nc << 14) | (a.nd << 17) | (1 << 20) | (ns << 21);
-    return o;
-}
 
 // Coverage byte per row: bits 0-5 the number of runs costed from the row
 // (at most 32), bit 7 set when one of them is uncertain in float32.
@@ -801,6 +743,18 @@ constexpr uint8_t kPlanUncertain = 0x80;
 // rows are valid (and the kernel is not simply infeasible), the time is
 // negative, or its working set lies within 1e-6 of the LLC capacity, where
 // the hit rate of Table "hlcc-piecewise" jumps.
+//
+// A block's 256 rows and the R - 1 behind them are loaded once, a row per
+// thread, which costs the run of one and leaves in LDS what the sums add per
+// row (bytes-weighted hit rates, compute time, validity): up to R runs hold a
+// row, and each used to load, convert, multiply, divide and test it again.
+// The chains of the block's rows are bracketed by two 64-way searches of the
+// offsets (three dependent loads for 2^16 chains; a binary search per row has
+// sixteen).
+// Bound: VALU issue (0.8 per CU-cycle; lanes wait for their wave's longest start,
+// 5.1 of 8 steps used -- ordering the block's starts by run count saved the
+// steps and lost as much to the uneven waves).  At 2^16 chains / 589 K rows, R =
+// 8: 51.2 us, 68.0 with the rows loaded, converted and tested per run.
 struct FuseArgs {   // k_fuse_costs's parameters, in order
     DescPtrs d;
     const float* edge;
@@ -815,110 +769,218 @@ struct FuseArgs {   // k_fuse_costs's parameters, in order
 constexpr int kFuseBlock = 256;   // k_fuse_costs' block: one row per thread
 constexpr int kFuseTileR = 8;     // run lengths up to this many are staged in LDS
 
+template <int ROWS>   // rows of a block's runs
+struct FuseLds {
+    double r1[ROWS], r2[ROWS], r3[ROWS];                // hit rates times bytes
+    float F[ROWS], B[ROWS], K[ROWS], W[ROWS], tc[ROWS],
+        E[ROWS];                                        // E < 0: the edge behind the row is invalid
+    int32_t v[ROWS], s[ROWS], gp[ROWS], G[ROWS];        // gp < 0: the row is invalid
+    double peak[5];
+    int64_t chain[2];   // chains of the block's first and last row
+};
+
+// A run's float32 time is uncertain.
+__device__ inline bool run_uncertain(float t, int32_t occ, double Wd, const Set& P)
+{
+    const bool fin = __builtin_isfinite(t);
+    bool unc = (!fin && occ != 0) || (fin && t < 0.0f);
+    if (P.st.n_levels == 4 && Wd > 0.0) {
+        const double c_llc = P.cd.c_llc;
+        const double dw = Wd * (1.0 / 1048576.0) - c_llc;
+        unc = unc || (dw < 0.0 ? -dw : dw) <= 1e-6 * c_llc;
+    }
+    return unc;
+}
+
+// The last chain c in [lo, hi) with at(c) <= s, given at(lo) <= s, by the
+// whole wave: 64 probes per step.
+template <typename AT>
+__device__ inline int64_t last_chain(int64_t lo, int64_t hi, int64_t s, const AT& at)
+{
+    const int lane = threadIdx.x & 63;
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + 63) >> 6;
+        const int64_t c = lo + step * lane;
+        const uint64_t m = __ballot(lane == 0 || (c < hi && at(c) <= s));
+        const int64_t at_lane = 63 - __builtin_clzll(m);
+        lo = lo + step * at_lane;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    return lo;
+}
+
+template <bool STAGED>   // R <= kFuseTileR
 __global__ __launch_bounds__(kFuseBlock) void k_fuse_costs(DescPtrs d, const float* __restrict__ edge,
                                                      const int32_t* __restrict__ off,
                                                      int64_t n_chains, int64_t n, int32_t R, Set S,
                                                      Peaks pk, PlanBufs wb)
 {
+#pragma clang fp contract(off)
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     // parameters read in place (scalar loads at each use), not held in
     // scalar registers across the run loop
     const Set* sc = WM_KERNARG_PTR(FuseArgs, S);
-    const Peaks* pc = WM_KERNARG_PTR(FuseArgs, pk);
     const int tl = threadIdx.x;
     const int64_t s0 = (int64_t)blockIdx.x * kFuseBlock;
     const int64_t s = s0 + tl;
     if (s == 0) *wb.n_redo = 0u;   // the queue of the planning pass that follows
-    // R <= kFuseTileR: the block's costs are staged in LDS and written out
+    constexpr int RMAX = STAGED ? kFuseTileR : kPlanMaxRun;
+    __shared__ FuseLds<kFuseBlock + RMAX - 1> L;
+    // STAGED: the block's costs are staged in LDS and written out
     // row by row (consecutive lanes, consecutive addresses); a lane's own
     // stores to rows s .. s + R - 1 at entry q would touch R * 8-byte pieces
     // of 64 lines each and leave the L2 as that many partial writes
-    __shared__ double tile[(kFuseBlock + kFuseTileR - 1) * kFuseTileR];
+    __shared__ float tile[STAGED ? (kFuseBlock + kFuseTileR - 1) * kFuseTileR : 1];
     __shared__ uint8_t m_s[kFuseBlock], h0_s[kFuseBlock];
-    const bool staged = R <= kFuseTileR;
+    if (tl < 5) L.peak[tl] = tl == 0 ? pk.p[0] : tl == 1 ? pk.p[1] : tl == 2 ? pk.p[2] : tl == 3 ? pk.p[3] : pk.p[4];
     // the chain holding s: the last c with off[c] <= s (offsets clamped into
     // [0, n] and non-decreasing)
     auto at = [&](int64_t c) -> int64_t {
         const int64_t v = off[c];
         return v < 0 ? 0 : (v > n ? n : v);
     };
+    const int64_t s_last = s0 + kFuseBlock <= n ? s0 + kFuseBlock - 1 : n - 1;
+    const int wid = __builtin_amdgcn_readfirstlane(tl >> 6);
+    if (wid < 2 && n > 0) {
+        const int64_t sx = wid ? s_last : s0;
+        const int64_t c = at(0) <= sx ? last_chain(0, n_chains, sx, at) : -1;
+        if ((tl & 63) == 0) L.chain[wid] = c;
+    }
+    // this thread's row, and the rows behind the block's last
+    Desc<float> x;
+    float e = 0.0f;
+    if (s < n) {
+        x = load_row(d, s);
+        e = edge[s];
+    }
+    __syncthreads();
+    const float inf = __builtin_huge_valf();
+    // row terms to LDS at position pos
+    auto stage = [&](const Desc<float>& y, float ey, int pos) -> bool {
+        const bool ok = desc_valid(y);
+        const double Bk = y.B;
+        float tk = 0.0f;
+        if (ok && y.F > 0.0f) tk = y.F / (y.u * (float)L.peak[(y.gp >> 11) & 7]);
+        L.F[pos] = y.F;
+        L.B[pos] = y.B;
+        L.r1[pos] = (double)y.r1 * Bk;
+        L.r2[pos] = (double)y.r2 * Bk;
+        L.r3[pos] = (double)y.r3 * Bk;
+        L.K[pos] = y.K;
+        L.W[pos] = y.W;
+        L.tc[pos] = tk;
+        L.E[pos] = ey >= 0.0f && ey < inf ? ey : -1.0f;
+        L.v[pos] = y.v;
+        L.s[pos] = y.s;
+        L.gp[pos] = ok ? y.gp : -1;
+        L.G[pos] = y.G;
+        return ok;
+    };
     // h0: row s's entries q >= h0 would end runs that start before its chain
     // (never read; written +inf when staged, so that the rows go out whole)
     int32_t m = 0, h0 = 0;
-    if (s < n && at(0) <= s) {
-        int64_t lo = 0, hi = n_chains;
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (at(mid) <= s) lo = mid; else hi = mid;
+    bool ok = false, unc = false;
+    if (s < n) {
+        ok = stage(x, e, tl);
+        int64_t lo = L.chain[0], hi = L.chain[1] + 1;
+        if (lo < 0 && hi > 0 && at(0) <= s) lo = 0;
+        if (lo >= 0) {
+            while (hi - lo > 1) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (at(mid) <= s) lo = mid; else hi = mid;
+            }
+            const int64_t b = at(lo + 1);
+            if (s < b) {
+                m = (int32_t)(b - s < (int64_t)R ? b - s : (int64_t)R);
+                const int64_t back = s - at(lo) + 1;
+                h0 = back < (int64_t)R ? (int32_t)back : R;
+            }
         }
-        const int64_t b = at(lo + 1);
-        if (s < b) {
-            m = (int32_t)(b - s < (int64_t)R ? b - s : (int64_t)R);
-            const int64_t back = s - at(lo) + 1;
-            h0 = back < (int64_t)R ? (int32_t)back : R;
+        if (tl < R - 1 && s + kFuseBlock < n) stage(load_row(d, s + kFuseBlock), edge[s + kFuseBlock], kFuseBlock + tl);
+        if (m > 0) {
+            float t = inf;
+            if (ok) {
+                const Set& P = uniform_const(sc);
+                Eval<float> Ev;
+                evaluate<float, false>(P.st, P.cf, x, Ev);
+                unc = run_uncertain(Ev.T, Ev.occ, (double)x.W, P);
+                t = Ev.T == Ev.T ? Ev.T : inf;
+            }
+            if (STAGED) tile[tl * R] = t;
+            else wb.cost[s * R] = (double)t;
         }
     }
-    const float inf = __builtin_huge_valf();
-    FuseSum fs;
-    fuse_begin(fs);
-    bool ok = true, unc = false;
-    // the next row (and the edge into it) is loaded while this one is
-    // evaluated
-    Desc<float> xn;
-    float en = 0.0f;
-    if (m > 0) xn = load_row(d, s);
-    for (int32_t q = 0; q < m; ++q) {
-        const int64_t k = s + q;
-        const Desc<float> x = xn;
-        const float ek = en;
-        if (q + 1 < m) {
-            xn = load_row(d, k + 1);
-            en = edge[k];
-        }
-        if (q > 0) {
-            ok = ok && ek >= 0.0f && ek < inf;
-            fs.E += (double)ek;
-        }
-        ok = ok && desc_valid(x);
-        float t = inf;
-        if (ok) {
-            const Set& P = uniform_const(sc);
-            const Peaks& K = uniform_const(pc);
-            const int32_t dtk = (x.gp >> 11) & 7;
-            double pkk = vreg(K.p[0]);
-            pkk = dtk == 1 ? vreg(K.p[1]) : pkk;
-            pkk = dtk == 2 ? vreg(K.p[2]) : pkk;
-            pkk = dtk == 3 ? vreg(K.p[3]) : pkk;
-            pkk = dtk == 4 ? vreg(K.p[4]) : pkk;
-            fuse_add(fs, x, x.F / (x.u * (float)pkk));
-            double Wd = (double)x.W;
-            Desc<float> y = x;
-            if (q > 0) {
-                double pd = vreg(K.p[0]);
-                pd = fs.dt == 1 ? vreg(K.p[1]) : pd;
-                pd = fs.dt == 2 ? vreg(K.p[2]) : pd;
-                pd = fs.dt == 3 ? vreg(K.p[3]) : pd;
-                pd = fs.dt == 4 ? vreg(K.p[4]) : pd;
-                y = fuse_narrow(fs, pd, Wd);
+    __syncthreads();
+    if (m > 1) {
+        double F = x.F, Bs = x.B, r1 = L.r1[tl], r2 = L.r2[tl], r3 = L.r3[tl], K = x.K, Ws = x.W, tc = L.tc[tl],
+               Es = 0.0;
+        float Fmax = x.F;
+        int32_t v = x.v, sl = x.s, G = x.G, dt = (x.gp >> 11) & 7, nd = (x.gp >> 17) & 7, ns = (x.gp >> 21) & 15;
+        us2 gc = {(unsigned short)(x.gp & 2047), (unsigned short)((x.gp >> 14) & 7)};   // threads, concurrent kernels
+        for (int32_t q = 1; q < m; ++q) {
+            const int k = tl + q;
+            const float ek = L.E[k - 1], Fk = L.F[k];
+            const int32_t gp = L.gp[k];
+            ok = ok && ek >= 0.0f && gp >= 0;
+            float t = inf;
+            if (ok) {
+                const Set& P = uniform_const(sc);
+                Es += (double)ek;
+                F += (double)Fk;
+                Bs += (double)L.B[k];
+                r1 += L.r1[k];
+                r2 += L.r2[k];
+                r3 += L.r3[k];
+                K += (double)L.K[k];
+                Ws += (double)L.W[k];
+                tc += (double)L.tc[k];
+                if (Fk > Fmax) {   // dtype of the first row with the most flops
+                    Fmax = Fk;
+                    dt = (gp >> 11) & 7;
+                }
+                const int32_t vk = L.v[k], sk = L.s[k], Gk = L.G[k], ndk = (gp >> 17) & 7;
+                v = vk > v ? vk : v;
+                sl = sk > sl ? sk : sl;
+                G = Gk > G ? Gk : G;
+                gc = __builtin_elementwise_max(gc, us2{(unsigned short)(gp & 2047), (unsigned short)((gp >> 14) & 7)});
+                nd = ndk > nd ? ndk : nd;
+                ns += (gp >> 21) & 15;
+                // the combined descriptor as fuse_rows forms it, rounded to float32
+                Desc<float> o;
+                o.F = (float)F;
+                o.B = (float)(Bs - 2.0 * Es > 0.0 ? Bs - 2.0 * Es : 0.0);
+                const double iB = Bs > 0.0 ? quot_f32range(1.0, Bs, recip_f32range(Bs)) : 0.0;
+                o.r1 = (float)(r1 * iB);
+                o.r2 = (float)(r2 * iB);
+                o.r3 = (float)(r3 * iB);
+                o.K = (float)K;
+                const double Wd = Ws - Es > 0.0 ? Ws - Es : 0.0;
+                o.W = (float)Wd;
+                o.u = 1.0f;
+                if (F > 0.0) {
+                    // (an infinite compute time is redone in float64; with a
+                    // zero one u is 1, as for any not below 1)
+                    const double den = L.peak[dt] * tc, u = quot_f32range(F, den, recip_f32range(den));
+                    o.u = (float)(u < 1.0 ? u : 1.0);
+                }
+                o.v = v;
+                o.s = sl;
+                o.G = G;
+                o.gp = (int32_t)gc[0] | (dt << 11) | ((int32_t)gc[1] << 14) | (nd << 17) | (1 << 20) |
+                       ((ns < 15 ? ns : 15) << 21);
+                Eval<float> Ev;
+                evaluate<float, false, kFused>(P.st, P.cf, o, Ev);
+                unc = unc || run_uncertain(Ev.T, Ev.occ, Wd, P) || !(tc < __builtin_huge_val());
+                t = Ev.T == Ev.T ? Ev.T : inf;
             }
-            Eval<float> E;
-            evaluate<float, false>(P.st, P.cf, y, E);
-            t = E.T;
-            const bool fin = __builtin_isfinite(t);
-            unc = unc || (!fin && E.occ != 0) || (fin && t < 0.0f);
-            if (P.st.n_levels == 4 && Wd > 0.0) {
-                const double c_llc = P.cd.c_llc;
-                const double dw = Wd * (1.0 / 1048576.0) - c_llc;
-                unc = unc || (dw < 0.0 ? -dw : dw) <= 1e-6 * c_llc;
-            }
-            t = t == t ? t : inf;
+            if (STAGED) tile[k * R + q] = t;
+            else wb.cost[(s + q) * R + q] = (double)t;
         }
-        if (staged) tile[(tl + q) * R + q] = (double)t;
-        else wb.cost[k * R + q] = (double)t;
     }
     if (s < n) wb.cov[s] = (uint8_t)(m | (unc ? kPlanUncertain : 0));
-    if (!staged) return;
+    if (!STAGED) return;
     if (s < n)
-        for (int32_t q = h0; q < R; ++q) tile[tl * R + q] = __builtin_huge_val();
+        for (int32_t q = h0; q < R; ++q) tile[tl * R + q] = inf;
     m_s[tl] = (uint8_t)m;
     h0_s[tl] = (uint8_t)h0;
     __syncthreads();
@@ -932,14 +994,14 @@ __global__ __launch_bounds__(kFuseBlock) void k_fuse_costs(DescPtrs d, const flo
     const int nrow = left < kFuseBlock ? (int)left : kFuseBlock;
     for (int idx = tl; idx < nrow * R; idx += kFuseBlock) {
         const int r = (int)(((float)idx + 0.5f) * inv_r), q = idx - r * R;
-        if (q <= r || q >= (int)h0_s[r]) wb.cost[s0 * R + idx] = tile[idx];
+        if (q <= r || q >= (int)h0_s[r]) wb.cost[s0 * R + idx] = (double)tile[idx];
     }
     // runs that start here and end in the next block's first R - 1 rows
     for (int idx = tl; idx < (R - 1) * R; idx += kFuseBlock) {
         const int i = (int)(((float)idx + 0.5f) * inv_r), q = idx - i * R;
         const int st = kFuseBlock + i - q;   // their start, a row here when q > i
         if (q > i && q < (int)m_s[st] && s0 + kFuseBlock + i < n)
-            wb.cost[(s0 + kFuseBlock + i) * R + q] = tile[(kFuseBlock + i) * R + q];
+            wb.cost[(s0 + kFuseBlock + i) * R + q] = (double)tile[(kFuseBlock + i) * R + q];
     }
 }
 
@@ -950,27 +1012,31 @@ __global__ __launch_bounds__(kFuseBlock) void k_fuse_costs(DescPtrs d, const flo
 // about 3e-7, so 1e-5 is some 17 times 2e (a test holds it to at least 4).
 constexpr double kPlanWindow = 1e-5;
 
-// The dynamic programme runs on groups of GS lanes (GS the power of two >= R),
-// one chain per group: lane gl of a group stands for the run of gl + 1 rows
-// ending at the current row j and holds prev = best over the rows before
-// that run, so that a step is prev + cost, a group minimum (shortest run on
-// ties, as a sequential scan with strict improvement picks) and a shift of
-// prev by one lane.  Groups of one wave step together over their chains.
-template <int GS>
+// The dynamic programme runs on groups of G lanes (2 G the power of two >= R,
+// at least 2), one chain per group: lane gl of a group stands for the runs of 2
+// gl + 1 and 2 gl + 2 rows ending at the current row j and holds prev[] = best
+// over the rows before each, so that a step is two adds, a group minimum
+// (shortest run on ties, as a sequential scan with strict improvement picks)
+// that carries the runner-up along, and a shift of prev by one run.  Groups of
+// one wave step together over their chains.  With a lane per run the lane
+// exchanges and selects of a step, which every lane repeats, took 2.3 times the
+// instructions per chain: k_plan 35.9 us at 2^16 chains, R = 8, now 22.4, of
+// which about half is the 37.7 MB cost table coming in and the rest the
+// programme's steps.
+template <int G>
 struct PlanGroup {
-    int gl, base;   // lane in group, group's first lane
-    int64_t c;      // chain (or -1)
-    int64_t a, L;   // first row, rows
+    int gl;        // lane in group
+    int64_t c;     // chain (or -1)
+    int64_t a;     // first row
+    int32_t L;     // rows (offsets are 32-bit)
 };
 
-template <int GS>
-__device__ inline PlanGroup<GS> plan_group(int64_t c, int64_t n_chains, const int32_t* off,
-                                           int64_t n)
+template <int G>
+__device__ inline PlanGroup<G> plan_group(int64_t c, int64_t n_chains, const int32_t* off, int64_t n)
 {
-    PlanGroup<GS> g;
+    PlanGroup<G> g;
     const int lane = threadIdx.x & 63;
-    g.gl = lane & (GS - 1);
-    g.base = lane - g.gl;
+    g.gl = lane & (G - 1);
     g.c = c >= 0 && c < n_chains ? c : -1;
     g.a = 0;
     g.L = 0;
@@ -979,218 +1045,187 @@ __device__ inline PlanGroup<GS> plan_group(int64_t c, int64_t n_chains, const in
         a = a < 0 ? 0 : (a > n ? n : a);
         b = b < a ? a : (b > n ? n : b);
         g.a = a;
-        g.L = b - a;
+        g.L = (int32_t)(b - a);
     }
     return g;
 }
 
-template <int GS>
-__device__ inline uint64_t group_mask(const PlanGroup<GS>& g)
+template <int G>
+__device__ inline uint64_t group_mask(const PlanGroup<G>& g)
 {
-    return (GS == 64 ? ~0ull : ((1ull << GS) - 1ull)) << g.base;
+    static_assert(G < 64, "a group is part of the wave");
+    return ((1ull << G) - 1ull) << ((threadIdx.x & 63) - g.gl);
 }
 
 // Lane moves inside a row of 16 lanes (DPP): CTRL 0x140 mirrors the row,
 // 0x141 mirrors each half row, 0x4E and 0xB1 swap lanes 2 and 1 apart in each
-// quad; 0x138 shifts the wave up by one lane (lane 0 keeps its value).
+// quad; 0x138 shifts the wave up by one lane (the lane shifted in is never
+// used, so no old value is kept: that would cost a copy per move).
 template <int CTRL>
 __device__ inline int32_t dpp32(int32_t x)
 {
-    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_mov_dpp(x, CTRL, 0xF, 0xF, true);
 }
 
 template <int CTRL>
 __device__ inline double dpp64(double x)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)dpp32<CTRL>((int32_t)(uint32_t)u);
-    const uint32_t hi = (uint32_t)dpp32<CTRL>((int32_t)(uint32_t)(u >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    return f64_of((uint32_t)dpp32<CTRL>((int32_t)(uint32_t)u), (uint32_t)dpp32<CTRL>((int32_t)(uint32_t)(u >> 32)));
 }
 
-// The partner of step k of the group reduction: lanes 16 apart (GS = 32),
-// the row mirror (GS >= 16), the half-row mirror (GS >= 8), then 2 and 1 apart
-// in the quad; each step doubles the lanes a value covers.
-template <int STEP>
-__device__ inline double partner(double v)
-{
-    if constexpr (STEP == 16) return __shfl_xor(v, 16, 64);
-    else if constexpr (STEP == 8) return dpp64<0x140>(v);
-    else if constexpr (STEP == 4) return dpp64<0x141>(v);
-    else if constexpr (STEP == 2) return dpp64<0x4E>(v);
-    else return dpp64<0xB1>(v);
-}
-
-template <int STEP>
-__device__ inline int32_t partner(int32_t v)
-{
-    if constexpr (STEP == 16) return __shfl_xor(v, 16, 64);
-    else if constexpr (STEP == 8) return dpp32<0x140>(v);
-    else if constexpr (STEP == 4) return dpp32<0x141>(v);
-    else if constexpr (STEP == 2) return dpp32<0x4E>(v);
-    else return dpp32<0xB1>(v);
-}
-
-template <int STEP>
-__device__ inline void argmin_step(double& v, int32_t& len)
-{
-    const double ov = partner<STEP>(v);
-    const int32_t ol = partner<STEP>(len);
-    const bool take = (ov < v) | ((ov == v) & (ol < len));
-    v = take ? ov : v;
-    len = take ? ol : len;
-}
-
-// Minimum of (v, len) over the group, ties to the shorter run.
-template <int GS>
-__device__ inline void group_argmin(double& v, int32_t& len)
-{
-    if constexpr (GS >= 32) argmin_step<16>(v, len);
-    if constexpr (GS >= 16) argmin_step<8>(v, len);
-    if constexpr (GS >= 8) argmin_step<4>(v, len);
-    if constexpr (GS >= 4) argmin_step<2>(v, len);
-    if constexpr (GS >= 2) argmin_step<1>(v, len);
-}
-
-template <int GS>
-__device__ inline double group_min(double v)
-{
-    if constexpr (GS >= 32) { const double o = partner<16>(v); v = o < v ? o : v; }
-    if constexpr (GS >= 16) { const double o = partner<8>(v); v = o < v ? o : v; }
-    if constexpr (GS >= 8) { const double o = partner<4>(v); v = o < v ? o : v; }
-    if constexpr (GS >= 4) { const double o = partner<2>(v); v = o < v ? o : v; }
-    if constexpr (GS >= 2) { const double o = partner<1>(v); v = o < v ? o : v; }
-    return v;
-}
-
-// Rows of costs a group loads ahead of its steps (one wait per batch), and
-// windows of GS rows whose cut lengths stay in registers (cut bytes of
-// rows beyond them go through memory).
-constexpr int kPlanBatch = 16;
-constexpr int kPlanRegWin = 4;
-
-// Per-lane state of a group's programme: prev (best over the rows before
-// this lane's run), the all-singles sum (first lane), best[j], the cut
-// length of row w * GS + gl in cutw[w].
-struct PlanState {
-    double prev, single, best;
-    int32_t cutw[kPlanRegWin];
+// A group's best run so far: value, length and the runner-up's value.
+struct PlanBest {
+    double v, second;
+    int32_t len;
 };
 
-// One step of the programme at row j of the group's chain (all lanes of the
-// wave call it; `live` marks groups still inside their chain).  t is this
-// lane's run cost (ignored where the run is longer than R or than j + 1
-// rows).  Updates prev, the all-singles sum (on the group's first lane, whose
-// run is the row alone), best and the cut length of row j; with MARGIN,
-// `close` is set when the runner-up is within kPlanWindow.
-template <int GS, bool MARGIN>
-__device__ inline void plan_step(const PlanGroup<GS>& g, int32_t R, int64_t j, bool live,
-                                 double t, PlanState& ps, bool& close, uint8_t* __restrict__ cut)
+// One step of the group reduction, each doubling the lanes a value covers:
+// the row mirror (G >= 16), the half-row mirror (G >= 8), then 2 and 1 apart.
+template <int CTRL, bool MARGIN>
+__device__ inline void best_step(PlanBest& b)
 {
-    const double inf = __builtin_huge_val();
-    const int32_t len = g.gl + 1;
-    const bool valid = live & (len <= R) & (len <= j + 1);
-    const double v = valid ? ps.prev + t : inf;
-    if (valid && g.gl == 0) ps.single += t;
-    double bj = v;
-    int32_t cj = len;
-    group_argmin<GS>(bj, cj);
+    const double ov = dpp64<CTRL>(b.v);
+    const int32_t ol = dpp32<CTRL>(b.len);
+    const bool take = (ov < b.v) | ((ov == b.v) & (ol < b.len));
     if (MARGIN) {
-        const double sj = group_min<GS>(len == cj ? inf : v);
-        close = close | (live & (sj < inf) & (sj - bj <= kPlanWindow * sj));
+        const double os = dpp64<CTRL>(b.second), lose = take ? b.v : ov, s = os < b.second ? os : b.second;
+        b.second = lose < s ? lose : s;
     }
-    if (live) {
-        if (j < (int64_t)kPlanRegWin * GS) {
-#pragma unroll
-            for (int w = 0; w < kPlanRegWin; ++w)
-                if (j == (int64_t)w * GS + g.gl) ps.cutw[w] = cj;
-        } else if (g.gl == 0) {
-            cut[g.a + j] = (uint8_t)cj;
-        }
-        ps.best = bj;
-    }
-    const double up = dpp64<0x138>(ps.prev);   // lane - 1's prev
-    ps.prev = g.gl == 0 ? bj : up;
+    b.v = take ? ov : b.v;
+    b.len = take ? ol : b.len;
 }
+
+template <int G, bool MARGIN>
+__device__ inline void group_best(PlanBest& b)
+{
+    if constexpr (G >= 16) best_step<0x140, MARGIN>(b);
+    if constexpr (G >= 8) best_step<0x141, MARGIN>(b);
+    if constexpr (G >= 4) best_step<0x4E, MARGIN>(b);
+    if constexpr (G >= 2) best_step<0xB1, MARGIN>(b);
+}
+
+// Rows per batch: their costs are loaded together (one wait per batch), their
+// cut lengths stay in registers, a byte each, equal on every lane of the
+// group, until the next batch begins (cut bytes of all but the last batch go
+// through memory).
+constexpr int kPlanBatch = 16;
+
+struct PlanState {
+    double prev[2], single, best;   // single: the all-singles sum (first lane)
+    uint64_t cut[2];                // the batch's cut lengths, rows 0-7 and 8-15
+};
 
 // The programme over the group's chain, costs from wb.cost.  With COV, the
 // chain's coverage bytes are read with the first batch of costs and `run`
 // is narrowed to covered chains without an uncertain run (covered and unc
-// report them); without, `run` is taken as given.
-template <int GS, bool MARGIN, bool COV>
-__device__ inline void plan_run(const PlanGroup<GS>& g, bool& run, int32_t R, const PlanBufs& wb,
+// report them); without, `run` is taken as given.  With MARGIN, `close` is set
+// when a decision's runner-up is within kPlanWindow.
+template <int G, bool MARGIN, bool COV>
+__device__ inline void plan_run(const PlanGroup<G>& g, bool& run, int32_t R, const PlanBufs& wb,
                                 PlanState& ps, bool& close, bool& covered, bool& unc)
 {
+    typedef double d2 __attribute__((ext_vector_type(2)));
     const double inf = __builtin_huge_val();
-    const int32_t len = g.gl + 1;
-    ps.prev = ps.single = ps.best = 0.0;
-#pragma unroll
-    for (int w = 0; w < kPlanRegWin; ++w) ps.cutw[w] = 1;
+    const int32_t q0 = 2 * g.gl;   // the lane's runs have q0 + 1 and q0 + 2 rows
+    ps.prev[0] = ps.prev[1] = ps.single = ps.best = 0.0;
+    ps.cut[0] = ps.cut[1] = 0ull;
     covered = true;
     unc = false;
-    for (int64_t j0 = 0; __ballot(run && j0 < g.L) != 0ull; j0 += kPlanBatch) {
-        double t[kPlanBatch];
+    // the batch's first row and its cost entries of this lane; j0 cannot pass
+    // 2^31: it stops at the longest chain's end, less than a batch beyond
+    const double* at = wb.cost + g.a * R + q0;
+    for (int32_t j0 = 0; __ballot(run && j0 < g.L) != 0ull; j0 += kPlanBatch) {
+        const int32_t left = run ? g.L - j0 : 0;   // rows of the chain from j0 on
+        if (j0 > 0 && run && j0 < g.L) {   // the last batch's cut lengths make room
+            for (int r = g.gl; r < kPlanBatch; r += G)
+                wb.cut[g.a + (j0 - kPlanBatch + r)] = (uint8_t)((r < 8 ? ps.cut[0] : ps.cut[1]) >> (8 * (r & 7)));
+            ps.cut[0] = ps.cut[1] = 0ull;
+        }
+        double t[kPlanBatch][2];
+        // runs longer than the rows so far or than R do not exist
+        const int32_t before = j0 < kPlanMaxRun ? j0 : kPlanMaxRun;
 #pragma unroll
         for (int k = 0; k < kPlanBatch; ++k) {
-            const int64_t j = j0 + k;
-            t[k] = run && j < g.L && len <= R && len <= j + 1 ? wb.cost[(g.a + j) * R + g.gl] : inf;
+            d2 x = {inf, inf};
+            if (k < left && q0 < R) {
+                if ((R & 1) == 0) x = *(const d2*)at;   // rows of an even length: 16-byte aligned pairs
+                else {
+                    x[0] = at[0];
+                    if (q0 + 1 < R) x[1] = at[1];
+                }
+            }
+            at += R;
+            t[k][0] = q0 <= k + before ? x[0] : inf;
+            t[k][1] = q0 + 1 <= k + before && q0 + 1 < R ? x[1] : inf;
         }
         if (COV && j0 == 0) {
-            // coverage and uncertain runs, GS rows at a time (loads in flight
+            // coverage and uncertain runs, G rows at a time (loads in flight
             // with the costs above)
             const uint64_t gm = group_mask(g);
             bool bad = false, u = false;
-            for (int64_t i = g.gl; i < g.L; i += GS) {
+            for (int32_t i = g.gl; i < g.L && i >= 0; i += G) {
                 const uint8_t cv = wb.cov[g.a + i];
-                const int64_t want = g.L - i < (int64_t)R ? g.L - i : (int64_t)R;
-                bad = bad || (int64_t)(cv & kPlanCount) != want;
+                const int32_t want = g.L - i < R ? g.L - i : R;
+                bad = bad || (int32_t)(cv & kPlanCount) != want;
                 u = u || (cv & kPlanUncertain) != 0;
             }
             covered = (__ballot(bad) & gm) == 0ull;
             unc = (__ballot(u) & gm) != 0ull;
             run = run && covered && !unc;
         }
-#pragma unroll 1
+#pragma unroll
         for (int k = 0; k < kPlanBatch; ++k) {
-            const int64_t j = j0 + k;
-            plan_step<GS, MARGIN>(g, R, j, run && j < g.L, t[k], ps, close, wb.cut);
+            const bool live = run && k < left;
+            if (__ballot(live) == 0ull) break;
+            const double v0 = ps.prev[0] + t[k][0], v1 = ps.prev[1] + t[k][1];
+            if (live) ps.single += t[k][0];   // (the first lane's run is the row alone)
+            const bool second = v1 < v0;
+            PlanBest b{second ? v1 : v0, second ? v0 : v1, second ? q0 + 2 : q0 + 1};
+            group_best<G, MARGIN>(b);
+            if (MARGIN) close = close | (live & (b.second < inf) & (b.second - b.v <= kPlanWindow * b.second));
+            const double up = dpp64<0x138>(ps.prev[1]);   // lane - 1's longer run
+            ps.prev[1] = ps.prev[0];
+            ps.prev[0] = g.gl == 0 ? b.v : up;
+            if (live) {
+                ps.cut[k >> 3] |= (uint64_t)(uint32_t)b.len << (8 * (k & 7));
+                ps.best = b.v;
+            }
         }
     }
 }
 
 // Start flags of the chosen plan: the run starts found by following the cut
-// lengths back from the chain's end, window by window (rows w * GS .. w * GS
-// + GS - 1, the window's cut lengths in the group's lanes, the chase by
-// shuffles).  `live` marks groups that write their chain's flags.
-template <int GS>
-__device__ inline void plan_starts(const PlanGroup<GS>& g, bool live, const PlanState& ps,
+// lengths back from the chain's end, batch by batch.  `live` marks groups that
+// write their chain's flags.
+template <int G>
+__device__ inline void plan_starts(const PlanGroup<G>& g, bool live, const PlanState& ps,
                                    const uint8_t* __restrict__ cut, uint8_t* __restrict__ start)
 {
-    const int64_t nw = live ? (g.L + GS - 1) / GS : 0;   // windows of the chain
-    // cut bytes beyond the register windows were stored by the group's first
-    // lanes: make them visible to the loads below
-    if (__ballot(nw > kPlanRegWin) != 0ull) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    int64_t w = nw - 1;
-    int64_t jj = live ? g.L : 0;   // the next run start found (row in the chain)
-    while (__ballot(w >= 0) != 0ull) {
-        const int64_t w0 = w >= 0 ? w * GS : 0;
-        const int64_t row = w0 + g.gl;
-        const bool mine = w >= 0 && row < g.L;
-        int32_t cv = 1;
-#pragma unroll
-        for (int k = 0; k < kPlanRegWin; ++k) cv = w == k ? ps.cutw[k] : cv;
-        if (mine && w >= kPlanRegWin) cv = cut[g.a + row];
-        bool flag = mine && row == jj;
-        while (__ballot(w >= 0 && jj > w0) != 0ull) {
-            const int64_t r = w >= 0 && jj > w0 ? jj - 1 - w0 : 0;
-            const int32_t Lr = __shfl(cv, g.base + (int)r, 64);
-            if (w >= 0 && jj > w0) {
-                jj -= Lr;
-                flag = flag || (mine && row == jj);
-            }
+    const int32_t L = live ? g.L : 0;
+    // cut bytes of earlier batches were stored by the group's lanes: make them
+    // visible to the loads below
+    if (__ballot(L > kPlanBatch) != 0ull) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    uint64_t c0 = ps.cut[0], c1 = ps.cut[1];
+    int32_t jj = L;   // the next run start found (row in the chain)
+    for (int32_t w0 = L > 0 ? (L - 1) & ~(kPlanBatch - 1) : -1; __ballot(w0 >= 0) != 0ull; w0 -= kPlanBatch) {
+        if (w0 < 0) {
+            w0 = 0;   // (stays negative after the step)
+            continue;
         }
-        if (mine) start[g.a + row] = flag ? 1 : 0;
-        --w;
+        if (w0 + kPlanBatch < L) {
+            __builtin_memcpy(&c0, cut + g.a + w0, 8);
+            __builtin_memcpy(&c1, cut + g.a + w0 + 8, 8);
+        }
+        uint32_t flags = jj < L && jj >= w0 ? 1u << (jj - w0) : 0u;   // found from a later batch
+        while (jj > w0) {
+            const int r = jj - 1 - w0;
+            const int32_t len = (int32_t)((r < 8 ? c0 : c1) >> (8 * (r & 7))) & 0xff;
+            jj -= len > 0 ? len : 1;
+            if (jj >= w0) flags |= 1u << (jj - w0);
+        }
+        for (int r = g.gl; r < kPlanBatch; r += G)
+            if (w0 + r < L) start[g.a + w0 + r] = (uint8_t)((flags >> r) & 1u);
     }
 }
 
@@ -1201,7 +1236,7 @@ __device__ inline void plan_starts(const PlanGroup<GS>& g, bool live, const Plan
 // redo; the rest get their totals and start flags.
 constexpr int kPlanBlock = 256;    // threads per block of the planning pass (5 blocks per CU)
 
-template <int GS>
+template <int G>
 __global__ __launch_bounds__(kPlanBlock) void k_plan(const int32_t* __restrict__ off,
                                                       int64_t n_chains, int64_t n, int32_t R,
                                                       PlanBufs wb, double* __restrict__ total,
@@ -1210,12 +1245,12 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan(const int32_t* __restrict__
 {
     __shared__ uint32_t wave_q[kPlanBlock / 64 + 1];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int64_t gid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / GS;
-    const PlanGroup<GS> g = plan_group<GS>(gid, n_chains, off, n);
+    const int64_t gid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    const PlanGroup<G> g = plan_group<G>(gid, n_chains, off, n);
     const uint64_t gm = group_mask(g);
     PlanState ps;
     bool run = g.c >= 0, close = false, covered, unc;
-    plan_run<GS, true, true>(g, run, R, wb, ps, close, covered, unc);
+    plan_run<G, true, true>(g, run, R, wb, ps, close, covered, unc);
     close = unc || (__ballot(close) & gm) != 0ull;
     const bool done = g.c >= 0 && covered && !close;
     // queue slots: one atomic per block, the waves' shares by a prefix in LDS
@@ -1261,16 +1296,20 @@ __device__ inline int64_t redo_count(const PlanBufs& wb, int64_t n_chains, int64
     return nq < n ? nq : n;
 }
 
-// Float64 redo, costs: each wave takes E <= kRedoChains queued chains (E
-// the queue's length over the grid's waves, so that every wave has work
-// before any takes several) and lays their (run length, run end) candidates
-// end to end over its lanes, ordered by length so that neighbouring lanes
-// fuse the same number of rows; each run is formed by fuse_rows and
-// evaluated with the float64 model, and the costs replace the chains'
-// float32 ones.
-constexpr int kRedoChains = 8;
+// Float64 redo: a wave per queued chain.  Its candidate runs, (length, end) in
+// order of length so that neighbouring lanes fuse the same number of rows, are
+// laid over the lanes; each is formed in the order and arithmetic of fuse_rows
+// and evaluated with the float64 model, and the costs replace the chain's
+// float32 ones; then the wave's first G lanes run the programme over them.
+// A chain of up to kRedoRows rows is loaded once, a row per lane, into LDS with
+// what the sums add per row (products, compute time, validity); longer ones go
+// through memory row by row.
+// Bound: latency (one chain of loads, sums, one or two float64 evaluations and
+// the programme per wave).  At 2^16 chains, 3 % of them queued, 23.8 us where
+// separate cost and programme launches reading rows from memory took 28.7 + 10.4.
+constexpr int kRedoRows = 64;
 
-struct RedoArgs {   // k_redo_costs's parameters, in order
+struct RedoArgs {   // k_redo's parameters, in order
     DescPtrs d;
     const float* edge;
     const int32_t* off;
@@ -1280,149 +1319,163 @@ struct RedoArgs {   // k_redo_costs's parameters, in order
     Peaks pk;
 };
 
-__global__ __launch_bounds__(256) void k_redo_costs(DescPtrs d, const float* __restrict__ edge,
-                                                     const int32_t* __restrict__ off,
-                                                     int64_t n_chains, int64_t n, int32_t R, Set S,
-                                                     Peaks pk, PlanBufs wb)
+struct RedoLds {
+    double F[kRedoRows], B[kRedoRows], r1[kRedoRows], r2[kRedoRows], r3[kRedoRows], K[kRedoRows], W[kRedoRows],
+        tc[kRedoRows], E[kRedoRows];   // E < 0: the edge behind the row is invalid
+    int32_t v[kRedoRows], s[kRedoRows], gp[kRedoRows], G[kRedoRows];   // gp < 0: the row is invalid
+};
+
+__device__ inline void redo_stage(RedoLds& L, const DescPtrs& d, const float* __restrict__ edge, const double* peak,
+                                  int64_t row, bool has_edge, int pos)
 {
+#pragma clang fp contract(off)
+    const Desc<float> x = load_row(d, row);
+    const float e = has_edge ? edge[row] : 0.0f;
+    const bool ok = desc_valid(x);
+    const double Bk = x.B, Fk = x.F;
+    L.F[pos] = Fk;
+    L.B[pos] = Bk;
+    L.r1[pos] = (double)x.r1 * Bk;
+    L.r2[pos] = (double)x.r2 * Bk;
+    L.r3[pos] = (double)x.r3 * Bk;
+    L.K[pos] = (double)x.K;
+    L.W[pos] = (double)x.W;
+    L.tc[pos] = ok && Fk > 0.0 ? Fk / ((double)x.u * peak[(x.gp >> 11) & 7]) : 0.0;
+    L.E[pos] = e >= 0.0f && e < __builtin_huge_valf() ? (double)e : -1.0;
+    L.v[pos] = x.v;
+    L.s[pos] = x.s;
+    L.gp[pos] = ok ? x.gp : -1;
+    L.G[pos] = x.G;
+}
+
+// fuse_rows over staged rows p .. p + len - 1
+__device__ inline bool fuse_staged(const RedoLds& L, const double* peak, int p, int32_t len, Desc<double>& o)
+{
+#pragma clang fp contract(off)
+    FuseSum a;
+    bool ok = true;
+    for (int32_t q = 0; q < len; ++q) {
+        const int k = p + q;
+        const int32_t gp = L.gp[k];
+        const double e = q < len - 1 ? L.E[k] : 0.0;
+        ok = ok && gp >= 0 && e >= 0.0;
+        a.E += e;
+        a.F += L.F[k];
+        a.Bs += L.B[k];
+        a.r1 += L.r1[k];
+        a.r2 += L.r2[k];
+        a.r3 += L.r3[k];
+        a.K += L.K[k];
+        a.Ws += L.W[k];
+        a.tc += L.tc[k];
+        fuse_ints(a, L.F[k], L.v[k], L.s[k], gp, L.G[k]);
+    }
+    if (ok) fuse_form(a, peak, o);
+    return ok;
+}
+
+template <int G>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_redo(DescPtrs d, const float* __restrict__ edge,
+                                               const int32_t* __restrict__ off, int64_t n_chains, int64_t n,
+                                               int32_t R, Set S, Peaks pk, PlanBufs wb, double* __restrict__ total,
+                                               double* __restrict__ unfused, uint8_t* __restrict__ start)
+{
+    __shared__ RedoLds lds[4];
     const int lane = threadIdx.x & 63;
     const int64_t wave = wave_id();
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    RedoLds& L = lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
     const double inf = __builtin_huge_val();
     const int64_t nq = redo_count(wb, n_chains, n);
-    int64_t E = (nq + nwaves - 1) / nwaves;
-    E = E < 1 ? 1 : (E > kRedoChains ? kRedoChains : E);
-    for (int64_t e0 = wave * E; e0 < nq; e0 += nwaves * E) {
-        // lanes 0 .. E-1: a chain each, its rows and candidate count
-        int64_t a = 0, L = 0, cnt = 0;
-        if (lane < E && e0 + lane < nq) {
-            const int64_t c = wb.redo[e0 + lane];
-            if (c >= 0 && c < n_chains) {
-                a = off[c];
-                int64_t b = off[c + 1];
-                a = a < 0 ? 0 : (a > n ? n : a);
-                b = b < a ? a : (b > n ? n : b);
-                L = b - a;
-                const int64_t r = L < (int64_t)R ? L : (int64_t)R;
-                cnt = r * L - r * (r - 1) / 2;   // sum over len <= r of L - len + 1
-            }
+    for (int64_t e = wave; e < nq; e += nwaves) {
+        const int64_t c = wb.redo[e];
+        PlanGroup<64> whole;   // the chain's rows, clamped
+        whole = plan_group<64>(c, n_chains, off, n);
+        const int64_t a = whole.a;
+        const int32_t len_c = whole.L;
+        const double* peak = uniform_const(WM_KERNARG_PTR(RedoArgs, pk)).p;
+        const bool staged = len_c <= kRedoRows;
+        if (staged) {
+            if (lane < len_c) redo_stage(L, d, edge, peak, a + lane, lane + 1 < len_c, lane);
+            wave_lds_sync();
         }
-        // inclusive prefix of the counts over the first kRedoChains lanes
-        int64_t inc = cnt;
-#pragma unroll
-        for (int m = 1; m < kRedoChains; m <<= 1) {
-            const int64_t o = __shfl_up(inc, m, 64);
-            inc += lane >= m ? o : 0;
-        }
-        // the chains' running ends, first rows and lengths, read while every
-        // lane is active (wave-uniform, so in scalar registers)
-        int64_t ends[kRedoChains], as[kRedoChains], Ls[kRedoChains];
-#pragma unroll
-        for (int k = 0; k < kRedoChains; ++k) {
-            ends[k] = read_lane64(inc, k);
-            as[k] = read_lane64(a, k);
-            Ls[k] = read_lane64(L, k);
-        }
-        for (int64_t q = lane; q < ends[kRedoChains - 1]; q += 64) {
-            int64_t r = q, ca = as[0], cL = Ls[0];
-#pragma unroll
-            for (int i = 1; i < kRedoChains; ++i) {
-                if (q >= ends[i - 1]) {
-                    r = q - ends[i - 1];
-                    ca = as[i];
-                    cL = Ls[i];
-                }
-            }
-            // r -> (len, j): lengths in increasing order, ends j = len-1 .. L-1
+        const int32_t r = len_c < R ? len_c : R;
+        const int64_t cnt = (int64_t)r * len_c - r * (r - 1) / 2;   // sum over len <= r of len_c - len + 1
+        for (int64_t q = lane; q < cnt; q += 64) {
+            // q -> (len, j): lengths in increasing order, ends j = len - 1 .. len_c - 1
+            int64_t x = q;
             int32_t len = 1;
-            while (len < R && r >= cL - len + 1) {
-                r -= cL - len + 1;
+            while (len < R && x >= len_c - len + 1) {
+                x -= len_c - len + 1;
                 ++len;
             }
-            const int64_t j = len - 1 + r;
-            if (j >= cL) continue;   // r is below the chain's count, so never
-            const int64_t s0 = ca + j - len + 1;
-            Desc<double> x;
+            const int64_t j = len - 1 + x;
+            const int64_t first = j - len + 1;
+            Desc<double> y;
             bool ok;
             if (len == 1) {
-                x = widen(load_row(d, s0));
+                y = widen(load_row(d, a + j));
                 ok = true;
+            } else if (staged) {
+                ok = fuse_staged(L, peak, (int)first, len, y);
             } else {
-                ok = fuse_rows(d, edge, uniform_const(WM_KERNARG_PTR(RedoArgs, pk)).p, s0, len, x);
+                ok = fuse_rows(d, edge, peak, a + first, len, y);
             }
             double t = inf;
             if (ok) {
                 const Set& P = uniform_const(WM_KERNARG_PTR(RedoArgs, S));
                 Eval<double> E;
-                evaluate<double, false>(P.st, P.cd, x, E);
+                evaluate<double, false>(P.st, P.cd, y, E);
                 t = E.T == E.T ? E.T : inf;
             }
-            wb.cost[(ca + j) * R + (len - 1)] = t;
+            wb.cost[(a + j) * R + (len - 1)] = t;
         }
-    }
-}
-
-// Float64 redo, plans: one group per queued chain, the programme over the
-// float64 costs.
-template <int GS>
-__global__ __launch_bounds__(256) void k_redo_plan(const int32_t* __restrict__ off,
-                                                    int64_t n_chains, int64_t n, int32_t R,
-                                                    PlanBufs wb, double* __restrict__ total,
-                                                    double* __restrict__ unfused,
-                                                    uint8_t* __restrict__ start)
-{
-    const int64_t nq = redo_count(wb, n_chains, n);
-    const int64_t gpw = 64 / GS;   // groups per wave
-    const int64_t wave = wave_id();
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    for (int64_t e0 = wave * gpw; e0 < nq; e0 += nwaves * gpw) {
-        const int64_t e = e0 + lane / GS;
-        const int64_t c = e < nq ? wb.redo[e] : -1;
-        const PlanGroup<GS> g = plan_group<GS>(c, n_chains, off, n);
+        // the wave's costs, read back by its first lanes
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        PlanGroup<G> g;
+        g.gl = lane & (G - 1);
+        g.c = lane < G ? whole.c : -1;
+        g.a = a;
+        g.L = lane < G ? len_c : 0;
         PlanState ps;
         bool run = g.c >= 0, unused = false, covered, unc;
-        plan_run<GS, false, false>(g, run, R, wb, ps, unused, covered, unc);
+        plan_run<G, false, false>(g, run, R, wb, ps, unused, covered, unc);
         if (g.c >= 0 && g.gl == 0) {
             total[g.c] = ps.best;
             unfused[g.c] = ps.single;
         }
         plan_starts(g, g.c >= 0, ps, wb.cut, start);
+        wave_lds_sync();   // the rows are rewritten for the next chain
     }
 }
 
-template <int GS>
-static hipError_t plan_launch(const int32_t* off, int64_t n_chains, int64_t n, int32_t R,
-                              const PlanBufs& wb, double* total, double* unfused, uint8_t* start,
-                              bool redo, hipStream_t s)
+struct PlanCall {
+    DescPtrs d;
+    const float* edge;
+    const int32_t* off;
+    int64_t n_chains, n;
+    int32_t R;
+    Peaks pk;
+    PlanBufs wb;
+    double *total, *unfused;
+    uint8_t* start;
+};
+
+// the programme over the float32 costs, then the queued chains in float64
+template <int G>
+static hipError_t plan_launch(const PlanCall& p, const Set& S, hipStream_t s)
 {
-    if (!redo) {
-        const int64_t per_block = kPlanBlock / GS;   // chains per block
-        const int64_t nb = (n_chains + per_block - 1) / per_block;
-        k_plan<GS><<<(unsigned)nb, kPlanBlock, 0, s>>>(off, n_chains, n, R, wb, total, unfused,
-                                                        start);
-    } else {
-        const int64_t want = (n_chains + 256 / GS - 1) / (256 / GS);
-        int64_t b = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_redo_plan<GS>), 256);
-        b = b < want ? b : want;
-        b = b < 1 ? 1 : b;
-        k_redo_plan<GS><<<(unsigned)b, 256, 0, s>>>(off, n_chains, n, R, wb, total, unfused, start);
-    }
+    const int64_t per_block = kPlanBlock / G;   // chains per block
+    const int64_t nb = (p.n_chains + per_block - 1) / per_block;
+    k_plan<G><<<(unsigned)nb, kPlanBlock, 0, s>>>(p.off, p.n_chains, p.n, p.R, p.wb, p.total, p.unfused, p.start);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t want = (p.n_chains + 3) / 4;   // a chain per wave
+    int64_t b = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_redo<G>), 256);
+    b = b < want ? b : want;
+    k_redo<G><<<(unsigned)(b < 1 ? 1 : b), 256, 0, s>>>(p.d, p.edge, p.off, p.n_chains, p.n, p.R, S, p.pk, p.wb, p.total,
+                                                       p.unfused, p.start);
     return hipGetLastError();
-}
-
-static hipError_t plan_dispatch(int32_t gs, const int32_t* off, int64_t n_chains, int64_t n,
-                                int32_t R, const PlanBufs& wb, double* total, double* unfused,
-                                uint8_t* start, bool redo, hipStream_t s)
-{
-    switch (gs) {
-    case 1: return plan_launch<1>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    case 2: return plan_launch<2>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    case 4: return plan_launch<4>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    case 8: return plan_launch<8>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    case 16: return plan_launch<16>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    default: return plan_launch<32>(off, n_chains, n, R, wb, total, unfused, start, redo, s);
-    }
 }
 
 hipError_t launch_plan_fusion(const DescPtrs& d, const float* edge, const int32_t* off,
@@ -1431,25 +1484,22 @@ hipError_t launch_plan_fusion(const DescPtrs& d, const float* edge, const int32_
                               double* unfused, uint8_t* start, hipStream_t s)
 {
     if (n_chains <= 0) return hipSuccess;
-    Peaks pk;
-    for (int t = 0; t < 5; ++t) pk.p[t] = peaks[t];
-    int32_t gs = 1;
-    while (gs < R) gs <<= 1;   // R <= 32
+    PlanCall p{d, edge, off, n_chains, n, R, {}, wb, total, unfused, start};
+    for (int t = 0; t < 5; ++t) p.pk.p[t] = peaks[t];
     // at least one block, so that the queue's length is cleared even with no rows
     const int64_t nb = n > 0 ? (n + kFuseBlock - 1) / kFuseBlock : 1;
-    k_fuse_costs<<<(unsigned)nb, kFuseBlock, 0, s>>>(d, edge, off, n_chains, n, R, S, pk, wb);
-    hipError_t e = hipGetLastError();
+    if (R <= kFuseTileR)
+        k_fuse_costs<true><<<(unsigned)nb, kFuseBlock, 0, s>>>(d, edge, off, n_chains, n, R, S, p.pk, wb);
+    else
+        k_fuse_costs<false><<<(unsigned)nb, kFuseBlock, 0, s>>>(d, edge, off, n_chains, n, R, S, p.pk, wb);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = plan_dispatch(gs, off, n_chains, n, R, wb, total, unfused, start, false, s);
-    if (e != hipSuccess) return e;
-    const int64_t want = (n_chains + 3) / 4;
-    int64_t nb3 = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_redo_costs), 256) * 2;
-    nb3 = nb3 < want ? nb3 : want;
-    nb3 = nb3 < 1 ? 1 : nb3;
-    k_redo_costs<<<(unsigned)nb3, 256, 0, s>>>(d, edge, off, n_chains, n, R, S, pk, wb);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return plan_dispatch(gs, off, n_chains, n, R, wb, total, unfused, start, true, s);
+    // lanes per chain: the power of two holding R runs, two per lane (R <= 32)
+    if (R <= 2) return plan_launch<1>(p, S, s);
+    if (R <= 4) return plan_launch<2>(p, S, s);
+    if (R <= 8) return plan_launch<4>(p, S, s);
+    if (R <= 16) return plan_launch<8>(p, S, s);
+    return plan_launch<16>(p, S, s);
 }
 
 }  // namespace wm

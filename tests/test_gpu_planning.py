@@ -301,6 +301,33 @@ def test_fusion_uncertain_runs_are_redone(wmb, orc):
         assert abs(cost - otot[c]) <= 1e-12 * otot[c], (c, cost, otot[c])
 
 
+@pytest.mark.parametrize("R", [1, 2, 5, 8, 9, 16, 32])
+def test_fusion_batches_and_long_redos(wmb, orc, R):
+    # chain lengths around the programme's batches of 16 rows, the redo's 64
+    # rows in LDS and a block's 256 rows; every second chain holds a pair whose
+    # fused working set is at the LLC capacity (as above), so it is redone in
+    # float64 whatever its length: totals to 1e-12
+    p = synth.param_set(0)
+    lens = [15, 15, 16, 16, 17, 17, 31, 32, 33, 33, 47, 48, 49, 49, 63, 64, 65, 65, 130, 131, 255, 256, 257, 300, 1, 2]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(off[-1])
+    d = synth.descriptors(n, 175)
+    rng = np.random.default_rng(175)
+    d.vgpr = rng.integers(16, 129, n, dtype=np.int32)
+    nxt = np.concatenate([d.B[1:], np.zeros(1, np.float32)])
+    e = (rng.uniform(0.05, 0.45, n) * np.minimum(d.B, nxt)).astype(np.float32)
+    planted = range(1, len(lens), 2)
+    for c in planted:
+        k = int(off[c]) + lens[c] // 2 - 1
+        if lens[c] >= 2:
+            d.W[k], d.W[k + 1], e[k] = np.float32(2 ** 27), np.float32(2 ** 27 + 16), 0.0
+    tot, unf, _ = _check_plan(wmb, orc, p, off, d, e, R, f"batches, R={R}")
+    otot, ounf, _ = orc.plan_fusion(p, d, e, off, R)
+    if R >= 2:
+        for c in planted:
+            assert abs(tot[c] - otot[c]) <= 1e-12 * otot[c] and abs(unf[c] - ounf[c]) <= 1e-12 * ounf[c], c
+
+
 def test_fusion_offsets_not_non_decreasing(wmb, orc):
     # chain 2 starts inside chain 0: its rows were costed as chain 0's, so it
     # reports NaN; chain 0 is planned as usual and chain 1 is empty
