@@ -8,6 +8,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_04178_amd import synth
 
@@ -445,3 +446,27 @@ def test_calibrate_resume_rejects_bad_states_before_any_hip_call(wmb):
     st.theta[13] = synth.param_set(0).theta[13]
     assert L.wm_calibrate_resume(C.byref(d), w, C.byref(p), C.byref(o), C.byref(st), 5, None, C.byref(pout),
                                  None, ws, 8, None) == wmb.WM_EWORKSPACE
+
+
+@pytest.mark.parametrize("conv", [list, tuple, np.array, torch.tensor, lambda t: list(t) + [7.0],
+                                  lambda t: [str(x) for x in t], lambda t: [int(x) for x in t]])
+def test_packed_structs_hold_every_field(wmb, conv):
+    """The packed structs, field by field, from every form of theta and of a
+    structural count that the converting form takes."""
+    p = synth.param_set(0)
+    th = conv([1.0 + j for j in range(wmb.N_THETA)])
+    for n_cu in (304, 304.0, np.int64(304), 304 + (1 << 32)):
+        q = p.copy(n_cu=n_cu)
+        o = wmb.params_struct(q, th)
+        assert [getattr(o, f) for f in wmb._PFIELDS] == [304 if f == "n_cu" else getattr(p, f) for f in wmb._PFIELDS]
+        assert [o.f_clk, o.w_lo_mib, o.c_llc_mib] == [q.f_clk, q.w_lo_mib, q.c_llc_mib]
+        assert list(o.theta) == [1.0 + j for j in range(wmb.N_THETA)]
+    s = synth.seg_params(0)
+    o = wmb.segparams_struct(s)
+    assert list(o.kappa) == list(s.kappa) and (o.bw_h2d, o.bw_d2h, o.tau_memcpy) == (s.bw_h2d, s.bw_d2h, s.tau_memcpy)
+    d = wmb.DeviceDescriptors.from_host(synth.descriptors(5, 1), device="cpu")
+    o = d.struct()
+    assert [getattr(o, f) for f in d.FLOATS + d.INTS] == [getattr(d, f).data_ptr() for f in d.FLOATS + d.INTS]
+    assert o.n == 5
+    with pytest.raises(IndexError):
+        wmb.params_struct(p, [1.0] * (wmb.N_THETA - 1))
