@@ -325,7 +325,7 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
 
     // stage times
     R ip;
-    if (TILE) {   // dtype uniform over the wave: scalar selects
+    if (TILE) {   // double, few lanes: the compiler's choice of selects or a load
         ip = c.inv_peak[0];
         ip = dt == 1 ? c.inv_peak[1] : ip;
         ip = dt == 2 ? c.inv_peak[2] : ip;

@@ -192,3 +192,47 @@ def test_float32_cost_error_is_inside_the_window(wmb, orc, pset):
     say(f"tile costs ({pset}): {int(fin.sum())} feasible of {c64.size}, float32 error max {err.max():.2e}, "
         f"99.9th percentile {np.quantile(err, 0.999):.2e}; window 3e-5 / 4 = 7.5e-6")
     assert 4.0 * err.max() <= 3e-5
+
+
+_PARTS = {
+    "wave 32": dict(wave=32),
+    "byte LDS granule past 2^21": dict(lds_cu=(3 << 20) + 7, lds_gran=1),
+    "most LDS, widest granules": dict(lds_cu=1 << 24, lds_gran=1 << 20, vgpr_gran=512),
+    "little LDS": dict(lds_cu=20_000, lds_gran=4),
+    "odd VGPRs": dict(vgpr_simd=4099, vgpr_gran=1),
+    "a chip of 2^26 workgroups": dict(n_cu=65535, n_simd=16, waves_simd=64, vgpr_simd=65536, vgpr_gran=2),
+    "capped overlap": dict(combine=1, mwp=6, cwp=3),
+    "one workgroup in flight": dict(combine=1, mwp=1),
+}
+
+
+@pytest.mark.parametrize("part", _PARTS)
+def test_tile_costs_and_runs_at_the_edges(wmb, orc, part):
+    """The tile cost's integer quotients in float over structural parameters
+    at the edges of their ranges, on grids below and past 2^21 workgroups, and
+    runs of shapes whose lists are empty, split a batch, fill it exactly (704) or
+    exceed it, or put more of a list than the queue holds into the window.
+    Costs: some 30 roundings and 7 reciprocals within one ulp each are below
+    44 * 2^-23 = 5.3e-6 when all add up; a wrong quotient is off by far more."""
+    p = synth.param_set(0).copy(**_PARTS[part])
+    rng = np.random.Generator(np.random.PCG64(77))
+    tiles = synth.all_tile_codes()
+    lens = np.array([0, 1, 63, 64, 65, 350, 354, 703, 704, 705, 1500])
+    n = 700
+    cnt = lens[rng.integers(0, len(lens), n)]
+    lists = [tiles[rng.integers(0, 384, c)] if i % 5 else np.repeat(tiles[rng.integers(0, 384)], c)
+             for i, c in enumerate(cnt)]
+    off = np.zeros(n + 1, np.int32)
+    off[1:] = np.cumsum(cnt)
+    M, N, K = (np.exp(rng.uniform(0, np.log(2.0 ** 31 - 1), n)).astype(np.int64).clip(1, 2 ** 31 - 1).astype(np.int32)
+               for _ in range(3))
+    M[::3], N[::3] = rng.integers(1, 40_000, M[::3].size), rng.integers(1, 40_000, N[::3].size)
+    sh = synth.Shapes(M, N, K, rng.integers(0, 4, n).astype(np.int32), off, np.concatenate(lists).astype(np.uint32))
+    c32 = wmb.tile_costs(wmb.DeviceShapes.from_host(sh), p).cpu().numpy().astype(np.float64)
+    c64 = orc.tile_costs(p, sh)
+    fin = np.isfinite(c64)
+    assert np.array_equal(np.isfinite(c32), fin)
+    err = np.abs(c32[fin] - c64[fin]) / c64[fin]
+    say(part, "worst float32 cost error", err.max() if err.size else 0.0, "of", err.size)
+    assert err.size == 0 or err.max() <= 5.3e-6
+    _check(wmb, orc, p, sh, part)
