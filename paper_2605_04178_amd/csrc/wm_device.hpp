@@ -209,19 +209,20 @@ __device__ inline bool last_block(uint32_t* ticket, uint32_t nblocks)
 }
 
 // Column sums of rows first, first + step, ... below nrows (`stride` doubles
-// apart), by a block of 256: thread 26 g + c adds column c of every ninth row
-// from the g-th, LOADS of them in flight, so that consecutive threads read
-// consecutive doubles (one row per thread would spread each load over 64 rows);
-// its sum goes to part[26 g + c].  SHARED: rows stored by store_shared in this
-// launch.
-constexpr int kRowGroups = 9;   // 9 x 26 of the 256 threads
-template <bool SHARED, int LOADS>
+// apart), by a block of 256: thread COLS g + c adds column c of every G-th row
+// from the g-th (G groups of COLS threads), LOADS of them in flight, so that
+// consecutive threads read consecutive doubles (one row per thread would spread
+// each load over 64 rows); its sum goes to part[COLS g + c].  SHARED: rows stored
+// by store_shared in this launch.
+constexpr int kRowGroups = 256 / kAcc;   // 9 x 26 of the 256 threads
+template <bool SHARED, int LOADS, int COLS = kAcc>
 __device__ inline void column_parts(const double* rows, int nrows, int first, int step, int64_t stride, double* part)
 {
-    const int g = (int)threadIdx.x / kAcc, c = (int)threadIdx.x - g * kAcc;
-    if (g >= kRowGroups) return;
+    constexpr int G = 256 / COLS;
+    const int g = (int)threadIdx.x / COLS, c = (int)threadIdx.x - g * COLS;
+    if (g >= G) return;
     double v = 0.0;
-    const int64_t hop = (int64_t)step * kRowGroups;
+    const int64_t hop = (int64_t)step * G;
     for (int64_t r0 = first + (int64_t)step * g; r0 < nrows; r0 += hop * LOADS) {
         double x[LOADS];
 #pragma unroll
@@ -236,25 +237,28 @@ __device__ inline void column_parts(const double* rows, int nrows, int first, in
     part[threadIdx.x] = v;
 }
 
-__device__ inline double add_parts(const double* part)   // threads 0 .. 25, after a barrier
+template <int COLS = kAcc>
+__device__ inline double add_parts(const double* part)   // threads 0 .. COLS - 1, after a barrier
 {
     double v = 0.0;
 #pragma unroll
-    for (int g = 0; g < kRowGroups; ++g) v += part[g * kAcc + threadIdx.x];
+    for (int g = 0; g < 256 / COLS; ++g) v += part[g * COLS + threadIdx.x];
     return v;
 }
 
-// The end of a float64 pass: this block's row of column sums (thread j < 26:
+// The end of a float64 pass: this block's row of column sums (thread j < COLS:
 // t, plus the parts of the sweep's rows) goes to rows2, and the last block to
 // finish sums the rows.  True on the threads of that block, with tot[j] in LDS.
-__device__ inline bool finish_rows(double t, double* part /* [9 * 26] */, double* rows2, int64_t stride, uint32_t* ticket,
+template <int COLS = kAcc>
+__device__ inline bool finish_rows(double t, double* part /* [256] */, double* rows2, int64_t stride, uint32_t* ticket,
                                    double* tot)
 {
-    if (threadIdx.x < kAcc) store_shared(rows2 + (int64_t)blockIdx.x * stride + threadIdx.x, t + add_parts(part));
+    static_assert(COLS <= 64, "a row is stored by one wave");
+    if (threadIdx.x < COLS) store_shared(rows2 + (int64_t)blockIdx.x * stride + threadIdx.x, t + add_parts<COLS>(part));
     if (!last_block(ticket, gridDim.x)) return false;
-    column_parts<true, 15>(rows2, (int)gridDim.x, 0, 1, stride, part);
+    column_parts<true, 15, COLS>(rows2, (int)gridDim.x, 0, 1, stride, part);
     __syncthreads();
-    if (threadIdx.x < kAcc) tot[threadIdx.x] = add_parts(part);
+    if (threadIdx.x < COLS) tot[threadIdx.x] = add_parts<COLS>(part);
     __syncthreads();
     return true;
 }

@@ -40,6 +40,36 @@ __device__ inline SegRow load_seg(const SegPtrs& sg, int64_t i)
     return r;
 }
 
+// row base + k (base block-uniform, off = lane_offset(k))
+__device__ inline SegRow load_seg_at(const SegPtrs& sg, int64_t base, uint32_t off)
+{
+    SegRow r;
+    r.ne = ntload_at(sg.n_exec + base, off);
+    r.nk = ntload_at(sg.n_kern + base, off);
+    r.c = ntload_at(sg.cls + base, off);
+    r.h = ntload_at(sg.h2d + base, off);
+    r.dd = ntload_at(sg.d2h + base, off);
+    return r;
+}
+
+__device__ inline Desc<float> load_desc_at(const DescPtrs& d, int64_t base, uint32_t off)
+{
+    Desc<float> x;
+    x.F = ntload_at(d.F + base, off);
+    x.B = ntload_at(d.B + base, off);
+    x.r1 = ntload_at(d.r1 + base, off);
+    x.r2 = ntload_at(d.r2 + base, off);
+    x.r3 = ntload_at(d.r3 + base, off);
+    x.K = ntload_at(d.K + base, off);
+    x.u = ntload_at(d.u + base, off);
+    x.W = ntload_at(d.W + base, off);
+    x.v = ntload_at(d.vgpr + base, off);
+    x.s = ntload_at(d.lds + base, off);
+    x.gp = ntload_at(d.gpack + base, off);
+    x.G = ntload_at(d.grid + base, off);
+    return x;
+}
+
 __device__ inline bool seg_row_valid(const SegRow& r)
 {
     const float inf = __builtin_huge_valf();
@@ -72,31 +102,26 @@ __device__ inline R seg_time(R Tk, const SegRow& r, const SegConst<R>& q, R t_la
     return (R)r.ne * t;
 }
 
-// Fixed-order block sum of NA float64 accumulators into out[NA].
-template <int NA>
-__device__ inline void block_sum(double* acc, double* lds /* [waves][NA] */, double* out)
+// Block sum of eight per-thread accumulators (fixed order): the wave halves the
+// columns over lane bits 5..3 and adds over bits 2..0, which leaves column c on the
+// lanes 8c .. 8c + 7; then the waves' rows are added in LDS.  Thread c < 8 returns
+// column c.
+__device__ inline double block_reduce_eight(double* v, double* lds /* [waves][8] */)
 {
     const int lane = threadIdx.x & 63;
-    const int wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        double v = acc[j];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-        acc[j] = v;
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < NA; ++j) lds[wid * NA + j] = acc[j];
-    }
+    halve_columns<32, 4>(v, lane);
+    halve_columns<16, 2>(v, lane);
+    halve_columns<8, 1>(v, lane);
+    double s = v[0] + row_move<0x141>(row_move<0x1B>(v[0]));
+    s += row_move<0x4E>(s);
+    s += row_move<0xB1>(s);
+    if ((lane & 7) == 0) lds[(threadIdx.x >> 6) * 8 + (lane >> 3)] = s;
     __syncthreads();
-    if (threadIdx.x < NA) {
-        const int nw = blockDim.x >> 6;
-        double s = 0.0;
-        for (int w = 0; w < nw; ++w) s += lds[w * NA + threadIdx.x];
-        out[threadIdx.x] = s;
-    }
+    double t = 0.0;
+    if (threadIdx.x < 8)
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += lds[w * 8 + threadIdx.x];
     __syncthreads();
+    return t;
 }
 
 // Application totals.  A block takes BLOCK consecutive applications (one per
@@ -257,8 +282,7 @@ __device__ inline double block_total(double v, double* lds /* [BLOCK / 64] */)
 
 // The block's kAppRow float64 sums of the lanes' float32 partial sums: the 26
 // loss / count / theta columns (slots 0 and 1 from lc, 15 .. 21 from ovh, the
-// rest from acc) by the recursive-halving block reduction, the eight segment
-// sums by a plain one (fixed order throughout).
+// rest from acc) and the eight segment sums (fixed order throughout).
 template <typename LC, typename OV, typename SA>
 __device__ inline void store_row(const float* acc, LC lc, OV ovh, SA sacc, double* lds, double* row)
 {
@@ -269,7 +293,8 @@ __device__ inline void store_row(const float* acc, LC lc, OV ovh, SA sacc, doubl
     double s64[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) s64[j] = (double)sacc[j];
-    block_sum<8>(s64, lds, row + kAcc);
+    const double t = block_reduce_eight(s64, lds);
+    if (threadIdx.x < 8) row[kAcc + threadIdx.x] = t;
 }
 
 // The one-pass sweep.  A block takes BLOCK consecutive applications and walks
@@ -288,12 +313,19 @@ __device__ inline void store_row(const float* acc, LC lc, OV ovh, SA sacc, doubl
 // segment sums sit in LDS columns (they take one add per row or per
 // application), the other 17 in registers: 95 VGPRs, five waves per SIMD
 // (101 and four with all of them in registers).
+// Bound by vector instructions and loads that overlap only across a CU's five
+// blocks.  A piece therefore takes two barriers: the owners mark their rows in
+// the shadow of the rows' loads, in the one of two arrays that the other rows
+// have cleared since (138 -> 135 us at 2^20 applications; a prefetch of the next
+// piece into the L2 cost 12).
 template <int BLOCK, int MODE>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
 void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, SegSet Q,
                  const float* __restrict__ meas, double* __restrict__ rows, uint64_t* __restrict__ aflags,
-                 uint64_t* __restrict__ lflags, uint64_t* __restrict__ rflags, float* __restrict__ wrow)
+                 uint64_t* __restrict__ lflags, uint64_t* __restrict__ rflags, float* __restrict__ wrow,
+                 uint32_t* ticket)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;   // the float64 pass counts its blocks
     __shared__ float ts[BLOCK];
     __shared__ uint16_t own[BLOCK];
     __shared__ int32_t lo_s[BLOCK], hi_s[BLOCK];
@@ -335,7 +367,7 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
         bool near_mine = false, long_mine = false;
         int t0 = 0;   // first application of the next piece (uniform over the block)
         while (t0 < na) {
-            const int32_t p0 = lo_s[t0];
+            const int32_t p0 = __builtin_amdgcn_readfirstlane(lo_s[t0]);
             // an application longer than a piece becomes an empty piece here
             // (one control path, so the loop-carried sums keep one register
             // set) and is left to k_apps_long
@@ -363,9 +395,11 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
             SegRow r;
             float tsv = 0.0f;
             if (row) {
-                r = load_seg(sg, j);
+                const uint32_t off = lane_offset(tid);
+                r = load_seg_at(sg, p0, off);
+                const Desc<float> x = load_desc_at(d, p0, off);
                 const Set& Sx = uniform_const(sc);
-                evaluate<float, true>(Sx.st, Sx.cf, load_desc(d, j), E);
+                evaluate<float, true>(Sx.st, Sx.cf, x, E);
                 tsv = seg_time<float>(E.T, r, uniform_const(qc).f, Sx.cf.ov[0]);
             }
             ts[tid] = tsv;
@@ -432,6 +466,7 @@ __global__ __launch_bounds__(256) void k_apps_long(DescPtrs d, SegPtrs sg, int64
     for (int j = 0; j < 8; ++j) sacc[j] = 0.0f;
     const float inf = __builtin_huge_valf();
     const int64_t nwords = (n_apps + 63) >> 6;
+    bool any = false;
     // block b takes flag words [256 b, 256 b + 256), [256 (b + grid), ...),
     // staged in LDS by one parallel load, then walked in index order
     for (int64_t w0 = (int64_t)blockIdx.x * 256; w0 < nwords; w0 += (int64_t)gridDim.x * 256) {
@@ -439,6 +474,7 @@ __global__ __launch_bounds__(256) void k_apps_long(DescPtrs d, SegPtrs sg, int64
         const uint64_t mine = wt < nwords ? lflags[wt] : 0ull;
         words[threadIdx.x] = mine;
         if (!__syncthreads_or(mine != 0ull)) continue;   // no long application in this group
+        any = true;
         for (int q = 0; q < 256; ++q) {
         uint64_t fw = words[q];
         const int64_t wi = w0 + q;
@@ -474,84 +510,69 @@ __global__ __launch_bounds__(256) void k_apps_long(DescPtrs d, SegPtrs sg, int64
         }
         __syncthreads();   // words[] is rewritten by the next group
     }
-    store_row(acc, acc, acc + 15, sacc, red, rows + (int64_t)blockIdx.x * kAppRow);
+    double* row = rows + (int64_t)blockIdx.x * kAppRow;
+    if (any) store_row(acc, acc, acc + 15, sacc, red, row);
+    else if (threadIdx.x < kAppRow) row[threadIdx.x] = 0.0;
 }
 
-// Block sum of kAppRow float64 accumulators (fixed order): the first 26 by
-// the halving reduction, the eight segment sums by a plain one.
-__device__ inline void block_row(double* acc, double* lds, double* row)
+// The totals in LDS become [loss, count, grad theta[24], grad seg params[7]]
+// divided by the count (MODE 1), or the plain sums [grad theta[24], grad seg
+// params[7]] (MODE 2).
+template <int MODE>
+__device__ inline void apps_finish(const double* tot /* [kAppRow] */, const SegSet& Q, double* out)
 {
-    block_reduce_acc(acc, lds, row);
-    block_sum<8>(acc + kAcc, lds, row + kAcc);
-}
-
-// The final fixed-order reduction of the float64 pass's rows into [loss,
-// count, grad theta[24], grad seg params[7]] divided by the count (vjp =
-// false), or the plain sums [grad theta[24], grad seg params[7]] (vjp).
-// Thread (g, c) for c < kAppRow and g < 7 adds column c of rows g, g + 7,
-// ... (34 consecutive threads read one row: coalesced); column c is then the
-// sum of its seven partials in g order.  nrows <= kRedoMaxBlocks; called by
-// a whole block of 256.
-__device__ inline void apps_final(const double* rows, int nrows, const SegSet& Q, bool vjp,
-                                  double* part /* [7 * kAppRow] */, double* tot /* [kAppRow] */, double* out)
-{
-    constexpr int G = 256 / kAppRow;
-    constexpr int K = (kRedoMaxBlocks + G - 1) / G;   // rows per thread at most
     const int t = threadIdx.x;
-    if (t < G * kAppRow) {
-        const int g = t / kAppRow, c = t - g * kAppRow;
-        double x[K];   // every load in flight before the in-order additions
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int r = g + k * G;
-            x[k] = r < nrows ? rows[(int64_t)r * kAppRow + c] : 0.0;
-        }
-        double v = 0.0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) v += x[k];
-        part[g * kAppRow + c] = v;
-    }
-    __syncthreads();
-    if (t < kAppRow) {
-        double v = 0.0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) v += part[g * kAppRow + t];
-        tot[t] = v;
-    }
-    __syncthreads();
     const double* sa = tot + kAcc;   // extra launches, kappa[4], h2d, d2h, transfers
-    if (vjp) {
-        if (t >= kTheta + kSegParams) return;
-        double v;
-        if (t < kTheta) v = tot[2 + t] + (t == 13 ? sa[0] : 0.0);
-        else if (t < kTheta + 4) v = sa[1 + (t - kTheta)];
-        else if (t == kTheta + 4) v = -sa[5] * Q.inv_bw2_h2d;
-        else if (t == kTheta + 5) v = -sa[6] * Q.inv_bw2_d2h;
-        else v = sa[7];
-        out[t] = v;
-        return;
-    }
-    if (t >= kAppsOut) return;
-    const double c = tot[1];
-    const double ic = c > 0.0 ? 1.0 / c : 0.0;
+    const double c = MODE == 1 ? tot[1] : 1.0;
+    const double ic = MODE == 2 ? 1.0 : (c > 0.0 ? 1.0 / c : 0.0);
+    const int k = MODE == 2 ? t + 2 : t;   // place in the longer list
+    if (k >= kAppsOut) return;
     double v;
-    if (t == 0) v = tot[0] * ic;
-    else if (t == 1) v = c;
-    else if (t < kAcc) v = (tot[t] + (t == 2 + 13 ? sa[0] : 0.0)) * ic;
-    else if (t < kAcc + 4) v = sa[1 + (t - kAcc)] * ic;
-    else if (t == kAcc + 4) v = -sa[5] * Q.inv_bw2_h2d * ic;
-    else if (t == kAcc + 5) v = -sa[6] * Q.inv_bw2_d2h * ic;
+    if (k == 0) v = tot[0] * ic;
+    else if (k == 1) v = c;
+    else if (k < kAcc) v = (tot[k] + (k == 2 + 13 ? sa[0] : 0.0)) * ic;
+    else if (k < kAcc + 4) v = sa[1 + (k - kAcc)] * ic;
+    else if (k == kAcc + 4) v = -sa[5] * Q.inv_bw2_h2d * ic;
+    else if (k == kAcc + 5) v = -sa[6] * Q.inv_bw2_d2h * ic;
     else v = sa[7] * ic;
     out[t] = v;
 }
 
-// The float64 pass: block b folds the sweep's rows b, b + gridDim.x, ...
-// (fixed order); then (MODE 1) every application flagged near T = m is done
-// in full in float64 by one wave, its lanes over the rows -- total, weight,
-// loss, the rows' Jacobian terms and segment sums -- and every row flagged
-// near a max/min switch (in an application decided in float32) adds its
-// float64 Jacobian row times the weight kept in wrow.  Each block writes one
-// row to rows2.
+// One row's float64 terms for an application weight w: the Jacobian row times
+// w n_exec kappa and the segment sums, into acc[kAppRow].
+__device__ inline void add_app_row(const Set& S, const SegSet& Q, const Eval<double>& E, const SegRow& r, double w,
+                                   double* acc)
+{
+    const double ne = r.ne;
+    accumulate_partials<double>(S.st, S.cd, E, w * ne * kappa_of(Q.d, r.c), acc);
+    double* sa = acc + kAcc;
+    sa[0] += w * (ne * (double)(r.nk - 1));
+    const double v = w * (ne * E.T);
+    sa[1] += r.c == 0 ? v : 0.0;
+    sa[2] += r.c == 1 ? v : 0.0;
+    sa[3] += r.c == 2 ? v : 0.0;
+    sa[4] += r.c == 3 ? v : 0.0;
+    if (r.h > 0.0f) {
+        sa[5] += w * (ne * (double)r.h);
+        sa[7] += w * ne;
+    }
+    if (r.dd > 0.0f) {
+        sa[6] += w * (ne * (double)r.dd);
+        sa[7] += w * ne;
+    }
+}
+
+// The float64 pass and the end of the call.  Block b folds the sweep's rows b,
+// b + gridDim.x, ... (fixed order).  MODE 1: every application flagged near T = m
+// is done in full in float64 -- total, weight, loss, the rows' Jacobian terms and
+// segment sums -- by 16 lanes over its rows; a lane's first row is evaluated once
+// for both.  Every row flagged near a max/min switch (in an application decided
+// in float32) adds its float64 Jacobian row times the weight kept in wrow.  The
+// last block to finish sums the blocks' rows and writes the result.
+// Latency only, so from four blocks on the applications go to a quarter of the
+// blocks and the rows to the others (one float64 chain per block rather than
+// three), flagged rows fill the lanes, and the rows' sums are read column-wise:
+// at 2^20 applications 15.4 us against 24.8 and 4.6 for the reduction's launch.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, int64_t n_seg,
                                                          int64_t n_apps, Set S, SegSet Q,
@@ -560,36 +581,34 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
                                                          const uint64_t* __restrict__ rflags,
                                                          const float* __restrict__ wrow,
                                                          const double* __restrict__ rows1, int nrows1,
-                                                         double* __restrict__ rows2)
+                                                         double* rows2, uint32_t* ticket, double* __restrict__ out)
 {
-    __shared__ double red[4 * kAppRow];
+    __shared__ double red[4 * kAcc], part[256], sums[kAppRow], tot[kAppRow];
+    __shared__ int64_t queue[4][kFlagQueue];
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x;
+    const bool split = MODE == 1 && nb >= 4;
+    const int na = split ? nb >> 2 : nb;       // blocks of the applications: 0 .. na - 1
+    const int r0 = split ? na : 0;             // and of the rows: r0 .. nb - 1
+    column_parts<false, 2, kAppRow>(rows1, nrows1, b, nb, kAppRow, part);
     double acc[kAppRow];
 #pragma unroll
     for (int j = 0; j < kAppRow; ++j) acc[j] = 0.0;
-    for (int r = blockIdx.x + gridDim.x * threadIdx.x; r < nrows1; r += gridDim.x * blockDim.x) {
-#pragma unroll
-        for (int j = 0; j < kAppRow; ++j) acc[j] += rows1[(int64_t)r * kAppRow + j];
-    }
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    if (MODE == 1) {
+    if (MODE == 1 && b < na) {
         // Each wave loads 64 flag words at once and takes their flagged
-        // applications in batches of up to eight, in flag order: lane group
-        // grp = lane / 8 does application grp of the batch -- total, weight,
-        // loss, the rows' Jacobian terms and segment sums -- its eight lanes
-        // over the rows.
+        // applications four at a time, in flag order.
         const int64_t nwords = (n_apps + 63) >> 6;
-        const int grp = lane >> 3, sub = lane & 7;
-        for (int64_t w0 = (t0 >> 6) << 6; w0 < nwords; w0 += stride) {
+        const int grp = lane >> 4, sub = lane & 15;
+        for (int64_t w0 = ((int64_t)b * 4 + wid) * 64; w0 < nwords; w0 += (int64_t)na * 256) {
             const int64_t wl = w0 + lane;
             uint64_t rem = wl < nwords ? aflags[wl] : 0ull;   // this lane's flags not yet taken
             for (uint64_t todo = __ballot(rem != 0ull); todo; todo = __ballot(rem != 0ull)) {
                 int64_t my_app = -1;
-                for (int nb = 0; nb < 8 && todo; ++nb) {
+                for (int k = 0; k < 4 && todo; ++k) {
                     const int q = __builtin_ctzll(todo);
                     const uint64_t fw = __shfl(rem, q, 64);
-                    if (grp == nb) my_app = ((w0 + q) << 6) + __builtin_ctzll(fw);
+                    if (grp == k) my_app = ((w0 + q) << 6) + __builtin_ctzll(fw);
                     if (lane == q) rem &= rem - 1;
                     if ((fw & (fw - 1)) == 0ull) todo &= todo - 1;   // lane q has no more
                 }
@@ -600,17 +619,25 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
                     lo = lo < 0 ? 0 : (lo > n_seg ? n_seg : lo);
                     hi = hi < lo ? lo : (hi > n_seg ? n_seg : hi);
                 }
-                double part = 0.0;
-                for (int64_t j = lo + sub; j < hi; j += 8) {
+                Eval<double> E0;
+                SegRow s0;
+                double T = 0.0;
+                const int64_t j0 = lo + sub;
+                if (j0 < hi) {
+                    s0 = load_seg(sg, j0);
+                    evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j0)), E0);
+                    T = seg_time<double>(E0.T, s0, Q.d, S.cd.ov[0]);
+                }
+                for (int64_t j = j0 + 16; j < hi; j += 16) {
                     Eval<double> E;
                     evaluate<double, false>(S.st, S.cd, widen(load_desc(d, j)), E);
-                    part += seg_time<double>(E.T, load_seg(sg, j), Q.d, S.cd.ov[0]);
+                    T += seg_time<double>(E.T, load_seg(sg, j), Q.d, S.cd.ov[0]);
                 }
                 // the group's lanes end with the same (fixed-order) total
-                part += __shfl_xor(part, 4, 64);
-                part += __shfl_xor(part, 2, 64);
-                part += __shfl_xor(part, 1, 64);
-                const double T = part;
+                T += row_move<0x128>(T);
+                T += row_move<0x141>(row_move<0x1B>(T));
+                T += row_move<0x4E>(T);
+                T += row_move<0xB1>(T);
                 if (my_app < 0 || !(T - T == 0.0)) continue;
                 const double m = meas[my_app];
                 const double im = 1.0 / m;
@@ -620,53 +647,31 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
                     acc[1] += 1.0;
                 }
                 if (w == 0.0) continue;
-                for (int64_t j = lo + sub; j < hi; j += 8) {
+                const double inf = __builtin_huge_val();
+                if (j0 < hi && E0.T < inf) add_app_row(S, Q, E0, s0, w, acc);
+                for (int64_t j = j0 + 16; j < hi; j += 16) {
                     Eval<double> E;
                     evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j)), E);
-                    if (!(E.T < __builtin_huge_val())) continue;
-                    const SegRow r = load_seg(sg, j);
-                    const double ne = r.ne;
-                    accumulate_partials<double>(S.st, S.cd, E, w * ne * kappa_of(Q.d, r.c), acc);
-                    double* sa = acc + kAcc;
-                    sa[0] += w * (ne * (double)(r.nk - 1));
-                    const double v = w * (ne * E.T);
-                    sa[1] += r.c == 0 ? v : 0.0;
-                    sa[2] += r.c == 1 ? v : 0.0;
-                    sa[3] += r.c == 2 ? v : 0.0;
-                    sa[4] += r.c == 3 ? v : 0.0;
-                    if (r.h > 0.0f) {
-                        sa[5] += w * (ne * (double)r.h);
-                        sa[7] += w * ne;
-                    }
-                    if (r.dd > 0.0f) {
-                        sa[6] += w * (ne * (double)r.dd);
-                        sa[7] += w * ne;
-                    }
+                    if (E.T < inf) add_app_row(S, Q, E, load_seg(sg, j), w, acc);
                 }
             }
         }
     }
-    const int64_t rwords = (n_seg + 63) >> 6;
-    for (int64_t wi = t0; wi < rwords; wi += stride) {
-        uint64_t fw = rflags[wi];
-        while (fw) {
-            const int bit = __builtin_ctzll(fw);
-            fw &= fw - 1;
-            const int64_t j = (wi << 6) + bit;
-            Eval<double> E;
-            evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j)), E);
-            if (E.T < __builtin_huge_val()) accumulate_partials<double>(S.st, S.cd, E, (double)wrow[j], acc);
-        }
-    }
-    block_row(acc, red, rows2 + (int64_t)blockIdx.x * kAppRow);
-}
-
-__global__ __launch_bounds__(256) void k_apps_final(const double* __restrict__ rows, int nrows, SegSet Q,
-                                                    int vjp, double* __restrict__ out)
-{
-    __shared__ double part[(256 / kAppRow) * kAppRow];
-    __shared__ double tot[kAppRow];
-    apps_final(rows, nrows, Q, vjp != 0, part, tot, out);
+    if (b >= r0)
+        for_flagged(FlagWalk(rflags, (n_seg + 63) >> 6, ((int64_t)(b - r0) * 4 + wid) * 64, (int64_t)(nb - r0) * 256),
+                    queue[wid], [&](int64_t j) {
+                        Eval<double> E;
+                        evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j)), E);
+                        if (E.T < __builtin_huge_val())
+                            accumulate_partials<double>(S.st, S.cd, E, (double)wrow[j], acc);
+                    });
+    const double s = block_reduce_eight(acc + kAcc, red);
+    if (threadIdx.x < 8) sums[kAcc + threadIdx.x] = s;
+    const double t = block_reduce_value(acc, red);
+    if (threadIdx.x < kAcc) sums[threadIdx.x] = t;
+    __syncthreads();
+    if (finish_rows<kAppRow>(threadIdx.x < kAppRow ? sums[threadIdx.x] : 0.0, part, rows2, kAppRow, ticket, tot))
+        apps_finish<MODE>(tot, Q, out);
 }
 
 __global__ __launch_bounds__(256) void k_zero_words(uint64_t* __restrict__ w, int64_t n)
@@ -727,12 +732,24 @@ static hipError_t apps_grad_t(const DescPtrs& d, const SegPtrs& sg, int64_t n_se
         const int64_t zb = (rwords + 255) / 256;
         k_zero_words<<<(int)(zb < 1024 ? zb : 1024), 256, 0, s>>>(rflags, rwords);
     }
-    int nb1 = 1;
+    // the rows of the sweep, of the long applications and of the float64 pass,
+    // and the pass's count of finished blocks in the first row past them (one
+    // block less where every row is taken)
+    constexpr int kRows = kAppsMaxBlocks + kAppsLongBlocks + kRedoMaxBlocks;
+    int nb1 = 1, nrows1 = 0, nb2 = 1;
+    uint32_t* ticket = nullptr;
+    const auto place = [&] {
+        nrows1 = nb1 + kAppsLongBlocks;
+        nb2 = apps_redo_blocks(n_apps, n_seg);
+        nb2 = nrows1 + nb2 < kRows ? nb2 : kRows - nrows1 - 1;
+        ticket = (uint32_t*)(rows + (int64_t)(nrows1 + nb2) * kAppRow);
+    };
 #define WM_APPS_CASE(B)                                                                               \
     case B:                                                                                           \
         nb1 = apps_grid<B, MODE>(n_apps, c.grid_mult);                                               \
+        place();                                                                                      \
         k_apps_grad<B, MODE><<<nb1, B, 0, s>>>(d, sg, n_seg, n_apps, S, Q, meas, rows, aflags, lflags, \
-                                               rflags, wrow);                                        \
+                                               rflags, wrow, ticket);                                \
         break;
     switch (c.block) {
         WM_APPS_CASE(64)
@@ -748,14 +765,8 @@ static hipError_t apps_grad_t(const DescPtrs& d, const SegPtrs& sg, int64_t n_se
                                                       wrow, rows + (int64_t)nb1 * kAppRow);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int nb2 = apps_redo_blocks(n_apps, n_seg);
-    const int nrows1 = nb1 + kAppsLongBlocks;
-    double* rows2 = rows + (int64_t)nrows1 * kAppRow;
-    k_apps_grad_redo<MODE><<<nb2, 256, 0, s>>>(d, sg, n_seg, n_apps, S, Q, meas, aflags, rflags, wrow, rows,
-                                               nrows1, rows2);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_apps_final<<<1, 256, 0, s>>>(rows2, nb2, Q, MODE == 2 ? 1 : 0, out);
+    k_apps_grad_redo<MODE><<<nb2, 256, 0, s>>>(d, sg, n_seg, n_apps, S, Q, meas, aflags, rflags, wrow, rows, nrows1,
+                                               rows + (int64_t)nrows1 * kAppRow, ticket, out);
     return hipGetLastError();
 }
 

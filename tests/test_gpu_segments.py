@@ -218,3 +218,29 @@ def test_apps_vjp_and_autograd(wmb, orc):
                         (np.float32, np.int32, np.int32, np.float32, np.float32)])
     z = wmb.apps_vjp(*_dev(wmb, s0, d0), torch.zeros(0, device="cuda"), p, q)
     assert np.array_equal(z.cpu().numpy(), np.zeros(31))
+
+
+@pytest.mark.parametrize("n_apps,smin,smax", [(1, 1, 1), (5, 200, 700), (300, 0, 40), (12_000, 0, 40), (70_000, 0, 2),
+                                              (9_000, 30, 33)])
+def test_apps_float64_pass_splits(wmb, orc, n_apps, smin, smax):
+    """The float64 pass on one block, on few blocks (applications and rows on
+    the same) and on enough to split them, with every third application
+    decided in float64, on rows past a lane group's 16, on applications longer
+    than a piece, and with empty ones among them; every replay of a workspace
+    counts its blocks afresh.  Tolerance: that of every gradient check here."""
+    p = synth.param_set(8)
+    q = synth.seg_params(18)
+    sg, d = synth.segments(n_apps, 151 + n_apps, smin, smax)
+    Ta, _ = orc.predict_apps(p, q, d, sg)
+    noise = synth.lognormal_noise(n_apps, 152, 0.05)
+    noise[::3] = 1.0
+    m = Ta * noise
+    first = _grad_check(wmb, orc, p, q, sg, d, m, f"{n_apps} of {smin}-{smax}")
+    dd, ds = _dev(wmb, sg, d)
+    mt = torch.from_numpy(np.asarray(m, np.float32)).cuda()
+    ws = torch.full((wmb.apps_workspace_bytes(dd.n, ds.n_apps),), 255, dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        assert np.array_equal(wmb.apps_loss_grad(dd, ds, mt, p, q, ws=ws).cpu().numpy(), first)
+    w = torch.ones(n_apps, dtype=torch.float32, device="cuda")
+    g = [wmb.apps_vjp(dd, ds, w, p, q, ws=ws).cpu().numpy() for _ in range(2)]
+    assert np.array_equal(g[0], g[1]) and np.isfinite(g[0]).all()
