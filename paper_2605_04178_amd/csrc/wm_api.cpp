@@ -86,14 +86,17 @@ Struct make_struct(const wm_params_t* p)
     Struct s;
     std::memset(&s, 0, sizeof(s));
     s.n_levels = p->n_levels;
-    s.n_cu = p->n_cu;
-    s.n_simd = p->n_simd;
+    s.n_cu = (float)p->n_cu;
+    s.n_simd = (float)p->n_simd;
     s.wave_shift = ilog2(p->wave);
-    s.vgpr_simd = p->vgpr_simd;
-    s.vgpr_gran_mask = p->vgpr_gran - 1;
-    s.waves_simd = p->waves_simd;
+    // powers of two and integers below 2^24: every one of these floats is exact
+    // (lds_units is not from 2^23 on, where the device does not use it)
+    s.inv_vgran = 1.0f / (float)p->vgpr_gran;
+    s.vgpr_units = ((float)p->vgpr_simd + 0.5f) * s.inv_vgran;
+    s.waves_simd = (float)p->waves_simd;
     s.lds_cu = p->lds_cu;
-    s.lds_gran_mask = p->lds_gran - 1;
+    s.inv_lgran = 1.0f / (float)p->lds_gran;
+    s.lds_units = ((float)p->lds_cu + 0.5f) * s.inv_lgran;
     s.mwp = p->mwp;
     s.cwp = p->cwp;
     s.combine = p->combine;

@@ -29,9 +29,17 @@ constexpr int kTheta = 24;
 constexpr int kAcc = 26;  // loss, count, 24 gradient slots
 
 // structural integers of a parameter set, as the kernels use them
+// The occupancy's limits are held as the floats its quotients need (all exact):
+// counts as they are, (VGPRs + 1/2) and (LDS bytes + 1/2) in granules.
 struct Struct {
-    int32_t n_levels, n_cu, n_simd, wave_shift, vgpr_simd, vgpr_gran_mask, waves_simd, lds_cu,
-        lds_gran_mask, mwp, cwp, combine, bytes_inflight_wave, pad_;
+    int32_t n_levels;
+    float n_cu, n_simd;
+    int32_t wave_shift;
+    float vgpr_units, inv_vgran, waves_simd;
+    int32_t lds_cu;
+    float inv_lgran;
+    int32_t mwp, cwp, combine, bytes_inflight_wave;
+    float lds_units;
     double f_clk, w_lo_mib, c_llc_mib;
 };
 
@@ -116,19 +124,8 @@ template <> struct Ar<double> {
     static __device__ inline double ex2(double x) { return exp2(x); }
 };
 
-// floor(a / b) for a < 2^24, 1 <= b < 2^24 and a quotient below 2^21: the
-// float estimate a * rcp(b) is within 0.37 of a / b (rcp 1 ulp, product
-// 0.5 ulp), so truncation is off by at most one, which the remainder fixes.
-__device__ inline uint32_t udiv_small(uint32_t a, uint32_t b)
-{
-    uint32_t q = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
-    const int32_t r = (int32_t)(a - __umul24(q, b));   // q, b < 2^24: low 32 bits
-    q = r < 0 ? q - 1u : (r >= (int32_t)b ? q + 1u : q);
-    return q;
-}
-
-// floor(a / b) for integers a < 2^21 and 1 <= b < 2^24 without a remainder
-// correction.  With q = floor(a / b), the value (a + 1/2) / b lies in
+// floor(a / b) for integers a < 2^21 and 1 <= b < 2^24 from the hardware
+// reciprocal, without a remainder correction.  With q = floor(a / b), the value (a + 1/2) / b lies in
 // [q + 1/(2b), q + 1 - 1/(2b)].  a + 1/2 and b are exact in float, the
 // hardware reciprocal is within 1 ulp (2^-23 relative) and the product adds
 // one rounding (2^-24), so the estimate is within (a + 1/2)/b * 1.51 * 2^-23
@@ -148,7 +145,8 @@ __device__ inline bool finite_nonneg(double x) { return x >= 0.0 && x < __builti
 // h_LLC exponent of its regime, the scale of a segment's class) written on
 // such copies stays a register select; on the parameters themselves the
 // compiler may turn it into a per-lane indexed load from the kernel-argument
-// segment, a vector memory access with its latency inside the evaluation.
+// segment, a vector memory access with its latency inside the evaluation.  The
+// copies are made before the select: made in its arms, each arm is a branch.
 // float (the bulk sweeps): a scalar register, which v_cndmask reads
 // directly -- the sweeps' parameter sets are wave-uniform, and a divergent
 // one would not compile; double (the rare re-evaluations): a vector register.
@@ -170,37 +168,69 @@ struct Desc {
 };
 
 // ---------------------------------------------------------------------------
-// occupancy (exact integers)
+// occupancy (exact integers, held in floats)
 // ---------------------------------------------------------------------------
 struct Occ {
-    int32_t o, k;
+    float o, k;
 };
 
+// of two floats >= 0, as a median: fminf and fmaxf first quiet each operand
+// that does not come straight from arithmetic
+__device__ inline float least(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+__device__ inline float most(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf()); }
+
+// floor(lds_cu / s rounded up to the granule) for LDS capacities past udiv21's
+// range, at most 1024: it only matters below o_w <= 1024.
+__device__ inline float lds_limit_wide(const Struct& st, uint32_t s)
+{
+    const uint32_t cu = (uint32_t)st.lds_cu;
+    if (s > cu) return 0.0f;
+    const uint32_t mask = (uint32_t)(1.0f / st.inv_lgran) - 1u;
+    const uint32_t q = cu / ((s + mask) & ~mask);
+    return (float)(q < 1024u ? q : 1024u);
+}
+
+// The quotients run in float from end to end: with (a + 1/2) / b in place of a / b
+// the floor of the hardware reciprocal's estimate is exact for a below 2^21
+// (udiv21: VGPR_SIMD <= 65536, N_SIMD * waves <= 1024, LDS by its own branch),
+// scaling both sides by a power of two changes no digit, so that rounding up to
+// a granule is a ceil, and of two limits the floor is taken once.  A need that
+// exceeds the resource gives a quotient below one and no LDS (s = 0) an infinite
+// one, so neither takes a test.  The gradient sweep of 2^24 rows is as near to its
+// vector instructions as to memory: on integers, with a conversion around each
+// quotient and a branch per test and per selected parameter, it issued 75.8e6
+// vector and 31.2e6 scalar instructions (157.3 us), this way 69.9e6 and 23.9e6
+// (155.0).
 __device__ inline Occ occupancy(const Struct& st, int32_t v, int32_t s, int32_t g)
 {
-    // the first two dividends are below 2^21 by the parameter limits
-    // (VGPR_SIMD <= 65536, N_SIMD * waves <= 1024): udiv21 is exact; the LDS
-    // dividend reaches 2^24 and takes udiv_small
     Occ r;
-    r.k = (g + (1 << st.wave_shift) - 1) >> st.wave_shift;
-    int32_t w = 0;
-    if (v <= st.vgpr_simd) {
-        int32_t va = (v + st.vgpr_gran_mask) & ~st.vgpr_gran_mask;
-        w = (int32_t)udiv21((uint32_t)st.vgpr_simd, (uint32_t)va);
-        w = w < st.waves_simd ? w : st.waves_simd;
-    }
-    int32_t o = (int32_t)udiv21(__umul24((uint32_t)st.n_simd, (uint32_t)w), (uint32_t)r.k);
-    if (s > 0) {
-        int32_t ol = 0;
-        if (s <= st.lds_cu) {
-            int32_t sa = (s + st.lds_gran_mask) & ~st.lds_gran_mask;
-            // o_l only matters below o_w <= 1024: cap it there so the quotient stays small
-            ol = (sa <= (st.lds_cu >> 10)) ? 1024 : (int32_t)udiv_small((uint32_t)st.lds_cu, (uint32_t)sa);
-        }
-        o = o < ol ? o : ol;
-    }
-    r.o = o;
+    r.k = (float)((g + (1 << st.wave_shift) - 1) >> st.wave_shift);
+    const float vu = __builtin_ceilf((float)v * st.inv_vgran);
+    const float w = least(__builtin_floorf(st.vgpr_units * __builtin_amdgcn_rcpf(vu)), st.waves_simd);
+    const float ow = __builtin_fmaf(w, st.n_simd, 0.5f) * __builtin_amdgcn_rcpf(r.k);
+    float ol = st.lds_units * __builtin_amdgcn_rcpf(__builtin_ceilf((float)s * st.inv_lgran));
+    if (st.lds_cu >= (1 << 21) && s > 0) ol = lds_limit_wide(st, (uint32_t)s);
+    r.o = __builtin_floorf(least(ow, ol));
     return r;
+}
+
+// ceil(G / (n_cu o)) workgroup rounds for o >= 1
+template <typename R>
+__device__ inline R rounds(const Struct& st, int32_t G, float o)
+{
+    // exact below 2^21; larger counts (grids beyond ~2^21 workgroups) take an
+    // integer division, behind a branch that the whole wave skips unless one of
+    // its lanes needs it
+    const float pr = st.n_cu * o, fG = (float)G;
+    R nr = (R)__builtin_floorf((fG + (pr - 0.5f)) * __builtin_amdgcn_rcpf(pr));
+    const bool big = fG + pr >= 2097152.0f;
+    if (__builtin_expect(__ballot(big) != 0, 0)) {
+        if (big) {
+            const uint32_t p = (uint32_t)st.n_cu * (uint32_t)o;
+            nr = (R)(((uint32_t)G + p - 1u) / p);
+        }
+    }
+    return nr;
 }
 
 template <typename R>
@@ -225,7 +255,7 @@ template <typename R>
 struct Eval {
     R T;
     int32_t occ;       // -1 invalid, 0 infeasible, else o
-    int32_t dt, nr, G;
+    int32_t dt, G;
     int32_t cnt[4];    // n_conc - 1, n_dev - 1, fused, n_sync
     int32_t llc_regime;  // 0 none/resident, 1 transition, 2 streaming
     R h3, s1, s2, s3, sh, a12, S, Lf, e, bwh, W;
@@ -265,25 +295,13 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
     E.cnt[3] = TILE ? 0 : (d.gp >> 21) & 15;
     E.G = d.G;
 
-    Occ oc = occupancy(st, d.v, d.s, g);
-    E.occ = oc.o;
-    if (oc.o == 0) {
+    const Occ oc = occupancy(st, d.v, d.s, g);
+    E.occ = (int32_t)oc.o;
+    if (oc.o == 0.0f) {
         E.T = (R)__builtin_huge_val();
         return;
     }
-    // n_cu <= 65536 and o <= 1024: 24-bit multiplies are exact
-    const uint32_t per_round = __umul24((uint32_t)st.n_cu, (uint32_t)oc.o);
-    const uint32_t num = (uint32_t)d.G + per_round - 1u;
-    // udiv21 is exact below 2^21 (per_round <= num is then below 2^21 too);
-    // larger counts (grids beyond ~2^21 workgroups) take an exact division,
-    // behind a branch that the whole wave skips unless one of its lanes needs it
-    const bool big = num >= (1u << 21);
-    uint32_t nru = udiv21(big ? 0u : num, big ? 1u : per_round);
-    if (__builtin_expect(__ballot(big) != 0, 0)) {
-        if (big) nru = num / per_round;
-    }
-    const int32_t nr = (int32_t)nru;
-    E.nr = nr;
+    const R nr = rounds<R>(st, d.G, oc.o);
 
     // traffic split: with W > 0 and an LLC, h_LLC(W) replaces r3
     // (Table "hlcc-piecewise"): 1 below W_lo, base^alpha in the transition
@@ -296,9 +314,11 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
         const int reg = Wm < c.w_lo ? 0 : (Wm <= c.c_llc ? 1 : 2);
         // (1 - (W - W_lo)/(C - W_lo)) written as (C - W)/(C - W_lo): same
         // value, no cancellation near C
-        R x = reg == 1 ? (c.c_llc - Wm) * c.inv_span : c.c_llc * A::rcp(Wm);
+        const R xa = (c.c_llc - Wm) * c.inv_span, xb = c.c_llc * A::rcp(Wm);
+        R x = reg == 1 ? xa : xb;
         x = reg == 0 ? (R)1 : x;
-        const R y = reg == 1 ? vreg(c.alpha) : vreg(c.beta);
+        const R ya = vreg(c.alpha), yb = vreg(c.beta);
+        const R y = reg == 1 ? ya : yb;
         const R l2 = A::lg2(x);
         h3 = x > (R)0 ? A::ex2(y * l2) : (R)0;
         E.llc_regime = reg;
@@ -315,8 +335,8 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
     }
     // Eq. (16) blend of the HBM bandwidth
     R e = (R)0, bwh = c.bw[3];
-    if (!TILE && c.blend_on && d.W > (R)0) {
-        e = A::ex2(d.W * c.blend_k);
+    if (!TILE && c.blend_on) {
+        e = d.W > (R)0 ? A::ex2(d.W * c.blend_k) : (R)0;
         bwh = c.bw[3] + c.bp_minus_bw * e;
     }
     const R S = TILE ? s2 * c.bw[1] + sh * bwh : s1 * c.bw[0] + s2 * c.bw[1] + s3 * c.bw[2] + sh * bwh;
@@ -332,19 +352,20 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
         ip = dt == 3 ? c.inv_peak[3] : ip;
         ip = dt == 4 ? c.inv_peak[4] : ip;
     } else {
-        ip = vreg(c.inv_peak[0]);
-        ip = dt == 1 ? vreg(c.inv_peak[1]) : ip;
-        ip = dt == 2 ? vreg(c.inv_peak[2]) : ip;
-        ip = dt == 3 ? vreg(c.inv_peak[3]) : ip;
-        ip = dt == 4 ? vreg(c.inv_peak[4]) : ip;
+        const R p0 = vreg(c.inv_peak[0]), p1 = vreg(c.inv_peak[1]), p2 = vreg(c.inv_peak[2]),
+                p3 = vreg(c.inv_peak[3]), p4 = vreg(c.inv_peak[4]);
+        ip = dt == 1 ? p1 : p0;
+        ip = dt == 2 ? p2 : ip;
+        ip = dt == 3 ? p3 : ip;
+        ip = dt == 4 ? p4 : ip;
     }
     const R Tc = TILE ? d.F * ip : d.F * ip * A::rcp(d.u);
     const R iS = A::rcp(S);
     const R Tb = d.B * iS;
-    const R q = (R)nr * d.B * A::rcp((R)d.G * (R)oc.k) * c.inv_lw;
+    const R q = nr * d.B * A::rcp((R)d.G * (R)oc.k) * c.inv_lw;
     const R Tlat = q * Lf;
 
-    const R nrK = (R)nr * d.K;
+    const R nrK = nr * d.K;
     const R Tov = TILE ? c.ov[0] + c.ov[1] * (R)d.G + c.ov[2] * nrK
                        : c.ov[0] + c.ov[1] * (R)d.G + c.ov[2] * nrK + (R)E.cnt[0] * c.ov[3] +
                              (R)E.cnt[1] * c.ov[4] + (R)E.cnt[2] * c.ov[5] + (R)E.cnt[3] * c.ov[6];
@@ -355,20 +376,19 @@ __device__ inline void evaluate(const Struct& st, const Const<R>& c, const Desc<
     bool near = false;
     const R tol = (R)1e-5;
     if (st.combine == 0) {
-        if (Tc >= Tb && Tc >= Tlat) {
-            step = Tc;
-            wc = (R)1;
-            if (FULL) near = (Tc - Tm) <= tol * Tc;
-        } else {
-            step = Tm;
-            if (mem_b) wb = (R)1; else wl = (R)1;
-            if (FULL) {
-                const R second = Tc > (mem_b ? Tlat : Tb) ? Tc : (mem_b ? Tlat : Tb);
-                near = (Tm - second) <= tol * Tm;
-            }
+        const bool c_first = (Tc >= Tb) & (Tc >= Tlat);
+        step = c_first ? Tc : Tm;
+        if (FULL) {
+            wc = c_first ? (R)1 : (R)0;
+            wb = !c_first && mem_b ? (R)1 : (R)0;
+            wl = !c_first && !mem_b ? (R)1 : (R)0;
+            const R mn = mem_b ? Tlat : Tb;
+            const R of_mem = Tc > mn ? Tc : mn;
+            const R second = c_first ? Tm : of_mem;
+            near = (step - second) <= tol * step;
         }
     } else {
-        int32_t neff = (int32_t)__umul24((uint32_t)oc.o, (uint32_t)oc.k);
+        int32_t neff = (int32_t)(oc.o * oc.k);
         if (st.mwp > 0) neff = neff < st.mwp ? neff : st.mwp;
         if (st.cwp > 0) neff = neff < st.cwp ? neff : st.cwp;
         const R a = (R)(neff - 1);

@@ -80,10 +80,10 @@ __device__ inline bool seg_row_valid(const SegRow& r)
 template <typename R>
 __device__ inline R kappa_of(const SegConst<R>& q, int32_t c)
 {
-    R k = vreg(q.kappa[0]);
-    k = c == 1 ? vreg(q.kappa[1]) : k;
-    k = c == 2 ? vreg(q.kappa[2]) : k;
-    k = c == 3 ? vreg(q.kappa[3]) : k;
+    const R k0 = vreg(q.kappa[0]), k1 = vreg(q.kappa[1]), k2 = vreg(q.kappa[2]), k3 = vreg(q.kappa[3]);
+    R k = c == 1 ? k1 : k0;
+    k = c == 2 ? k2 : k;
+    k = c == 3 ? k3 : k;
     return k;
 }
 
@@ -94,12 +94,12 @@ __device__ inline R kappa_of(const SegConst<R>& q, int32_t c)
 template <typename R>
 __device__ inline R seg_time(R Tk, const SegRow& r, const SegConst<R>& q, R t_launch)
 {
-    if (!seg_row_valid(r) || !(Tk == Tk)) return (R)__builtin_nan("");
-    if (!(Tk < (R)__builtin_huge_val())) return Tk;
     R t = kappa_of(q, r.c) * Tk + (R)(r.nk - 1) * t_launch;
-    if (r.h > 0.0f) t += (R)r.h * q.inv_bw_h2d + q.tau;
-    if (r.dd > 0.0f) t += (R)r.dd * q.inv_bw_d2h + q.tau;
-    return (R)r.ne * t;
+    const R up = (R)r.h * q.inv_bw_h2d + q.tau, down = (R)r.dd * q.inv_bw_d2h + q.tau;
+    t += r.h > 0.0f ? up : (R)0;
+    t += r.dd > 0.0f ? down : (R)0;
+    t = Tk < (R)__builtin_huge_val() ? (R)r.ne * t : Tk;
+    return seg_row_valid(r) && Tk == Tk ? t : (R)__builtin_nan("");
 }
 
 // Block sum of eight per-thread accumulators (fixed order): the wave halves the
@@ -255,14 +255,11 @@ __device__ inline void app_row_terms(const Struct& st, const Const<float>& cf, c
     sacc[2] += r.c == 1 ? v : 0.0f;
     sacc[3] += r.c == 2 ? v : 0.0f;
     sacc[4] += r.c == 3 ? v : 0.0f;
-    if (r.h > 0.0f) {
-        sacc[5] += wa * (r.ne * r.h);
-        sacc[7] += wa * r.ne;
-    }
-    if (r.dd > 0.0f) {
-        sacc[6] += wa * (r.ne * r.dd);
-        sacc[7] += wa * r.ne;
-    }
+    // (no transfer has no bytes)
+    sacc[5] += wa * (r.ne * r.h);
+    sacc[6] += wa * (r.ne * r.dd);
+    const float s0 = sacc[7], s1 = r.h > 0.0f ? __builtin_fmaf(wa, r.ne, s0) : s0;
+    sacc[7] = r.dd > 0.0f ? __builtin_fmaf(wa, r.ne, s1) : s1;
 }
 
 // float64 sum of one value over the block (fixed order); every thread gets it

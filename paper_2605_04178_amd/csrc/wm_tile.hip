@@ -74,21 +74,13 @@ __device__ inline double exact_cost(const Set& S, int32_t M, int32_t N, int32_t 
 //     their float forms are built from their exponents.
 //   - What only the shape decides (compulsory traffic, the dtype's peak) sits in
 //     the shape's record.
-//   - The occupancy's quotients of small integers run in float throughout: with
-//     (a + 1/2) / b in place of a / b the floor of the hardware reciprocal's
-//     estimate is exact below 2^21 (udiv21), scaling both sides by a power of two
-//     changes no digit, and the rounding up to a granule is a ceil.  A limit that
-//     the resources exceed gives a quotient below one, so it needs no test of its
-//     own.  One reciprocal of the waves per workgroup serves four quotients.
+//   - The quotients run in float as in occupancy(), VGPRs per thread included, and
+//     one reciprocal of the waves per workgroup serves four of them.
 // Invalid codes and infeasible tiles cost +inf.  No term can be NaN: parameters
 // are finite with positive bandwidths and peaks, and products stay below 2^108.
 // ---------------------------------------------------------------------------
 struct TileConst {
     float waves_half, pan_scale, pan_half;    // 2^-(s+1), 2^-(s+2), 2^-(s+3), s = log2 of the wave
-    float inv_vgran, v_base, v_units;         // 1 / granule, 16 / granule, (VGPRs + 1/2) / granule
-    float n_simd, waves_simd, n_cu;
-    float lds_scale, lds_units;               // 2 / granule, (LDS bytes + 1/2) / granule
-    int32_t lds_wide;                         // LDS capacity past udiv21's range
     float neff_max;                           // the smaller of MWP and CWP that is set
     uint32_t acc_exp;                         // exponent field of 2^(10 - s)
 };
@@ -97,19 +89,9 @@ static TileConst tile_const(const Struct& st)
 {
     TileConst k;
     const float w = 1.0f / (float)(1 << st.wave_shift);
-    const float vg = (float)(st.vgpr_gran_mask + 1), lg = (float)(st.lds_gran_mask + 1);
     k.waves_half = w / 2.0f;
     k.pan_scale = w / 4.0f;
     k.pan_half = w / 8.0f;
-    k.inv_vgran = 1.0f / vg;
-    k.v_base = 16.0f / vg;
-    k.v_units = ((float)st.vgpr_simd + 0.5f) / vg;
-    k.n_simd = (float)st.n_simd;
-    k.waves_simd = (float)st.waves_simd;
-    k.n_cu = (float)st.n_cu;
-    k.lds_scale = 2.0f / lg;
-    k.lds_units = ((float)st.lds_cu + 0.5f) / lg;
-    k.lds_wide = st.lds_cu >= (1 << 21);
     // workgroups times waves per CU stay below 2^14, so a bound of 2^20 bounds nothing
     int32_t m = 1 << 20;
     if (st.mwp > 0 && st.mwp < m) m = st.mwp;
@@ -149,10 +131,10 @@ __device__ inline TileShape tile_shape(const Const<float>& c, const TileConst& k
     z.K4 = ok ? (K - 1) >> 4 : 0;
     z.MN = fM * fN * (float)eo;
     z.U = (fM * fK + fK * fN) * (float)(1u << le) + z.MN;
-    float ip = vreg(c.inv_peak[0]);
-    ip = t == 1 ? vreg(c.inv_peak[1]) : ip;
-    ip = t == 2 ? vreg(c.inv_peak[2]) : ip;
-    ip = t == 3 ? vreg(c.inv_peak[3]) : ip;
+    const float p0 = vreg(c.inv_peak[0]), p1 = vreg(c.inv_peak[1]), p2 = vreg(c.inv_peak[2]), p3 = vreg(c.inv_peak[3]);
+    float ip = t == 1 ? p1 : p0;
+    ip = t == 2 ? p2 : ip;
+    ip = t == 3 ? p3 : ip;
     z.MN = ok ? z.MN : 0.0f;
     z.U = ok ? z.U : 0.0f;
     z.ip = ok ? ip : __builtin_huge_valf();            // an invalid shape costs +inf
@@ -160,11 +142,6 @@ __device__ inline TileShape tile_shape(const Const<float>& c, const TileConst& k
     z.D = 0;
     return z;
 }
-
-// of two floats >= 0, as a median: fminf and fmaxf first quiet each operand
-// that does not come straight from arithmetic
-__device__ inline float least(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
-__device__ inline float most(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf()); }
 
 __device__ inline float pow2_bits(uint32_t b) { return __uint_as_float(b); }
 
@@ -182,29 +159,25 @@ __device__ inline float tile_cost(const Struct& st, const Const<float>& c, const
     // VGPRs: accumulators and the panel share per thread
     const float va = __builtin_floorf((pow2_bits((mn + z.e) << 23) + (fw - k.waves_half)) * rw);
     const float vp = __builtin_floorf((__builtin_fmaf(pan, k.pan_scale, fw) - k.pan_half) * rw);
-    const float vu = __builtin_ceilf(__builtin_fmaf(va + vp, k.inv_vgran, k.v_base));
-    const float w = least(__builtin_floorf(k.v_units * __builtin_amdgcn_rcpf(vu)), k.waves_simd);
-    const float ow = __builtin_fmaf(w, k.n_simd, 0.5f) * rw;
-    const float lu = __builtin_ceilf(pan * k.lds_scale);
-    float ol = k.lds_units * __builtin_amdgcn_rcpf(lu);
-    if (k.lds_wide) {   // uniform: past udiv21's range the quotient is corrected
-        const uint32_t sa = ((uint32_t)(pan * 2.0f) + (uint32_t)st.lds_gran_mask) & ~(uint32_t)st.lds_gran_mask;
-        ol = sa <= (uint32_t)(st.lds_cu >> 10) ? 1024.0f : (float)udiv_small((uint32_t)st.lds_cu, sa);
-    }
+    const float vu = __builtin_ceilf((va + vp + 16.0f) * st.inv_vgran);
+    const float w = least(__builtin_floorf(st.vgpr_units * __builtin_amdgcn_rcpf(vu)), st.waves_simd);
+    const float ow = __builtin_fmaf(w, st.n_simd, 0.5f) * rw;
+    const float lds = pan * 2.0f;
+    float ol = st.lds_units * __builtin_amdgcn_rcpf(__builtin_ceilf(lds * st.inv_lgran));
+    if (st.lds_cu >= (1 << 21)) ol = lds_limit_wide(st, (uint32_t)lds);
     const float o = __builtin_floorf(least(ow, ol));
     bool ok = code < 512u && kd != 3u && o > 0.0f;
 
     // rounds of workgroups over the chip
-    const float pr = k.n_cu * o;
+    const float pr = st.n_cu * o;
     float G = (float)gm * (float)gn;
     float nr = __builtin_floorf((G + (pr - 0.5f)) * __builtin_amdgcn_rcpf(pr));
-    // from 2^21 on an exact division (and the grid limit), behind a branch
-    // that the whole wave skips unless one of its lanes needs it
+    // from 2^21 on an exact division (and the grid limit), as in rounds()
     const bool big = G + pr >= 2097152.0f;
     if (__builtin_expect(__ballot(big) != 0, 0)) {
         if (big) {
             const uint64_t Gi = (uint64_t)gm * gn;
-            const uint32_t p = __umul24((uint32_t)st.n_cu, (uint32_t)o);
+            const uint32_t p = (uint32_t)st.n_cu * (uint32_t)o;
             ok = ok && Gi <= 0x7fffffffull;
             G = (float)Gi;
             nr = ok ? (float)(((uint32_t)Gi + p - 1u) / p) : 1.0f;

@@ -215,3 +215,36 @@ def test_predict_hand_worked_latency_and_overhead_rows(wmb):
     err = rel_err(T.cpu().numpy(), want_T)
     say("hand-worked rows on the GPU: max rel err", err.max())
     assert err.max() <= TOL
+
+
+@pytest.mark.parametrize("part", [
+    dict(), dict(wave=32, waves_simd=64, vgpr_simd=65536, vgpr_gran=1), dict(vgpr_simd=4099, vgpr_gran=1),
+    dict(vgpr_simd=65536, vgpr_gran=65536), dict(lds_cu=0), dict(lds_cu=(1 << 21) - 1, lds_gran=1),
+    dict(lds_cu=1 << 21, lds_gran=1), dict(lds_cu=(1 << 24) - 1, lds_gran=4), dict(lds_cu=1 << 24, lds_gran=1 << 20),
+    dict(n_cu=65535, n_simd=16, waves_simd=64, vgpr_simd=65536), dict(n_cu=1, n_simd=1, waves_simd=1)])
+def test_occupancy_and_rounds_at_the_edges(wmb, orc, part):
+    """The quotients of the occupancy and of the workgroup rounds, exact over
+    structural parameters at the edges of their ranges, with VGPRs, LDS and
+    workgroups on both sides of every multiple and limit, up to 2^31 - 1."""
+    p = synth.param_set(0).copy(**part)
+    n = 60_000
+    rng = np.random.Generator(np.random.PCG64(91))
+    d = synth.descriptors(n, 92)
+
+    def around(limit, lo):   # quotients limit / k and their neighbours, and the whole range
+        k = rng.integers(1, 1100, n)
+        x = np.maximum(limit, 1) // k + rng.integers(-2, 3, n)
+        x[::5] = np.exp(rng.uniform(0, np.log(2.0 ** 31 - 1), x[::5].size)).astype(np.int64)
+        return np.clip(x, lo, 2 ** 31 - 1).astype(np.int32)
+
+    d.vgpr, d.lds = around(p.vgpr_simd, 1), around(p.lds_cu, 0)
+    g = rng.integers(1, 1025, n)
+    d.gpack = ((d.gpack.astype(np.int64) & ~2047) | g).astype(np.int32)
+    _, occ = orc.predict(p, d)
+    per = p.n_cu * np.maximum(occ, 1).astype(np.int64)
+    G = per * rng.integers(1, 5000, n) + rng.integers(-1, 2, n)
+    G[::7] = (1 << 21) - per[::7] + rng.integers(-1, 2, G[::7].size)   # where the exact division takes over
+    G[::11] = np.exp(rng.uniform(0, np.log(2.0 ** 31 - 1), G[::11].size)).astype(np.int64)
+    d.grid = np.clip(G, 1, 2 ** 31 - 1).astype(np.int32)
+    _, occ, _ = _parity(wmb, orc, p, d, str(part))
+    say(part, "feasible", int((occ > 0).sum()), "distinct", np.unique(occ).size)
