@@ -34,8 +34,9 @@ namespace wm {
 constexpr int kBwTheta = 24;
 
 struct BwStruct {
-    int32_t n_sm, max_cta;
-    int64_t tmem_bytes;
+    float n_sm, max_cta;   // whole numbers
+    int32_t tmem_bytes;    // below 2^30
+    float tmem_half;       // TMEM bytes + 1/2 (exact below 2^23; used below 2^21)
     double f_clk;
 };
 
@@ -99,10 +100,10 @@ template <typename R>
 struct BwEval {
     R T;
     int32_t cta;           // -1 invalid, 0 does not fit in TMEM, else CTAs per SM
-    int32_t dt, pair, comp, nbar, nr;
+    int32_t dt, pair, comp;
     bool compute_bound;
     bool near_kink;        // |T_compute - T_io| within 1e-5 relative
-    R Kt, MA, MB, Dread, Dacc, Tmma, inv_rtc, ta_tb, Tde, Dab, io_raw, ob_bytes;
+    R nr, nbar, Kt, MA, MB, Dread, Dacc, Tmma, inv_rtc, ta_tb, Tde, Dab, io_raw, ob_bytes;
 };
 
 __device__ inline bool bw_desc_valid(const BwDesc& d)
@@ -150,44 +151,55 @@ __device__ inline void evaluate_bw(const BwStruct& st, const BwConst<R>& c, cons
     E.dt = dt;
     E.pair = pair;
     E.comp = comp;
-    E.nbar = nbar;
+    E.nbar = (R)nbar;
 
-    // residency: accumulator bytes (8 per element for FP64, else 4); TMEM is
-    // below 2^30 bytes, so once the accumulator fits every quotient is a
-    // 32-bit one (n_sm * cta <= 2^22, G < 2^31).  An extent above the TMEM
-    // size cannot fit; otherwise both are below 2^30 and the product, at
-    // most 2^63, is exact in 64 unsigned bits.
-    const bool too_wide = (uint32_t)d.bM > (uint32_t)st.tmem_bytes || (uint32_t)d.bN > (uint32_t)st.tmem_bytes;
-    const uint64_t acc = too_wide ? ~(uint64_t)0 : (uint64_t)d.bM * (uint64_t)d.bN * (dt == 0 ? 8u : 4u);
-    const uint32_t cta = acc > (uint64_t)st.tmem_bytes
-                             ? 0u
-                             : udiv_capped((uint32_t)st.tmem_bytes, (uint32_t)acc, (uint32_t)st.max_cta);
+    // residency: CTAs per SM = floor(TMEM / accumulator bytes) (8 per element for
+    // FP64, else 4), at most max_cta.  Below 2^21 bytes of TMEM an accumulator
+    // that fits is a whole number in float and the quotient exact as udiv21's
+    // (one that does not fit gives a quotient below one); the integer form took
+    // 31 vector instructions, this one nine.
+    const R fM = (R)d.bM, fN = (R)d.bN, fK = (R)d.bK;
+    float cta;
+    R Dacc;
+    if (sizeof(R) == 4 && st.tmem_bytes < (1 << 21)) {
+        const float bytes = (float)fM * (float)fN * (dt == 0 ? 8.0f : 4.0f);
+        Dacc = (R)bytes;
+        cta = least(__builtin_floorf(st.tmem_half * __builtin_amdgcn_rcpf(bytes)), st.max_cta);
+    } else {
+        // TMEM is below 2^30 bytes, so once the accumulator fits every quotient is
+        // a 32-bit one.  An extent above the TMEM size cannot fit; otherwise both
+        // are below 2^30 and the product, at most 2^63, is exact in 64 unsigned bits.
+        const uint32_t tmem = (uint32_t)st.tmem_bytes;
+        const bool too_wide = (uint32_t)d.bM > tmem || (uint32_t)d.bN > tmem;
+        const uint64_t acc = too_wide ? ~(uint64_t)0 : (uint64_t)d.bM * (uint64_t)d.bN * (dt == 0 ? 8u : 4u);
+        cta = acc > (uint64_t)tmem ? 0.0f : (float)udiv_capped(tmem, (uint32_t)acc, (uint32_t)st.max_cta);
+        Dacc = (R)(uint32_t)acc;
+    }
     E.cta = (int32_t)cta;
-    if (cta < 1) {
+    if (cta < 1.0f) {
         E.T = (R)__builtin_huge_val();
         return;
     }
-    // rounds: per_round = n_sm * cta <= 2^22; udiv21 where the numerator is
-    // below 2^21, an exact division (behind a branch the wave skips unless a
-    // lane needs it) for the larger grids
-    const uint32_t per_round = (uint32_t)st.n_sm * cta;
-    const uint32_t num = (uint32_t)d.G + per_round - 1u;
-    const bool big = num >= (1u << 21);
-    uint32_t nr = udiv21(big ? 0u : num, big ? 1u : per_round);
+    // rounds over n_sm cta <= 2^22 CTAs, as rounds() counts them
+    const float pr = st.n_sm * cta, fG = (float)d.G;
+    R nr = (R)__builtin_floorf((fG + (pr - 0.5f)) * __builtin_amdgcn_rcpf(pr));
+    const bool big = fG + pr >= 2097152.0f;
     if (__builtin_expect(__ballot(big) != 0, 0)) {
-        if (big) nr = num / per_round;
+        if (big) {
+            const uint32_t p = (uint32_t)pr;
+            nr = (R)(((uint32_t)d.G + p - 1u) / p);
+        }
     }
-    E.nr = (int32_t)nr;
+    E.nr = nr;
 
     // element bytes 8, 4, 2, 1, 1/2 for dtypes 0..4 (exact powers of two)
     const R e = (R)__builtin_ldexpf(1.0f, 3 - dt);
     const R Kt = (R)d.Kt;
     E.Kt = Kt;
-    const R MA = (R)d.bM * (R)d.bK * e;
-    const R MB = (R)d.bN * (R)d.bK * e;
+    const R MA = fM * fK * e;
+    const R MB = fN * fK * e;
     E.MA = MA;
     E.MB = MB;
-    const R Dacc = (R)(uint32_t)acc;   // it fits in TMEM: below 2^30
     E.Dacc = Dacc;
 
     // Eq. (2), Eq. (3)
@@ -195,12 +207,14 @@ __device__ inline void evaluate_bw(const BwStruct& st, const BwConst<R>& c, cons
     E.Dread = Dread;
     const R Ttmem = Dread * c.inv_tr + c.lmma + Dacc * c.inv_tw;
     const R Tmgmt = bw_div(c.ltmgmt, Kt);
-    const R fl = (R)2 * (R)d.bM * (R)d.bN * (R)d.bK;
-    R inv_rtc = vreg(c.inv_rtc[0]);   // register selects, not an indexed load
-    inv_rtc = dt == 1 ? vreg(c.inv_rtc[1]) : inv_rtc;
-    inv_rtc = dt == 2 ? vreg(c.inv_rtc[2]) : inv_rtc;
-    inv_rtc = dt == 3 ? vreg(c.inv_rtc[3]) : inv_rtc;
-    inv_rtc = dt == 4 ? vreg(c.inv_rtc[4]) : inv_rtc;
+    const R fl = (R)2 * fM * fN * fK;
+    // register selects, not an indexed load
+    const R r0 = vreg(c.inv_rtc[0]), r1 = vreg(c.inv_rtc[1]), r2 = vreg(c.inv_rtc[2]), r3 = vreg(c.inv_rtc[3]),
+            r4 = vreg(c.inv_rtc[4]);
+    R inv_rtc = dt == 1 ? r1 : r0;
+    inv_rtc = dt == 2 ? r2 : inv_rtc;
+    inv_rtc = dt == 3 ? r3 : inv_rtc;
+    inv_rtc = dt == 4 ? r4 : inv_rtc;
     E.inv_rtc = inv_rtc;
     const R Tmma = fl * inv_rtc * (pair ? c.inv_s2sm : (R)1);
     E.Tmma = Tmma;
@@ -220,20 +234,19 @@ __device__ inline void evaluate_bw(const BwStruct& st, const BwConst<R>& c, cons
     const R Tup = dt == 4 ? Dab * c.inv_rdec + c.lsetup : (R)0;
 
     // sync, Eq. (7), Eq. (8)
-    const R Tsync = (R)nbar * c.lmbar + (pair ? c.lcommit : (R)0);
+    const R Tsync = E.nbar * c.lmbar + (pair ? c.lcommit : (R)0);
     const R io_raw = Ttma + Tde + Tup + Tdsm;
     E.io_raw = io_raw;
     const R Tio = c.eps * io_raw + Tsync;
     E.compute_bound = Tcomp >= Tio;
     const R Tm = E.compute_bound ? Tcomp : Tio;
     const R Tstep = Tm + Tsync + c.omisc;
-    E.ob_bytes = (R)d.bM * (R)d.bN * (R)d.ob;
+    E.ob_bytes = fM * fN * (R)d.ob;
     const R Tstore = E.ob_bytes * c.inv_gmem + c.lstore;
-    E.T = c.tlaunch + (R)nr * (Kt * Tstep + Tstore);
+    E.T = c.tlaunch + nr * (Kt * Tstep + Tstore);
     if (FULL) {
-        const R hi = Tcomp > Tio ? Tcomp : Tio;
-        const R gap = Tcomp > Tio ? Tcomp - Tio : Tio - Tcomp;
-        E.near_kink = gap <= (R)1e-5 * hi;
+        const R gap = Tcomp - Tio;
+        E.near_kink = (gap < (R)0 ? -gap : gap) <= (R)1e-5 * Tm;
     }
 }
 

@@ -330,9 +330,10 @@ BwSet make_bw_set(const wm_bw_params_t* p)
 {
     BwSet S;
     std::memset(&S, 0, sizeof(S));
-    S.st.n_sm = p->n_sm;
-    S.st.max_cta = p->max_cta;
-    S.st.tmem_bytes = p->tmem_bytes;
+    S.st.n_sm = (float)p->n_sm;
+    S.st.max_cta = (float)p->max_cta;
+    S.st.tmem_bytes = (int32_t)p->tmem_bytes;
+    S.st.tmem_half = (float)p->tmem_bytes + 0.5f;
     S.st.f_clk = p->f_clk;
     make_bw_const<float>(p->theta, S.st, S.cf);
     make_bw_const<double>(p->theta, S.st, S.cd);

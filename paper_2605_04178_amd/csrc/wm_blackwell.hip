@@ -111,13 +111,17 @@ __device__ inline void bw_grad_exact(const BwSet& S, const BwDesc& x, float wi, 
 
 // Phase 1: wave-aligned groups of 64 descriptors, one ballot word of redo
 // flags per group (written exactly once).
-// Bound: VALU issue (about 235 per 64 descriptors at 0.8 per CU-cycle, 63 % of
-// HBM peak on 36 B each).  At 2^24 descriptors the sweep takes 121 us; 168
-// when the tensor rate of the dtype was an indexed load from the kernel
-// arguments (twice per descriptor, its latency inside the evaluation) and
-// every array's address a 64-bit vector add.
+// Bound: vector instructions (225 per 64 descriptors, reciprocals counted once)
+// and the 36 B of each descriptor, both near their rates.  At 2^24 descriptors
+// the sweep took 168 us with the dtype's tensor rate an indexed load from the
+// kernel arguments (its latency inside the evaluation) and a 64-bit vector add
+// per address, 120 without; with the next group's loads issued before a group
+// is evaluated, at seven waves per SIMD for their nine registers, 108 (at six 109,
+// at five 132; 120 where the compiler is not held to seven).  The calibration's
+// sweep keeps eight waves and no loads ahead: its sums are what a fitted theta
+// repeats.
 template <int MODE, bool PTR, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, const float* __restrict__ wv,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PTR ? 1 : 7, PTR ? 8 : 7))) void k_bw_grad(BwDescPtrs d, int64_t n, const float* __restrict__ wv,
                                                   BwSet sv, const BwSet* __restrict__ sp,
                                                   double* __restrict__ partials,
                                                   uint64_t* __restrict__ flags, uint32_t* __restrict__ ticket)
@@ -133,10 +137,23 @@ __global__ __launch_bounds__(BLOCK) void k_bw_grad(BwDescPtrs d, int64_t n, cons
     // its loads take a scalar base and one 32-bit lane offset
     const int64_t first = (int64_t)blockIdx.x * BLOCK + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
+    BwDesc next = {};
+    float w_next = 0.0f;
+    const auto load = [&](int64_t base) {
+        if (lane < n - base) {   // n - base may be negative: nothing left
+            const uint32_t off = lane_offset(lane);
+            next = load_bw_desc(d, base, off);
+            w_next = ntload_at(wv + base, off);
+        }
+    };
+    if (!PTR) load(first);
     for (int64_t base = first; base < n; base += stride) {
         bool redo = false;
-        const uint32_t off = lane_offset(lane);
-        if (lane < n - base) redo = bw_grad_fast<MODE>(S, load_bw_desc(d, base, off), ntload_at(wv + base, off), acc);
+        if (PTR) load(base);
+        const BwDesc x = next;
+        const float w = w_next;
+        if (!PTR) load(base + stride);
+        if (lane < n - base) redo = bw_grad_fast<MODE>(S, x, w, acc);
         const uint64_t m = __ballot(redo);
         if (lane == 0) flags[base >> 6] = m;
     }

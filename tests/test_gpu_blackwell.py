@@ -162,3 +162,37 @@ def test_bw_calibration_recovers_parameters(wmb, orc):
                                           lr_final=1e-3, free_mask=mask)
     assert np.allclose(hist_g, hist_o, rtol=1e-5)
     assert np.allclose(th_g, th_o, rtol=1e-4)
+
+
+@pytest.mark.parametrize("tmem,max_cta,n_sm", [(1, 1, 1), (7, 64, 148), (262144, 64, 148), ((1 << 21) - 1, 64, 65536),
+                                               (1 << 21, 64, 65536), ((1 << 30) - 1, 64, 65536), ((1 << 24) + 1, 3, 148)])
+def test_bw_residency_and_rounds_at_the_edges(wmb, orc, tmem, max_cta, n_sm):
+    """CTA residency on both sides of the TMEM size from which its quotient is
+    taken in integers, with accumulators on both sides of every quotient, and
+    grids on both sides of whole rounds and of the 2^21 where the rounds go to an
+    integer division; the loss gradient over the same rows, ragged over its
+    groups (the next group's rows are loaded ahead)."""
+    p = synth.bw_param_set(5).copy(tmem_bytes=tmem, max_cta=max_cta, n_sm=n_sm)
+    n = 70_001
+    rng = np.random.Generator(np.random.PCG64(233))
+    d = synth.bw_descriptors(n, 234)
+    esz = np.where((d.flags & 7) == 0, 8, 4)
+    d.bN = np.exp(rng.uniform(0, np.log(4096), n)).astype(np.int32)
+    want = np.maximum(1, tmem // (esz * d.bN.astype(np.int64) * rng.integers(1, 70, n)) + rng.integers(-1, 2, n))
+    d.bM = np.clip(want, 1, 2 ** 31 - 1).astype(np.int32)
+    _, cta = orc.bw_predict(p, d)
+    per = n_sm * np.maximum(cta, 1).astype(np.int64)
+    G = per * rng.integers(1, 3000, n) + rng.integers(-1, 2, n)
+    G[::7] = (1 << 21) - per[::7] + rng.integers(-1, 2, G[::7].size)
+    d.G = np.clip(G, 1, 2 ** 31 - 1).astype(np.int32)
+    dd = wmb.DeviceBwDescriptors.from_host(d)
+    T, c = wmb.bw_predict(dd, p)
+    To, co = orc.bw_predict(p, d)
+    say("bw edges", tmem, max_cta, n_sm, "CTAs", np.unique(co)[:8], "fit", int((co > 0).sum()))
+    assert np.array_equal(c.cpu().numpy(), co)
+    assert rel_err(T.cpu().numpy(), To).max() <= 1e-5
+    m = np.where(np.isfinite(To), To * synth.lognormal_noise(n, 235, 0.05), 1.0).astype(np.float32)
+    out = wmb.bw_loss_grad(dd, torch.from_numpy(m).cuda(), p).cpu().numpy()
+    loss, cnt, g = orc.bw_loss_grad(p, d, m)
+    assert int(out[1]) == cnt and abs(out[0] - loss) <= 1e-5 * abs(loss)
+    check_grad(out[2:], g, p.theta, f"bw edges {tmem}", 1e-4, names=synth.BW_THETA_NAMES)
