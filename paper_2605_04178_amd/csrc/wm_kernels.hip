@@ -215,15 +215,18 @@ __device__ inline void grad_exact(const Set& S, const Desc<float>& x, float wi, 
 // word, written exactly once (no clearing needed, order fixed).  X64: every
 // descriptor is evaluated and differentiated in float64 (the exact variant);
 // nothing is flagged, so the float64 pass only folds the partial rows.
+// Bound: the float32 sweep, memory and vector issue alike (2^24 descriptors 148
+// us, 5.9 TB/s, 267 instructions per 64); the exact one, float64 issue: at three
+// waves per SIMD (164 registers; 172 left it two) and with the parameters read
+// in place rather than spilled across the evaluation, 296 us a call where it
+// took 430 (three waves alone 371; four spill, 712).
 template <int MODE, bool PTR, int BLOCK, bool X64 = false>
-__global__ __launch_bounds__(BLOCK) void k_grad(DescPtrs d, int64_t n, const float* __restrict__ wv,
-                                               Set sv, const Set* __restrict__ sp,
-                                               double* __restrict__ partials,
-                                               uint64_t* __restrict__ flags, uint32_t* __restrict__ ticket)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(X64 ? 3 : 1))) void k_grad(
+    DescPtrs d, int64_t n, const float* __restrict__ wv, Set sv, const Set* __restrict__ sp,
+    double* __restrict__ partials, uint64_t* __restrict__ flags, uint32_t* __restrict__ ticket)
 {
     __shared__ double red[16 * kAcc];
     if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;   // counted by the float64 pass
-    const Set& S = PTR ? *sp : sv;
     struct Args { DescPtrs d; int64_t n; const float* wv; Set sv; };
     const Set* sc = PTR ? sp : WM_KERNARG_PTR(Args, sv);   // the set, read in place
     // per-lane partial sums: float32 in the bulk sweep (each lane adds the
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad(DescPtrs d, int64_t n, const flo
         if (i < n) {
             const Desc<float> x = load_desc(d, i);
             const float w = ntload(wv + i);
-            if constexpr (X64) grad_exact<MODE>(S, x, w, acc);
+            if constexpr (X64) grad_exact<MODE>(uniform_const(sc), x, w, acc);
             else redo = grad_fast<MODE>(uniform_const(sc), x, w, acc);
         }
         const uint64_t m = __ballot(redo);
