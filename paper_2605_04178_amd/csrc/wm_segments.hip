@@ -569,7 +569,9 @@ __device__ inline void add_app_row(const Set& S, const SegSet& Q, const Eval<dou
 // Latency only, so from four blocks on the applications go to a quarter of the
 // blocks and the rows to the others (one float64 chain per block rather than
 // three), flagged rows fill the lanes, and the rows' sums are read column-wise:
-// at 2^20 applications 15.4 us against 24.8 and 4.6 for the reduction's launch.
+// at 2^20 applications 12.3 us (15.4 with the parameters
+// held, and spilled, across the evaluations) against 24.8 and 4.6 for the
+// reduction's launch.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, int64_t n_seg,
                                                          int64_t n_apps, Set S, SegSet Q,
@@ -582,6 +584,8 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
 {
     __shared__ double red[4 * kAcc], part[256], sums[kAppRow], tot[kAppRow];
     __shared__ int64_t queue[4][kFlagQueue];
+    const Set* sc = WM_KERNARG_PTR(AppsArgs, S);   // read in place: held across the evaluations they spill
+    const SegSet* qc = WM_KERNARG_PTR(AppsArgs, Q);
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int nb = (int)gridDim.x, b = (int)blockIdx.x;
@@ -621,14 +625,16 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
                 double T = 0.0;
                 const int64_t j0 = lo + sub;
                 if (j0 < hi) {
+                    const Set& Sx = uniform_const(sc);
                     s0 = load_seg(sg, j0);
-                    evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j0)), E0);
-                    T = seg_time<double>(E0.T, s0, Q.d, S.cd.ov[0]);
+                    evaluate<double, true>(Sx.st, Sx.cd, widen(load_desc(d, j0)), E0);
+                    T = seg_time<double>(E0.T, s0, uniform_const(qc).d, Sx.cd.ov[0]);
                 }
                 for (int64_t j = j0 + 16; j < hi; j += 16) {
+                    const Set& Sx = uniform_const(sc);
                     Eval<double> E;
-                    evaluate<double, false>(S.st, S.cd, widen(load_desc(d, j)), E);
-                    T += seg_time<double>(E.T, load_seg(sg, j), Q.d, S.cd.ov[0]);
+                    evaluate<double, false>(Sx.st, Sx.cd, widen(load_desc(d, j)), E);
+                    T += seg_time<double>(E.T, load_seg(sg, j), uniform_const(qc).d, Sx.cd.ov[0]);
                 }
                 // the group's lanes end with the same (fixed-order) total
                 T += row_move<0x128>(T);
@@ -645,11 +651,12 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
                 }
                 if (w == 0.0) continue;
                 const double inf = __builtin_huge_val();
-                if (j0 < hi && E0.T < inf) add_app_row(S, Q, E0, s0, w, acc);
+                if (j0 < hi && E0.T < inf) add_app_row(uniform_const(sc), uniform_const(qc), E0, s0, w, acc);
                 for (int64_t j = j0 + 16; j < hi; j += 16) {
+                    const Set& Sx = uniform_const(sc);
                     Eval<double> E;
-                    evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j)), E);
-                    if (E.T < inf) add_app_row(S, Q, E, load_seg(sg, j), w, acc);
+                    evaluate<double, true>(Sx.st, Sx.cd, widen(load_desc(d, j)), E);
+                    if (E.T < inf) add_app_row(Sx, uniform_const(qc), E, load_seg(sg, j), w, acc);
                 }
             }
         }
@@ -657,10 +664,11 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
     if (b >= r0)
         for_flagged(FlagWalk(rflags, (n_seg + 63) >> 6, ((int64_t)(b - r0) * 4 + wid) * 64, (int64_t)(nb - r0) * 256),
                     queue[wid], [&](int64_t j) {
+                        const Set& Sx = uniform_const(sc);
                         Eval<double> E;
-                        evaluate<double, true>(S.st, S.cd, widen(load_desc(d, j)), E);
+                        evaluate<double, true>(Sx.st, Sx.cd, widen(load_desc(d, j)), E);
                         if (E.T < __builtin_huge_val())
-                            accumulate_partials<double>(S.st, S.cd, E, (double)wrow[j], acc);
+                            accumulate_partials<double>(Sx.st, Sx.cd, E, (double)wrow[j], acc);
                     });
     const double s = block_reduce_eight(acc + kAcc, red);
     if (threadIdx.x < 8) sums[kAcc + threadIdx.x] = s;
