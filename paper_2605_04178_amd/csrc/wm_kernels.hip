@@ -464,6 +464,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int b = blockIdx.x, nb = gridDim.x;
     const int it0 = (int)((int64_t)n_items * b / nb);
     const int it1 = (int)((int64_t)n_items * (b + 1) / nb);
+    // Every block is resident, and some take an item more than the others (4 of
+    // 3.3 on average for 1e7 descriptors): they issue first, so that they end
+    // with the others rather than on a CU left to them (100 -> 94 us).
+    if (it1 - it0 > n_items / nb) __builtin_amdgcn_s_setprio(3);
     const int lane = threadIdx.x & 63;
     for (int k = 0; k < n_sets; ++k) {  // uniform over the block
         const int o0 = item_off[k], o1 = item_off[k + 1];
