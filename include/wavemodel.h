@@ -378,8 +378,9 @@ int32_t wm_calibrate_resume(const wm_desc_t *desc, const float *measured, const 
  * each; different sizes and hierarchies, as in porting the model to several
  * architectures by parameters alone, Section IV-B) advanced together: each
  * step is one persistent sweep over all sets' descriptors in items of
- * `chunk` (each block takes a contiguous range of items), one float64 pass
- * with a block row per set, and one per-set reduce-and-Adam launch.  sets, measured, p0, opts, p_out: host
+ * `chunk` (each block takes a contiguous range of items) and one float64 pass
+ * with a block row per set, whose last block per set sums the set's rows and
+ * takes its Adam step.  sets, measured, p0, opts, p_out: host
  * arrays of n_sets entries (measured[s] device pointers); every set uses
  * opts[s] but all must have the same step count; loss_hist host
  * [n_sets][steps] or NULL.  Workspace: wm_workspace_bytes(
@@ -448,7 +449,7 @@ int32_t wm_predict_apps_vjp(const wm_desc_t *desc, const wm_segs_t *segs, const 
  * [n] float32 = mult * T, stats [4] float64 = training error sum, training
  * rows, held-out error sum, held-out rows.  Ratios and weights are float64;
  * a group of up to 64 rows is sorted by (ratio, row) across one wave's lanes
- * (two groups of up to 32 rows share a wave) and its cumulative weights are
+ * (two groups share a wave where their rows fit) and its cumulative weights are
  * a float64 prefix sum in tree order; larger groups compare every candidate
  * with every row (float32 ratio order, float64 where those tie, float64 sums
  * in row order).  Either way a multiplier can differ from the sequential

@@ -3,12 +3,12 @@
 // Adam and the multi-set calibration sweep.
 //
 // Memory layout: descriptors are structure-of-arrays; the forward kernel
-// streams them with 16-byte nontemporal loads (4 descriptors per thread per
-// array) and writes T / occ with nontemporal stores, so a sweep larger than
-// the 256 MB Infinity Cache does not evict anything useful.  The gradient
-// kernels are persistent (grid-stride) and keep 26 FP64 accumulators per
-// thread, reduced across the wave with shuffles, across the block through LDS
-// and across blocks by a second single-block kernel in a fixed order.
+// streams them with nontemporal loads (a descriptor per thread) and writes T /
+// occ with nontemporal stores, so a sweep larger than the 256 MB Infinity Cache
+// does not evict anything useful.  The gradient kernels are persistent
+// (grid-stride) and keep 26 sums per thread, added in float64 across the wave by
+// lane-row swaps and DPP moves, across the block through LDS and across blocks by
+// the last block of the float64 pass, in a fixed order.
 #include "wm_device.hpp"
 
 #include <map>

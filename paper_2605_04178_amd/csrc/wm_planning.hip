@@ -751,10 +751,11 @@ constexpr uint8_t kPlanUncertain = 0x80;
 // The chains of the block's rows are bracketed by two 64-way searches of the
 // offsets (three dependent loads for 2^16 chains; a binary search per row has
 // sixteen).
-// Bound: VALU issue (0.8 per CU-cycle; lanes wait for their wave's longest start,
+// Bound: VALU issue (0.86 per CU-cycle; lanes wait for their wave's longest start,
 // 5.1 of 8 steps used -- ordering the block's starts by run count saved the
 // steps and lost as much to the uneven waves).  At 2^16 chains / 589 K rows, R =
-// 8: 51.2 us, 68.0 with the rows loaded, converted and tested per run.
+// 8: 46.2 us; 51.4 with the model's quotients on integers and its selects as
+// branches, 68.0 with the rows loaded, converted and tested per run as well.
 struct FuseArgs {   // k_fuse_costs's parameters, in order
     DescPtrs d;
     const float* edge;
@@ -1305,7 +1306,7 @@ __device__ inline int64_t redo_count(const PlanBufs& wb, int64_t n_chains, int64
 // what the sums add per row (products, compute time, validity); longer ones go
 // through memory row by row.
 // Bound: latency (one chain of loads, sums, one or two float64 evaluations and
-// the programme per wave).  At 2^16 chains, 3 % of them queued, 23.8 us where
+// the programme per wave).  At 2^16 chains, 3 % of them queued, 23.2 us where
 // separate cost and programme launches reading rows from memory took 28.7 + 10.4.
 constexpr int kRedoRows = 64;
 

@@ -313,7 +313,8 @@ __device__ inline void store_row(const float* acc, LC lc, OV ovh, SA sacc, doubl
 // Bound by vector instructions and loads that overlap only across a CU's five
 // blocks.  A piece therefore takes two barriers: the owners mark their rows in
 // the shadow of the rows' loads, in the one of two arrays that the other rows
-// have cleared since (138 -> 135 us at 2^20 applications; a prefetch of the next
+// have cleared since (138 -> 135 us at 2^20 applications, 118 with the model's
+// quotients in float and its selects without branches; a prefetch of the next
 // piece into the L2 cost 12).
 template <int BLOCK, int MODE, bool ALONE = false>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
