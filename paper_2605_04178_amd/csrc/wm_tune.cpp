@@ -125,8 +125,16 @@ LaunchCfg default_cfg(int op)
     c.vec = 1;
     c.grid_mult = 1;
     c.chunk = 0;
+    // The application totals take up to four times the resident blocks: a chunk of
+    // applications per block up to 10^6 of them, so that no resident block has a
+    // chunk more than the others (2.3 on average there).  One, two, four times, in
+    // blocks of 256: 16.2 / 16.0 / 15.8 us at 10^5 applications, 85.3 / 77.8 / 77.5
+    // at 2^20 (64 to 512 threads at once the resident blocks: 86.0, 88.8, 85.3, 75.6
+    // there, but 512 is slower at 3 x 10^5, 27.9 against 26.2).  The totals' sums
+    // do not depend on it.
     switch (canonical_op(op)) {
     case kOpCalibrateBatched: c.chunk = 2048; break;
+    case kOpPredictApps: c.grid_mult = 4; break;
     default: break;
     }
     return c;
