@@ -254,7 +254,13 @@ __device__ inline bool finish_rows(double t, double* part /* [256] */, double* r
                                    double* tot)
 {
     static_assert(COLS <= 64, "a row is stored by one wave");
-    if (threadIdx.x < COLS) store_shared(rows2 + (int64_t)blockIdx.x * stride + threadIdx.x, t + add_parts<COLS>(part));
+    const double row = threadIdx.x < COLS ? t + add_parts<COLS>(part) : 0.0;
+    if (gridDim.x == 1) {   // a block that is alone has the totals (1 us less: 12.5 -> 11.5 at 16000 descriptors)
+        if (threadIdx.x < COLS) tot[threadIdx.x] = row;
+        __syncthreads();
+        return true;
+    }
+    if (threadIdx.x < COLS) store_shared(rows2 + (int64_t)blockIdx.x * stride + threadIdx.x, row);
     if (!last_block(ticket, gridDim.x)) return false;
     column_parts<true, 15, COLS>(rows2, (int)gridDim.x, 0, 1, stride, part);
     __syncthreads();

@@ -358,8 +358,8 @@ __device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
 // queued for a float64 re-evaluation by a second pass that counts as it appends
 // (a queue that overflows is evaluated and the window appended again); the queue
 // fills across batches.  At the end the waves of a block evaluate their queues
-// together: a wave's own is a sixth full (16 of 96 windows' worth), and a float64
-// evaluation costs the same however many lanes have one.  The result per shape is
+// together: a wave's own holds some 16 entries, and a float64 evaluation costs the
+// same however many of the 64 lanes have one.  The result per shape is
 // the smallest float64 cost (the lowest index winning exact ties) and the
 // second-smallest, for the near-tie flag.  A shape of more than kTileSpan
 // candidates, or one whose window would not fit an empty queue, goes without the
