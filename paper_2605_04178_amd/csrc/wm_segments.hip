@@ -311,11 +311,12 @@ __device__ inline void store_row(const float* acc, LC lc, OV ovh, SA sacc, doubl
 // application), the other 17 in registers: 95 VGPRs, five waves per SIMD
 // (101 and four with all of them in registers).
 // Bound by vector instructions and loads that overlap only across a CU's five
-// blocks.  A piece therefore takes two barriers: the owners mark their rows in
-// the shadow of the rows' loads, in the one of two arrays that the other rows
-// have cleared since (138 -> 135 us at 2^20 applications, 118 with the model's
-// quotients in float and its selects without branches; a prefetch of the next
-// piece into the L2 cost 12).
+// blocks.  A piece takes two barriers: the owners mark their rows in the shadow
+// of the rows' loads, in the one of two arrays that the other rows have cleared
+// since, where a third barrier and the marks after the totals held the block
+// (119 -> 112 us at 2^20 applications; 138 before the model's quotients in float
+// and its selects without branches).  A prefetch of the next piece into the L2
+// cost 12.
 template <int BLOCK, int MODE, bool ALONE = false>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
 void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, SegSet Q,
@@ -329,7 +330,7 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
     if (ALONE)
         for (int64_t w = threadIdx.x; w < (n_seg + 63) >> 6; w += BLOCK) rflags[w] = 0ull;
     __shared__ float ts[BLOCK];
-    __shared__ uint16_t own[BLOCK];
+    __shared__ uint16_t own_s[2][BLOCK];
     __shared__ int32_t lo_s[BLOCK], hi_s[BLOCK];
     __shared__ float wa_s[BLOCK];
     __shared__ double red[(BLOCK / 64) * kAppRow];
@@ -348,6 +349,8 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
 #pragma unroll
     for (int j = 0; j < 7; ++j) ovh[j] = 0.0f;
     const float inf = __builtin_huge_valf();
+    own_s[0][tid] = 0xFFFFu;
+    int turn = 0;
     const int64_t nchunks = (n_apps + BLOCK - 1) / BLOCK;
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const int64_t a = ch * BLOCK + tid;
@@ -369,6 +372,8 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
         bool near_mine = false, long_mine = false;
         int t0 = 0;   // first application of the next piece (uniform over the block)
         while (t0 < na) {
+            uint16_t* own = own_s[turn];
+            turn ^= 1;
             const int32_t p0 = __builtin_amdgcn_readfirstlane(lo_s[t0]);
             // an application longer than a piece becomes an empty piece here
             // (one control path, so the loop-carried sums keep one register
@@ -395,20 +400,27 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
             const int64_t j = (int64_t)p0 + tid;
             Eval<float> E;
             SegRow r;
-            float tsv = 0.0f;
+            Desc<float> x;
+            const bool owner = !too_long && tid >= t0 && tid <= t1;
+            const int32_t jb = lo > p0 ? lo : p0, je = hi < pend ? hi : pend;
             if (row) {
                 const uint32_t off = lane_offset(tid);
+                x = load_desc_at(d, p0, off);
                 r = load_seg_at(sg, p0, off);
-                const Desc<float> x = load_desc_at(d, p0, off);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the loads go out first
+            if (owner)
+                for (int32_t k = jb; k < je; ++k) own[k - p0] = (uint16_t)tid;
+            float tsv = 0.0f;
+            if (row) {
                 const Set& Sx = uniform_const(sc);
                 evaluate<float, true>(Sx.st, Sx.cf, x, E);
                 tsv = seg_time<float>(E.T, r, uniform_const(qc).f, Sx.cf.ov[0]);
             }
             ts[tid] = tsv;
-            own[tid] = 0xFFFFu;
             __syncthreads();
-            if (!too_long && tid >= t0 && tid <= t1) {
-                const int32_t jb = lo > p0 ? lo : p0, je = hi < pend ? hi : pend;
+            own_s[turn][tid] = 0xFFFFu;   // the next piece's
+            if (owner) {
                 double T = 0.0;
                 int32_t k = jb;
                 for (; je - k > 3; k += 4) {   // four reads in flight, added in row order
@@ -419,7 +431,6 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
                     T += (double)x3;
                 }
                 for (; k < je; ++k) T += (double)ts[k - p0];
-                for (k = jb; k < je; ++k) own[k - p0] = (uint16_t)tid;
                 bool nr;
                 wa_s[tid] = app_weight<MODE>(T, mv, lc, nr);
                 near_mine = near_mine || nr;
@@ -432,7 +443,6 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
                     app_row_terms(Sx.st, Sx.cf, uniform_const(qc).f, E, r, wa, j, acc, ovh, sacc, rflags, wrow);
                 }
             }
-            __syncthreads();   // ts, own and wa_s are rewritten by the next piece
             t0 = t1 + 1;
         }
         const uint64_t lw = __ballot(long_mine);
@@ -441,7 +451,6 @@ void k_apps_grad(DescPtrs d, SegPtrs sg, int64_t n_seg, int64_t n_apps, Set S, S
             const uint64_t fw = __ballot(near_mine);
             if ((tid & 63) == 0 && a < n_apps) aflags[a >> 6] = fw;
         }
-        __syncthreads();   // lo_s / hi_s are rewritten by the next chunk
     }
     store_row(acc, lc, ovh, sacc, red, rows + (int64_t)blockIdx.x * kAppRow);
 }
