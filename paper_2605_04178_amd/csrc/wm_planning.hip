@@ -18,6 +18,7 @@
 // margin, or a run float32 cannot represent) are redone in float64, one wave
 // per chain, so plans match a float64 evaluation except at its own ties.
 #include "wm_device.hpp"
+#include "wm_plan_rows.hpp"
 
 namespace wm {
 
@@ -1106,12 +1107,6 @@ __device__ inline void group_best(PlanBest& b)
     if constexpr (G >= 2) best_step<0xB1, MARGIN>(b);
 }
 
-// Rows per batch: their costs are loaded together (one wait per batch), their
-// cut lengths stay in registers, a byte each, equal on every lane of the
-// group, until the next batch begins (cut bytes of all but the last batch go
-// through memory).
-constexpr int kPlanBatch = 16;
-
 struct PlanState {
     double prev[2], single, best;   // single: the all-singles sum (first lane)
     uint64_t cut[2];                // the batch's cut lengths, rows 0-7 and 8-15
@@ -1133,19 +1128,18 @@ __device__ inline void plan_run(const PlanGroup<G>& g, bool& run, int32_t R, con
     ps.cut[0] = ps.cut[1] = 0ull;
     covered = true;
     unc = false;
-    // the batch's first row and its cost entries of this lane; j0 cannot pass
-    // 2^31: it stops at the longest chain's end, less than a batch beyond
-    const double* at = wb.cost + g.a * R + q0;
-    for (int32_t j0 = 0; __ballot(run && j0 < g.L) != 0ull; j0 += kPlanBatch) {
-        const int32_t left = run ? g.L - j0 : 0;   // rows of the chain from j0 on
-        if (j0 > 0 && run && j0 < g.L) {   // the last batch's cut lengths make room
+    const double* at = wb.cost + g.a * R + q0;   // this lane's cost entries of the next row
+    for (PlanRows rows(g.L); __ballot(run && rows.more()) != 0ull; rows.next()) {
+        const int32_t left = run ? rows.left() : 0;
+        if (rows.at > 0u && left > 0) {   // the last batch's cut lengths make room
             for (int r = g.gl; r < kPlanBatch; r += G)
-                wb.cut[g.a + (j0 - kPlanBatch + r)] = (uint8_t)((r < 8 ? ps.cut[0] : ps.cut[1]) >> (8 * (r & 7)));
+                wb.cut[g.a + (int64_t)(rows.at - kPlanBatch) + r] =
+                    (uint8_t)((r < 8 ? ps.cut[0] : ps.cut[1]) >> (8 * (r & 7)));
             ps.cut[0] = ps.cut[1] = 0ull;
         }
         double t[kPlanBatch][2];
         // runs longer than the rows so far or than R do not exist
-        const int32_t before = j0 < kPlanMaxRun ? j0 : kPlanMaxRun;
+        const int32_t before = rows.at < (uint32_t)kPlanMaxRun ? (int32_t)rows.at : kPlanMaxRun;
 #pragma unroll
         for (int k = 0; k < kPlanBatch; ++k) {
             d2 x = {inf, inf};
@@ -1160,15 +1154,15 @@ __device__ inline void plan_run(const PlanGroup<G>& g, bool& run, int32_t R, con
             t[k][0] = q0 <= k + before ? x[0] : inf;
             t[k][1] = q0 + 1 <= k + before && q0 + 1 < R ? x[1] : inf;
         }
-        if (COV && j0 == 0) {
+        if (COV && rows.at == 0u) {
             // coverage and uncertain runs, G rows at a time (loads in flight
             // with the costs above)
             const uint64_t gm = group_mask(g);
             bool bad = false, u = false;
-            for (int32_t i = g.gl; i < g.L && i >= 0; i += G) {
+            for (uint32_t i = (uint32_t)g.gl; i < rows.L; i += G) {
                 const uint8_t cv = wb.cov[g.a + i];
-                const int32_t want = g.L - i < R ? g.L - i : R;
-                bad = bad || (int32_t)(cv & kPlanCount) != want;
+                const uint32_t want = rows.L - i < (uint32_t)R ? rows.L - i : (uint32_t)R;
+                bad = bad || (uint32_t)(cv & kPlanCount) != want;
                 u = u || (cv & kPlanUncertain) != 0;
             }
             covered = (__ballot(bad) & gm) == 0ull;
@@ -1209,12 +1203,12 @@ __device__ inline void plan_starts(const PlanGroup<G>& g, bool live, const PlanS
     if (__ballot(L > kPlanBatch) != 0ull) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     uint64_t c0 = ps.cut[0], c1 = ps.cut[1];
     int32_t jj = L;   // the next run start found (row in the chain)
-    for (int32_t w0 = L > 0 ? (L - 1) & ~(kPlanBatch - 1) : -1; __ballot(w0 >= 0) != 0ull; w0 -= kPlanBatch) {
+    for (int32_t w0 = last_batch(L); __ballot(w0 >= 0) != 0ull; w0 -= kPlanBatch) {
         if (w0 < 0) {
             w0 = 0;   // (stays negative after the step)
             continue;
         }
-        if (w0 + kPlanBatch < L) {
+        if (batch_stored(w0, L)) {
             __builtin_memcpy(&c0, cut + g.a + w0, 8);
             __builtin_memcpy(&c1, cut + g.a + w0 + 8, 8);
         }
@@ -1226,7 +1220,7 @@ __device__ inline void plan_starts(const PlanGroup<G>& g, bool live, const PlanS
             if (jj >= w0) flags |= 1u << (jj - w0);
         }
         for (int r = g.gl; r < kPlanBatch; r += G)
-            if (w0 + r < L) start[g.a + w0 + r] = (uint8_t)((flags >> r) & 1u);
+            if (r < L - w0) start[g.a + w0 + r] = (uint8_t)((flags >> r) & 1u);
     }
 }
 
