@@ -15,8 +15,8 @@
 // run's combined descriptor in float32; a group of lanes per chain runs the
 // prefix dynamic programme over those costs in float64.  Chains where float32
 // could decide differently from float64 (a decision within a small relative
-// margin, or a run float32 cannot represent) are redone in float64, one wave
-// per chain, so plans match a float64 evaluation except at its own ties.
+// margin, or a run float32 cannot represent) are redone in float64, so plans
+// match a float64 evaluation except at its own ties.
 #include "wm_device.hpp"
 #include "wm_plan_rows.hpp"
 
@@ -1291,17 +1291,25 @@ __device__ inline int64_t redo_count(const PlanBufs& wb, int64_t n_chains, int64
     return nq < n ? nq : n;
 }
 
-// Float64 redo: a wave per queued chain.  Its candidate runs, (length, end) in
-// order of length so that neighbouring lanes fuse the same number of rows, are
-// laid over the lanes; each is formed in the order and arithmetic of fuse_rows
-// and evaluated with the float64 model, and the costs replace the chain's
-// float32 ones; then the wave's first G lanes run the programme over them.
-// A chain of up to kRedoRows rows is loaded once, a row per lane, into LDS with
-// what the sums add per row (products, compute time, validity); longer ones go
-// through memory row by row.
-// Bound: latency (one chain of loads, sums, one or two float64 evaluations and
-// the programme per wave).  At 2^16 chains, 3 % of them queued, 23.2 us where
-// separate cost and programme launches reading rows from memory took 28.7 + 10.4.
+// Float64 redo.  Wave w takes entries w, w + waves, ... of the queue, as many at
+// once as it runs programmes side by side (64 / G), so that a chain has a wave to
+// itself until the queue is longer than the waves.  Chains of up to kRedoRows rows
+// together are loaded once, a row per lane, into LDS with what the sums add per
+// row (products, compute time, validity), and their candidate runs, chain by
+// chain and (length, end) in order of length, are laid end to end over the lanes;
+// a longer chain goes alone, through memory row by row.  Each run is formed in
+// the order and arithmetic of fuse_rows and evaluated with the float64 model, and
+// the costs replace the chains' float32 ones; after all of the wave's costs,
+// groups of G lanes run its chains' programmes over them (in one loop with the
+// costs, the model's constants stay in registers across the programme: 25 to 77
+// spilled, 10 us of the call).
+// Bound: latency with a short queue (one chain of loads, sums, one or two float64
+// evaluations and the programme per wave), float64 issue with a long one, as
+// chains of repeated kernels make it.  The call over 2^16 chains of 2-16 rows, R =
+// 8, 4 % of them queued: 96 us, as with a wave per chain at any length of the
+// queue; half of them repeated kernels (29 % queued) 182 -> 141, all queued 395
+// -> 231; all queued with 2 rows, R = 2, 187 -> 38.5, and 2-5 rows, R = 8, 240 ->
+// 88 (57 and 143 with separate cost and programme launches).
 constexpr int kRedoRows = 64;
 
 struct RedoArgs {   // k_redo's parameters, in order
@@ -1318,6 +1326,10 @@ struct RedoLds {
     double F[kRedoRows], B[kRedoRows], r1[kRedoRows], r2[kRedoRows], r3[kRedoRows], K[kRedoRows], W[kRedoRows],
         tc[kRedoRows], E[kRedoRows];   // E < 0: the edge behind the row is invalid
     int32_t v[kRedoRows], s[kRedoRows], gp[kRedoRows], G[kRedoRows];   // gp < 0: the row is invalid
+    // the chains at hand: first row, rows, and how many rows and runs they and
+    // those before them have (a chain of more than kRedoRows rows counts one row
+    // more than that and no runs)
+    int32_t first[64], len[64], rows_to[64], runs_to[64];
 };
 
 __device__ inline void redo_stage(RedoLds& L, const DescPtrs& d, const float* __restrict__ edge, const double* peak,
@@ -1369,11 +1381,36 @@ __device__ inline bool fuse_staged(const RedoLds& L, const double* peak, int p, 
     return ok;
 }
 
+// sum of v over the lanes up to this one (every lane active)
+__device__ inline int32_t lanes_sum(int32_t v)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t o = __shfl_up(v, d, 64);
+        v += lane >= d ? o : 0;
+    }
+    return v;
+}
+
+// the first k in [k0, k1) with to[k] above x, to[] not decreasing and to[k1 - 1] > x
+__device__ inline int first_above(const int32_t* to, int32_t x, int k0, int k1)
+{
+    int hi = k1 - 1;
+    while (k0 < hi) {
+        const int mid = (k0 + hi) >> 1;
+        if (to[mid] > x) hi = mid;
+        else k0 = mid + 1;
+    }
+    return k0;
+}
+
 template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_redo(DescPtrs d, const float* __restrict__ edge,
                                                const int32_t* __restrict__ off, int64_t n_chains, int64_t n,
-                                               int32_t R, Set S, Peaks pk, PlanBufs wb, double* __restrict__ total,
-                                               double* __restrict__ unfused, uint8_t* __restrict__ start)
+                                               int32_t R, Set S, Peaks pk, PlanBufs wb,
+                                               double* __restrict__ total, double* __restrict__ unfused,
+                                               uint8_t* __restrict__ start)
 {
     __shared__ RedoLds lds[4];
     const int lane = threadIdx.x & 63;
@@ -1382,56 +1419,101 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     RedoLds& L = lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
     const double inf = __builtin_huge_val();
     const int64_t nq = redo_count(wb, n_chains, n);
-    for (int64_t e = wave; e < nq; e += nwaves) {
-        const int64_t c = wb.redo[e];
-        PlanGroup<64> whole;   // the chain's rows, clamped
-        whole = plan_group<64>(c, n_chains, off, n);
-        const int64_t a = whole.a;
-        const int32_t len_c = whole.L;
+    constexpr int kSide = 64 / G;   // programmes side by side
+    // the wave's chains are entries wave, wave + nwaves, ... of the queue; lane k
+    // (or group k) takes the k-th of the next kSide
+    const auto entry = [&](int64_t e, int k) -> int64_t {
+        const int64_t i = e + k * nwaves;
+        return k < kSide && i < nq ? wb.redo[i] : -1;
+    };
+    for (int64_t e = wave; e < nq; e += kSide * nwaves) {
+        int m;   // chains at hand
+        {
+            const int64_t id = entry(e, lane);
+            m = __popcll(__ballot(id >= 0));
+            const PlanGroup<64> c = plan_group<64>(id, n_chains, off, n);
+            const int32_t r = c.L < R ? c.L : R;
+            const int32_t rows = c.L <= kRedoRows ? c.L : kRedoRows + 1;
+            const int32_t runs = c.L <= kRedoRows ? r * c.L - r * (r - 1) / 2 : 0;   // sum over len <= r of L - len + 1
+            L.first[lane] = (int32_t)c.a;
+            L.len[lane] = c.L;
+            L.rows_to[lane] = m > 1 ? lanes_sum(rows) : rows;
+            L.runs_to[lane] = m > 1 ? lanes_sum(runs) : runs;
+        }
+        wave_lds_sync();
         const double* peak = uniform_const(WM_KERNARG_PTR(RedoArgs, pk)).p;
-        const bool staged = len_c <= kRedoRows;
-        if (staged) {
-            if (lane < len_c) redo_stage(L, d, edge, peak, a + lane, lane + 1 < len_c, lane);
-            wave_lds_sync();
+        for (int k0 = 0, row0 = 0, run0 = 0; k0 < m;) {   // row0, run0: of the chains before k0
+            // chains k0 .. k1 - 1: as many as fit, or one that does not
+            const int fit = __popcll(__ballot(lane >= k0 && lane < m && L.rows_to[lane] - row0 <= kRedoRows));
+            const bool staged = fit > 0;
+            const int k1 = k0 + (staged ? fit : 1);
+            int64_t runs = __builtin_amdgcn_readfirstlane(L.runs_to[k1 - 1]) - run0;
+            if (staged) {
+                if (row0 + lane < L.rows_to[k1 - 1]) {
+                    const int k = first_above(L.rows_to, row0 + lane, k0, k1);
+                    const int32_t j = row0 + lane - (k > 0 ? L.rows_to[k - 1] : 0);
+                    redo_stage(L, d, edge, peak, (int64_t)L.first[k] + j, j + 1 < L.len[k], lane);
+                }
+                wave_lds_sync();
+            } else {   // longer than R
+                runs = (int64_t)R * __builtin_amdgcn_readfirstlane(L.len[k0]) - R * (R - 1) / 2;
+            }
+            for (int64_t q = lane; q < runs; q += 64) {
+                const int k = staged ? first_above(L.runs_to, run0 + (int32_t)q, k0, k1) : k0;
+                const int64_t a = L.first[k];
+                const int32_t len_c = L.len[k];
+                // its place x among the chain's runs -> (len, j): lengths in
+                // increasing order, ends j = len - 1 .. len_c - 1
+                int64_t x = q;
+                if (k > k0) x -= L.runs_to[k - 1] - run0;
+                int32_t len = 1;
+                while (len < R && x >= len_c - len + 1) {
+                    x -= len_c - len + 1;
+                    ++len;
+                }
+                const int64_t s = a + x;   // the run's first row
+                double* out = wb.cost + (s + len - 1) * R + (len - 1);
+                asm("" : "+v"(out));   // formed before the evaluation, which leaves no register for its parts
+                Desc<double> y;
+                bool ok;
+                if (len == 1) {
+                    y = widen(load_row(d, s));
+                    ok = true;
+                } else if (staged) {
+                    ok = fuse_staged(L, peak, (k > 0 ? L.rows_to[k - 1] : 0) - row0 + (int)x, len, y);
+                } else {
+                    ok = fuse_rows(d, edge, peak, s, len, y);
+                }
+                double t = inf;
+                if (ok) {
+                    const Set& P = uniform_const(WM_KERNARG_PTR(RedoArgs, S));
+                    Eval<double> E;
+                    evaluate<double, false>(P.st, P.cd, y, E);
+                    t = E.T == E.T ? E.T : inf;
+                }
+                *out = t;
+            }
+            row0 = __builtin_amdgcn_readfirstlane(L.rows_to[k1 - 1]);
+            run0 = __builtin_amdgcn_readfirstlane(L.runs_to[k1 - 1]);
+            wave_lds_sync();   // the rows are rewritten next
+            k0 = k1;
         }
-        const int32_t r = len_c < R ? len_c : R;
-        const int64_t cnt = (int64_t)r * len_c - r * (r - 1) / 2;   // sum over len <= r of len_c - len + 1
-        for (int64_t q = lane; q < cnt; q += 64) {
-            // q -> (len, j): lengths in increasing order, ends j = len - 1 .. len_c - 1
-            int64_t x = q;
-            int32_t len = 1;
-            while (len < R && x >= len_c - len + 1) {
-                x -= len_c - len + 1;
-                ++len;
-            }
-            const int64_t j = len - 1 + x;
-            const int64_t first = j - len + 1;
-            Desc<double> y;
-            bool ok;
-            if (len == 1) {
-                y = widen(load_row(d, a + j));
-                ok = true;
-            } else if (staged) {
-                ok = fuse_staged(L, peak, (int)first, len, y);
-            } else {
-                ok = fuse_rows(d, edge, peak, a + first, len, y);
-            }
-            double t = inf;
-            if (ok) {
-                const Set& P = uniform_const(WM_KERNARG_PTR(RedoArgs, S));
-                Eval<double> E;
-                evaluate<double, false>(P.st, P.cd, y, E);
-                t = E.T == E.T ? E.T : inf;
-            }
-            wb.cost[(a + j) * R + (len - 1)] = t;
-        }
-        // the wave's costs, read back by its first lanes
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        wave_lds_sync();   // the chains at hand are rewritten next
+    }
+    // the wave's costs, read back by other lanes of it
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    for (int64_t e = wave; e < nq; e += kSide * nwaves) {
+        const int k = lane / G;
+        const int64_t c = entry(e, k);
         PlanGroup<G> g;
-        g.gl = lane & (G - 1);
-        g.c = lane < G ? whole.c : -1;
-        g.a = a;
-        g.L = lane < G ? len_c : 0;
+        if (wave + kSide * nwaves < nq) {
+            g = plan_group<G>(c, n_chains, off, n);
+        } else {   // still in LDS
+            g.gl = lane & (G - 1);
+            g.c = c;
+            g.a = L.first[k];
+            g.L = L.len[k];   // 0 past the chains at hand
+        }
         PlanState ps;
         bool run = g.c >= 0, unused = false, covered, unc;
         plan_run<G, false, false>(g, run, R, wb, ps, unused, covered, unc);
@@ -1440,7 +1522,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             unfused[g.c] = ps.single;
         }
         plan_starts(g, g.c >= 0, ps, wb.cut, start);
-        wave_lds_sync();   // the rows are rewritten for the next chain
     }
 }
 

@@ -328,6 +328,35 @@ def test_fusion_batches_and_long_redos(wmb, orc, R):
             assert abs(tot[c] - otot[c]) <= 1e-12 * otot[c] and abs(unf[c] - ounf[c]) <= 1e-12 * ounf[c], c
 
 
+@pytest.mark.parametrize("R", [1, 2, 4, 8, 32])
+def test_fusion_long_queue_of_short_chains(wmb, orc, R):
+    # every chain with an edge holds a pair whose fused working set is at the LLC
+    # capacity (as above), so the float64 redo has more chains than waves, and for
+    # R > 16 more than its waves run programmes at once; chains of 62 to 70 rows
+    # among them, which fill a wave's 64 rows in LDS or go through memory
+    p = synth.param_set(0)
+    rng = np.random.default_rng(178)
+    n = 15000
+    lens = rng.integers(1, 5, n)
+    lens[rng.integers(0, n, 60)] = rng.integers(62, 71, 60)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = int(off[-1])
+    d = synth.descriptors(rows, 178)
+    d.vgpr = rng.integers(16, 129, rows, dtype=np.int32)
+    nxt = np.concatenate([d.B[1:], np.zeros(1, np.float32)])
+    e = (rng.uniform(0.05, 0.45, rows) * np.minimum(d.B, nxt)).astype(np.float32)
+    planted = np.flatnonzero(lens >= 2)
+    k = off[planted] + lens[planted] // 2 - 1
+    d.W[k], d.W[k + 1], e[k] = np.float32(2 ** 27), np.float32(2 ** 27 + 16), 0.0
+    tot, unf, _ = _check_plan(wmb, orc, p, off, d, e, R, f"long queue, R={R}")
+    if R >= 2:
+        otot, ounf, _ = orc.plan_fusion(p, d, e, off, R)
+        for got, ref in ((tot[planted], otot[planted]), (unf[planted], ounf[planted])):
+            fin = np.isfinite(ref)
+            assert np.array_equal(np.isfinite(got), fin)
+            assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-12 * ref[fin])
+
+
 def test_fusion_offsets_not_non_decreasing(wmb, orc):
     # chain 2 starts inside chain 0: its rows were costed as chain 0's, so it
     # reports NaN; chain 0 is planned as usual and chain 1 is empty
