@@ -348,10 +348,10 @@ GradLayout grad_layout(int64_t n)
     return L;
 }
 
-// Blocks of 256 threads that are resident at once on the current device for
-// a kernel (occupancy x compute units), cached per device and kernel.  A
+// Blocks of a kernel that are resident at once on the current device (occupancy,
+// at most max_waves waves per SIMD, x compute units), cached per device and kernel.  A
 // persistent grid of exactly this size has no second, half-empty round.
-int resident_blocks(const void* kernel, int block)
+int resident_blocks(const void* kernel, int block, int max_waves)
 {
     static std::mutex mu;
     static std::map<std::pair<int, const void*>, int> cache;
@@ -365,6 +365,9 @@ int resident_blocks(const void* kernel, int block)
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, 0) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 1;
+    // whole blocks within max_waves waves on each of a CU's four SIMDs
+    const int most = 4 * max_waves / ((block + 63) / 64);
+    per_cu = per_cu < most ? per_cu : most;
     int r = per_cu * cus;
     r = r < 1 ? 1 : r;
     cache[key] = r;
@@ -376,7 +379,13 @@ static int grad_grid_t(int64_t n, int grid_mult)
 {
     const GradLayout L = grad_layout(n);
     const int64_t want = (n + BLOCK - 1) / BLOCK;
-    int64_t r = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_grad<MODE, PTR, BLOCK>), BLOCK) *
+    // The adjoint sweep (mode 0) takes the seven waves per SIMD that mode 1's
+    // registers leave, not the eight that its own 64 do: a call 47.5 us where it
+    // took 56.3 at 2^22 descriptors, 152.5 where it took 185.8 at 2^24 (blocks of
+    // 128 and 512: 159 / 196 and 145 / 173; of 64, whose eight waves were timed
+    // only, 192).
+    constexpr int kWaves = MODE == 0 && BLOCK > 64 ? 7 : 8;
+    int64_t r = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_grad<MODE, PTR, BLOCK>), BLOCK, kWaves) *
                 (grid_mult < 1 ? 1 : grid_mult);
     r = r < want ? r : want;
     r = r < L.nb ? r : L.nb;

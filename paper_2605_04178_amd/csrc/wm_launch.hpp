@@ -142,8 +142,9 @@ inline RedoLayout redo_layout(const GradLayout& L, int nb, double* partials)
 // resident at once on the current device times cfg.grid_mult, so partial
 // rows = that + nb2
 int grad_grid(int mode, bool from_device_set, int64_t n, const LaunchCfg& cfg);
-// blocks of `block` threads of `kernel` resident at once on the current device
-int resident_blocks(const void* kernel, int block);
+// blocks of `block` threads of `kernel` resident at once on the current device,
+// with at most max_waves waves per SIMD (one value per kernel)
+int resident_blocks(const void* kernel, int block, int max_waves = 8);
 // blocks for the multi-set sweep over n_items work items
 int batched_grid(int n_items, int grid_mult);
 // blocks per set of the multi-set float64 pass (at most cap): all sets'

@@ -212,3 +212,23 @@ def test_float64_pass_flags_and_row_slots(wmb, orc, n, block):
     assert int(out[1]) == cnt
     assert abs(out[0] - loss) <= 1e-13
     assert np.all(np.abs(out[2:] - g) * np.abs(p.theta) <= 1e-11 * absum + 1e-300)
+
+
+def test_vjp_sweep_keeps_seven_waves_per_simd(wmb):
+    """The adjoint sweep's partial rows in the workspace (26 doubles per block,
+    then the float64 pass's and its count of finished blocks): seven blocks of 256
+    per CU at 2^20 descriptors, whatever registers the kernel has."""
+    n = 1 << 20
+    p = synth.param_set(0)
+    d = synth.descriptors(n, 106)
+    w = np.random.default_rng(106).random(n).astype(np.float32)
+    ws = torch.full((wmb.workspace_bytes(wmb.OP_VJP, n),), 0xAB, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    wmb.vjp(wmb.DeviceDescriptors.from_host(d), p, torch.from_numpy(w).cuda(), ws=ws)
+    first = ws[:26 * 8 * 4096].view(torch.int64).view(-1, 26)[:, 0].cpu().numpy()
+    untouched = np.frombuffer(b"\xab" * 8, np.int64)[0]
+    rows = int(np.argmax(first == untouched))
+    words = n // 64
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    say("rows written", rows)
+    assert rows == 7 * cus + words // 256 + 1
