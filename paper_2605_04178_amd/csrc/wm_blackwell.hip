@@ -118,8 +118,7 @@ __device__ inline void bw_grad_exact(const BwSet& S, const BwDesc& x, float wi, 
 // per address, 120 without; with the next group's loads issued before a group
 // is evaluated, at seven waves per SIMD for their nine registers, 108 (at six 109,
 // at five 132; 120 where the compiler is not held to seven).  The calibration's
-// sweep keeps eight waves and no loads ahead: its sums are what a fitted theta
-// repeats.
+// sweep loads nothing ahead and takes seven waves of its eight (bw_grid_t).
 template <int MODE, bool PTR, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PTR ? 1 : 7, PTR ? 8 : 7))) void k_bw_grad(BwDescPtrs d, int64_t n, const float* __restrict__ wv,
                                                   BwSet sv, const BwSet* __restrict__ sp,
@@ -233,7 +232,11 @@ static int bw_grid_t(int64_t n, int grid_mult)
 {
     const GradLayout L = grad_layout(n);
     const int64_t want = (n + 255) / 256;
-    int64_t r = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_bw_grad<MODE, PTR, 256>), 256) *
+    // The calibration's sweep has room for eight waves per SIMD and takes seven: a
+    // lane's rows, and with them the last digits that a fitted theta repeats, are
+    // those of the seven that its registers once left.  100 steps at 2^20 / 2^22
+    // / 2^23 descriptors 2.76 / 4.94 / 7.15 ms, with eight 2.82 / 5.26 / 7.46.
+    int64_t r = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_bw_grad<MODE, PTR, 256>), 256, PTR ? 7 : 8) *
                 (grid_mult < 1 ? 1 : grid_mult);
     r = r < want ? r : want;
     r = r < L.nb ? r : L.nb;

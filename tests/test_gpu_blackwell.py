@@ -196,3 +196,23 @@ def test_bw_residency_and_rounds_at_the_edges(wmb, orc, tmem, max_cta, n_sm):
     loss, cnt, g = orc.bw_loss_grad(p, d, m)
     assert int(out[1]) == cnt and abs(out[0] - loss) <= 1e-5 * abs(loss)
     check_grad(out[2:], g, p.theta, f"bw edges {tmem}", 1e-4, names=synth.BW_THETA_NAMES)
+
+
+def test_bw_calibration_sweep_keeps_seven_waves_per_simd(wmb):
+    """The partial rows (26 doubles per block) that a calibration leaves in its
+    workspace at 2^20 descriptors, of the 8192 + 64 it has room for: seven
+    blocks of 256 per CU, then the float64 pass's 64 and its count of finished
+    blocks, whatever registers the sweep has."""
+    n = 1 << 20
+    p = synth.bw_param_set(0)
+    dd = wmb.DeviceBwDescriptors.from_host(synth.bw_descriptors(n, 236))
+    T, _ = wmb.bw_predict(dd, p)
+    m = torch.where(torch.isfinite(T), 1.02 * T, torch.ones_like(T))
+    ws = torch.full((wmb.bw_workspace_bytes(wmb.BW_OP_CALIBRATE, n, 1),), 0xAB, dtype=torch.uint8, device="cuda")
+    wmb.bw_calibrate(dd, m, p, steps=1, ws=ws)
+    w = ws[:ws.numel() // 8 * 8].view(torch.int64).cpu().numpy()
+    untouched = int((w == np.frombuffer(b"\xab" * 8, np.int64)[0]).sum())
+    rows = 7 * torch.cuda.get_device_properties(0).multi_processor_count + 64 + 1
+    say("untouched words", untouched, "of rows", untouched / 26)
+    # a ticket's row but its first word, and the ends of 256-byte fields, stay untouched too
+    assert 0 <= untouched - 26 * (8192 + 64 - rows) < 26 * 16
