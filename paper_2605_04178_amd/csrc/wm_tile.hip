@@ -308,32 +308,27 @@ __device__ inline void clamp_list(int64_t n_cand, int64_t& a, int64_t& b)
     b = b < a ? a : (b > n_cand ? n_cand : b);
 }
 
-// One shape on the whole wave, without the queue: float32 minimum over its
-// list, then the float64 window evaluated lane-parallel and reduced across
-// the wave.  For batches too long for LDS or with too large a window.
-__device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
-{
-    const Set& S = C.S;
-    const TileConst& tk = C.tk;
-    const double dinf = __builtin_huge_val();
-    const float finf = __builtin_huge_valf();
-    const int32_t M = C.sh.M[i], N = C.sh.N[i], K = C.sh.K[i], t = C.sh.dtype[i];
-    int64_t a = C.off[i], b = C.off[i + 1];
-    clamp_list(C.n_cand, a, b);
-    const TileShape z = tile_shape(S.cf, tk, M, N, K, t);
-    float c32 = finf;
-    for (int64_t j = a + lane; j < b; j += 64)
-        c32 = __builtin_fminf(c32, tile_cost(S.st, S.cf, tk, z, C.code[j]));
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) c32 = __builtin_fminf(c32, __shfl_xor(c32, m, 64));
-    Best2 r{dinf, dinf, 0x7fffffff};
-    if (c32 < finf) {
-        const float thr = c32 * (1.0f + kTileWindow);
-        for (int64_t j = a + lane; j < b; j += 64) {
-            if (!(tile_cost(S.st, S.cf, tk, z, C.code[j]) <= thr)) continue;
-            r.add(exact_cost(S, M, N, K, t, C.code[j]), (int32_t)(j - a));
-        }
+// A shape's extents and dtype in a loop over its candidates, of which a lane has
+// one or two: nothing formed of them is held across the float64 cost, where it
+// would spill (and a kernel with scratch memory starts later).
+struct ShapeDims {
+    int32_t M, N, K, t;
+    __device__ inline ShapeDims(const ShapePtrs& sh, int64_t i)   // i wave-uniform
+        : M(__builtin_amdgcn_readfirstlane(sh.M[i])), N(__builtin_amdgcn_readfirstlane(sh.N[i])),
+          K(__builtin_amdgcn_readfirstlane(sh.K[i])), t(__builtin_amdgcn_readfirstlane(sh.dtype[i]))
+    {
     }
+    __device__ inline ShapeDims late() const
+    {
+        ShapeDims x = *this;
+        asm volatile("" : "+s"(x.M), "+s"(x.N), "+s"(x.K), "+s"(x.t));
+        return x;
+    }
+};
+
+// shape i's result from the lanes' shares of its window
+__device__ inline void write_best_of_wave(const TileArgs& C, Best2 r, int64_t i, int lane)
+{
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
         const double oc1 = __shfl_xor(r.c1, m, 64);
@@ -350,6 +345,53 @@ __device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
     if (lane == 0) write_best(r, i, C.best, C.best_cost, C.near_tie);
 }
 
+// A shape of the batch whose window is too large for the queue, on the whole
+// wave: record z, window by the float32 costs in LDS.
+__device__ inline void wide_window(const TileArgs& C, const TileQueue& q, const TileShape& z, int64_t i, int lane)
+{
+    const ShapeDims s(C.sh, i);
+    int64_t a = C.off[i], b = C.off[i + 1];
+    clamp_list(C.n_cand, a, b);
+    const int32_t P = z.P, len = (int32_t)(b - a);
+    Best2 r{__builtin_huge_val(), __builtin_huge_val(), 0x7fffffff};
+    for (int32_t j = lane; j < len; j += 64) {
+        if (!(q.cost32[P + j] <= z.thr)) continue;
+        const ShapeDims x = s.late();
+        r.add(exact_cost(C.S, x.M, x.N, x.K, x.t, C.code[a + j]), j);
+    }
+    write_best_of_wave(C, r, i, lane);
+}
+
+// One shape on the whole wave, without LDS: float32 minimum over its list, then
+// the float64 window evaluated lane-parallel and reduced across the wave.  For
+// lists too long for LDS.
+__device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
+{
+    const Set& S = C.S;
+    const TileConst& tk = C.tk;
+    const double dinf = __builtin_huge_val();
+    const float finf = __builtin_huge_valf();
+    const ShapeDims s(C.sh, i);
+    int64_t a = C.off[i], b = C.off[i + 1];
+    clamp_list(C.n_cand, a, b);
+    const TileShape z = tile_shape(S.cf, tk, s.M, s.N, s.K, s.t);
+    float c32 = finf;
+    for (int64_t j = a + lane; j < b; j += 64)
+        c32 = __builtin_fminf(c32, tile_cost(S.st, S.cf, tk, z, C.code[j]));
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) c32 = __builtin_fminf(c32, __shfl_xor(c32, m, 64));
+    Best2 r{dinf, dinf, 0x7fffffff};
+    if (c32 < finf) {
+        const float thr = c32 * (1.0f + kTileWindow);
+        for (int64_t j = a + lane; j < b; j += 64) {
+            if (!(tile_cost(S.st, S.cf, tk, z, C.code[j]) <= thr)) continue;
+            const ShapeDims x = s.late();
+            r.add(exact_cost(S, x.M, x.N, x.K, x.t, C.code[j]), (int32_t)(j - a));
+        }
+    }
+    write_best_of_wave(C, r, i, lane);
+}
+
 // A wave takes `per` consecutive shapes, in batches of as many as fit the LDS
 // (at most kTileBatch shapes and kTileSpan candidates), and lays a batch's
 // candidate lists end to end over its lanes, so that short lists leave no lane
@@ -362,8 +404,11 @@ __device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
 // same however many of the 64 lanes have one.  The result per shape is
 // the smallest float64 cost (the lowest index winning exact ties) and the
 // second-smallest, for the near-tie flag.  A shape of more than kTileSpan
-// candidates, or one whose window would not fit an empty queue, goes without the
-// queue.
+// candidates goes without the queue, and where a batch's windows would not fit
+// an empty queue, so do its shapes with more than an equal share of it: their
+// windows are read from the costs in LDS, the other shapes' fit.  (2^16 shapes of
+// up to 96 candidates, all of them one tile repeated: 91 us, and 64 with only the
+// first twentieth so; with such batches cut in half until they fit, 211 and 141.)
 // A run per wave, cut where the LDS is full, takes short calls and long lists
 // where fixed batches of eight shapes left waves idle or went without the queue:
 // 1000 shapes of up to 96 candidates 16.1 -> 7.0 us, 2^14 of up to 384 87.4 -> 30.7.
@@ -383,7 +428,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
     int64_t s0 = wave * A.per;
     const int64_t end = s0 + A.per < A.n ? s0 + A.per : A.n;
     int ns = 0, qn = 0;
-    int most = kTileBatch;   // shapes a batch may take: fewer where their windows overfill the queue
     for (;;) {
         const bool done = s0 >= end;
         const TileArgs& B = late_args();
@@ -404,16 +448,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
         // list lengths, saturated
         const int32_t len = (int32_t)(b - a < kTileSpan + 1 ? b - a : kTileSpan + 1);
         const int32_t inc = sum_upto(len);
-        const int nb = __popcll(__ballot(has && inc <= kTileSpan && lane < most));   // shapes of this batch
+        const int nb = __popcll(__ballot(has && inc <= kTileSpan));   // shapes of this batch
         has = lane < nb;
         bool fin = false;
         int32_t rank = 0;   // among the batch's shapes with a finite minimum
         int32_t T = 0;
+        int r = -1;         // among the batch's shapes that have candidates
         if (nb > 0) {
             T = __builtin_amdgcn_readlane(inc, nb - 1);
             const int32_t P = inc - len;             // first batch position of lane's shape
             const bool some = has && len > 0;
-            const int r = (int)lanes_below(__ballot(some));
+            r = (int)lanes_below(__ballot(some));
+            r = some ? r : -1;
             wave_lds_sync();   // the previous batch's lanes are done reading
             if (lane < kTileSpan / 64) q.ends[lane] = 0;
             if (some) {
@@ -462,16 +508,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 q.bs[r].P = P;
             }
         }
-        const int nf = __popcll(__ballot(fin));
-        // The one flush site.  Attempt 0 flushes at the end, or when the
+        int nf = __popcll(__ballot(fin));
+        // The one flush site.  The first pass flushes at the end, or when the
         // batch's shapes would not find queue slots; then the batch's window
         // is appended after entry qn (shapes taking slots from ns in batch
         // order), entries past the queue's end counted but not written.  If
-        // the queue overflowed, attempt 1 evaluates what it held and appends
-        // the window again to the empty queue.
+        // the queue overflowed, the next pass evaluates what it held and appends
+        // the window again to the empty queue; if it overflowed from empty, the
+        // shapes with more than an equal share of it go without the queue, and
+        // the others' windows fit.
         bool flush = done || ns + nf > kTileSlots;
         int cnt = 0;
-        for (int attempt = 0; attempt < 2; ++attempt) {
+        for (;;) {
             if (flush) {
                 // Every queued candidate in float64 (codes and shapes are read
                 // back from memory, one load per lane); then one lane per shape
@@ -538,24 +586,41 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 }
                 cnt += __popcll(m);
             }
-            flush = qn + cnt > kTileQueue && qn > 0;
-            if (!flush) break;
+            if (qn + cnt <= kTileQueue) break;
+            flush = qn > 0;
+            if (flush) continue;
+            // the windows' sizes, in the minima's place
+            if (lane < kTileBatch) q.bmin[lane] = 0u;
+            wave_lds_sync();
+            before = 0;
+            for (int32_t v0 = 0; v0 < T; v0 += 64) {
+                const int32_t v = v0 + lane;
+                const int sl = lane_slot(q, v0 >> 6, before);
+                if (v < T && q.cost32[v] <= q.bs[sl].thr)
+                    __hip_atomic_fetch_add(&q.bmin[sl], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+            wave_lds_sync();
+            const bool wide = fin && (int)q.bmin[fin ? r : 0] * nf > kTileQueue;
+            for (uint64_t w = __ballot(wide); w; w &= w - 1) {
+                const int k = __builtin_ctzll(w);
+                wide_window(late_args(), q, q.bs[__builtin_amdgcn_readlane(r, k)], s0 + k, lane);
+            }
+            fin = fin && !wide;
+            rank = (int32_t)lanes_below(__ballot(fin));
+            nf = __popcll(__ballot(fin));
+            wave_lds_sync();
+            if (r >= 0) {
+                q.bs[r].rank = rank;
+                if (!fin) q.bs[r].thr = -finf;
+            }
         }
         if (done) break;
-        // shapes that go without the queue: a list too long for LDS, or a window
-        // longer than the whole queue
-        int alone = nb == 0 ? 1 : 0;
-        if (cnt > kTileQueue) {
-            alone = nb == 1 ? 1 : 0;
-            most = nb == 1 ? kTileBatch : nb >> 1;   // again with fewer shapes
-        } else {
-            qn += cnt;
-            ns += nf;
-            s0 += nb;
-        }
+        qn += cnt;
+        ns += nf;
+        const int alone = nb == 0 ? 1 : 0;   // a list too long for LDS
         const TileArgs& L = late_args();
-        for (int k = 0; k < alone; ++k) direct_shape(L, s0 + k, lane);
-        s0 += alone;
+        for (int k = 0; k < alone; ++k) direct_shape(L, s0, lane);
+        s0 += nb + alone;
     }
 }
 

@@ -236,3 +236,30 @@ def test_tile_costs_and_runs_at_the_edges(wmb, orc, part):
     say(part, "worst float32 cost error", err.max() if err.size else 0.0, "of", err.size)
     assert err.size == 0 or err.max() <= 5.3e-6
     _check(wmb, orc, p, sh, part)
+
+
+@pytest.mark.parametrize("grid_mult", [1, 8])
+@pytest.mark.parametrize("lens", [(12,), (4, 5, 60), (64, 64, 1), (127, 1, 2), (128, 129), (40, 44, 45), (300, 2, 705)])
+def test_select_tile_windows_past_the_queue(wmb, orc, lens, grid_mult):
+    """Lists of one tile repeated (every candidate within the window) among
+    ordinary ones, so that a batch's windows reach, pass or far exceed the 128
+    queue entries of a wave: shapes with more than an equal share of the queue go
+    without it, others keep their place in it.  Exact ties keep the first index."""
+    p = synth.param_set(0)
+    rng = np.random.Generator(np.random.PCG64(sum(lens)))
+    tiles = synth.all_tile_codes()
+    n = 700
+    cnt = np.array(lens)[np.arange(n) % len(lens)]
+    tied = (np.arange(n) < 200) | (rng.random(n) < 0.3)
+    lists = [np.repeat(tiles[rng.integers(0, len(tiles))], c) if t else tiles[rng.integers(0, len(tiles), c)]
+             for c, t in zip(cnt, tied)]
+    off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    M, N, K = (np.round(np.exp(rng.uniform(np.log(128), np.log(16384), n))).astype(np.int32) for _ in range(3))
+    sh = synth.Shapes(M, N, K, rng.integers(0, 4, n).astype(np.int32), off, np.concatenate(lists).astype(np.uint32))
+    default = wmb.get_launch(wmb.OP_SELECT_TILE, n)
+    wmb.set_launch(wmb.OP_SELECT_TILE, n, default["block"], 1, grid_mult)
+    try:
+        best, _, _, _, _ = _check(wmb, orc, p, sh, f"windows {lens}, grid_mult {grid_mult}")
+    finally:
+        wmb.set_launch(wmb.OP_SELECT_TILE, n, default["block"], default["per_thread"], default["grid_mult"])
+    assert np.all(best[tied & (best >= 0)] == 0)
