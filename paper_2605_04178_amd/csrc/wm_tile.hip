@@ -8,6 +8,7 @@
 // in LDS); the float64 re-evaluations of the near-minimum windows queue up in
 // LDS and run on all lanes of the block.
 #include "wm_device.hpp"
+#include "wm_shares.hpp"
 
 namespace wm {
 
@@ -629,15 +630,9 @@ static void select_t(const ShapePtrs& sh, const int32_t* off, const uint32_t* co
                      int64_t n_cand, const Set& S, int32_t* best, double* best_cost,
                      uint8_t* near_tie, int grid_mult, hipStream_t stream)
 {
-    // Equal runs of shapes for every wave that the chip holds; a run has no
-    // fewer shapes than fill a round of 64 candidates with lists of the average
-    // length (at most 8).
     const int64_t wpb = BLOCK / 64;
-    const int64_t waves = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_select_tile<BLOCK>), BLOCK) *
-                          (grid_mult < 1 ? 1 : grid_mult) * wpb;
-    const int64_t fill = n_cand > 8 * n ? 64 * n / n_cand : 8;
-    int64_t per = (n + waves - 1) / waves;
-    per = per < fill ? fill : per;
+    const int64_t waves = (int64_t)resident_blocks(reinterpret_cast<const void*>(&k_select_tile<BLOCK>), BLOCK) * wpb;
+    const int64_t per = tile_run(n, n_cand, waves, grid_mult);
     const int64_t b = ((n + per - 1) / per + wpb - 1) / wpb;
     k_select_tile<BLOCK><<<(int)b, BLOCK, 0, stream>>>(
         TileArgs{sh, off, code, n, n_cand, per, best, best_cost, near_tie, tile_const(S.st), S});
