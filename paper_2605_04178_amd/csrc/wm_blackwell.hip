@@ -183,7 +183,7 @@ struct BwFinishAdam {
 
 // Phase 2: fold the phase-1 rows (fixed order), redo flagged descriptors in
 // float64; the last block to finish sums the rows and ends the call.
-template <int MODE, bool PTR, typename FIN>
+template <int MODE, bool PTR, bool ONE, typename FIN>   // ONE: a single block, n <= kOneBlockRows
 __global__ __launch_bounds__(256) void k_bw_grad_redo(BwDescPtrs d, int64_t n,
                                                        const float* __restrict__ wv, BwSet sv,
                                                        const BwSet* sp,
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_bw_grad_redo(BwDescPtrs d, int64_t n,
     const BwSet& S = PTR ? *sp : sv;
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const typename FIN::Ahead ahead = fin.ahead();
-    const FlagWalk walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
+    const FlagWalk<ONE> walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
     column_parts<false, 4>(rows1, nrows1, (int)blockIdx.x, (int)gridDim.x, kAcc, part);
     double acc[kAcc];
 #pragma unroll
@@ -251,8 +251,12 @@ static hipError_t bw_grad_t(const BwDescPtrs& d, int64_t n, const float* w, cons
     const int nb = bw_grid_t<MODE, PTR>(n, c.grid_mult);
     const RedoLayout r = redo_layout(L, nb, partials);
     k_bw_grad<MODE, PTR, 256><<<nb, 256, 0, s>>>(d, n, w, S, S_dev, partials, flags, r.ticket);
-    k_bw_grad_redo<MODE, PTR><<<r.nb2, 256, 0, s>>>(d, n, w, S, S_dev, flags, partials, nb,
-                                                    partials + (int64_t)nb * kAcc, r.ticket, fin);
+    double* rows2 = partials + (int64_t)nb * kAcc;
+    if (r.nb2 == 1 && n <= kOneBlockRows)
+        k_bw_grad_redo<MODE, PTR, true><<<1, 256, 0, s>>>(d, n, w, S, S_dev, flags, partials, nb, rows2, r.ticket, fin);
+    else
+        k_bw_grad_redo<MODE, PTR, false><<<r.nb2, 256, 0, s>>>(d, n, w, S, S_dev, flags, partials, nb, rows2, r.ticket,
+                                                               fin);
     return hipGetLastError();
 }
 

@@ -289,9 +289,16 @@ __device__ inline uint32_t lanes_below(uint64_t m)
 
 constexpr int kFlagQueue = 128;   // row indices queued per wave
 
+constexpr int64_t kOneBlockRows = 4 * 64 * 64;   // a flag word per lane of a block
+
 // This lane's first two words of a walk over the flag words w0 .. w0 + 63, w0 +
 // stride ..., up to nwords (w0 and stride multiples of 64, wave-uniform),
-// loaded ahead of other work.
+// loaded ahead of other work.  ONE: a block that is alone, whose four waves share
+// the words of at most kOneBlockRows rows equally: with 64 to the first wave, 5000
+// rows that are all flagged were two waves' work, 100 us a call where it takes 45.
+// Larger grids leave at most one block short, and keep the division off the pass's
+// chain of latencies.
+template <bool ONE = false>
 struct FlagWalk {
     const uint64_t* flags;
     int64_t nwords, base, stride;
@@ -302,8 +309,16 @@ struct FlagWalk {
         return w < nwords ? flags[w] : 0ull;
     }
     __device__ inline FlagWalk(const uint64_t* f, int64_t nw, int64_t w0, int64_t st)
-        : flags(f), nwords(nw), base(w0), stride(st), m(word(w0)), next(word(w0 + st))
+        : flags(f), nwords(nw), base(w0), stride(st)
     {
+        if (ONE) {
+            const int64_t share = (nw + 3) >> 2;
+            base = (w0 >> 6) * share;
+            stride = nw;   // one step
+            nwords = base + share < nw ? base + share : nw;
+        }
+        m = word(base);
+        next = ONE ? 0ull : word(base + stride);
     }
 };
 
@@ -312,8 +327,8 @@ struct FlagWalk {
 // so rows are queued in LDS, lowest bit of each lane's word first, and f runs
 // with a row on every lane; called on the words' own lanes it would run once
 // for nearly every word, a lane or two at a time.
-template <typename F>
-__device__ inline void for_flagged(FlagWalk w, int64_t* queue /* [kFlagQueue], the wave's own */, F f)
+template <bool ONE, typename F>
+__device__ inline void for_flagged(FlagWalk<ONE> w, int64_t* queue /* [kFlagQueue], the wave's own */, F f)
 {
     const int lane = threadIdx.x & 63;
     int qn = 0;

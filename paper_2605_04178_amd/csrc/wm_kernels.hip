@@ -286,7 +286,7 @@ struct FinishAdam {   // one Adam step on log(theta); the set's constants rebuil
 // reduction, the count and the rows' read-back.  At 2^20 descriptors with the
 // Adam step as the end 12.0 us where the pass (8.0) and a launch of its own
 // for the end (7.7) took 15.7 and a gap; at 2^24 10.6 us against 12.9 + 5.8.
-template <int MODE, bool PTR, typename FIN>
+template <int MODE, bool PTR, bool ONE, typename FIN>   // ONE: a single block, n <= kOneBlockRows
 __global__ __launch_bounds__(256) void k_grad_redo(DescPtrs d, int64_t n,
                                                     const float* __restrict__ wv, Set sv,
                                                     const Set* sp,
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void k_grad_redo(DescPtrs d, int64_t n,
     const Set& S = PTR ? *sp : sv;
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const typename FIN::Ahead ahead = fin.ahead();
-    const FlagWalk walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
+    const FlagWalk<ONE> walk(flags, (n + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64, (int64_t)gridDim.x * 256);
     column_parts<false, 4>(rows1, nrows1, (int)blockIdx.x, (int)gridDim.x, kAcc, part);
     double acc[kAcc];
 #pragma unroll
@@ -307,6 +307,19 @@ __global__ __launch_bounds__(256) void k_grad_redo(DescPtrs d, int64_t n,
     for_flagged(walk, queue[wid], [&](int64_t i) { grad_exact<MODE>(S, load_desc(d, i), wv[i], acc); });
     const double t = block_reduce_value(acc, red);
     if (finish_rows(t, part, rows2, kAcc, ticket, tot)) fin(tot, ahead);
+}
+
+template <int MODE, bool PTR, typename FIN>
+static void launch_redo(const DescPtrs& d, int64_t n, const float* w, const Set& S, const Set* S_dev,
+                        const uint64_t* flags, double* partials, int nb, const RedoLayout& r, const FIN& fin,
+                        hipStream_t stream)
+{
+    double* rows2 = partials + (int64_t)nb * kAcc;
+    if (r.nb2 == 1 && n <= kOneBlockRows)
+        k_grad_redo<MODE, PTR, true><<<1, 256, 0, stream>>>(d, n, w, S, S_dev, flags, partials, nb, rows2, r.ticket, fin);
+    else
+        k_grad_redo<MODE, PTR, false><<<r.nb2, 256, 0, stream>>>(d, n, w, S, S_dev, flags, partials, nb, rows2,
+                                                                 r.ticket, fin);
 }
 
 // The exact variant: float64 sweep (k_grad<MODE, false, 256, true>), the
@@ -324,8 +337,7 @@ static void launch_grad_exact_t(const DescPtrs& d, int64_t n, const float* w, co
     nb = nb < 1 ? 1 : nb;
     const RedoLayout r = redo_layout(L, (int)nb, partials);
     k_grad<MODE, false, 256, true><<<(int)nb, 256, 0, stream>>>(d, n, w, S, nullptr, partials, flags, r.ticket);
-    k_grad_redo<MODE, false><<<r.nb2, 256, 0, stream>>>(d, n, w, S, nullptr, flags, partials, (int)nb,
-                                                        partials + nb * kAcc, r.ticket, FinishOut<MODE>{out});
+    launch_redo<MODE, false>(d, n, w, S, nullptr, flags, partials, (int)nb, r, FinishOut<MODE>{out}, stream);
 }
 
 hipError_t launch_grad_exact(int mode, const DescPtrs& d, int64_t n, const float* w, const Set& S,
@@ -428,8 +440,7 @@ static bool launch_grad_t(const DescPtrs& d, int64_t n, const float* w, const Se
     default: return false;
     }
 #undef WM_GRAD_CASE
-    k_grad_redo<MODE, PTR><<<r.nb2, 256, 0, stream>>>(d, n, w, S, S_dev, flags, partials, nb,
-                                                      partials + (int64_t)nb * kAcc, r.ticket, fin);
+    launch_redo<MODE, PTR>(d, n, w, S, S_dev, flags, partials, nb, r, fin, stream);
     return true;
 }
 
@@ -534,7 +545,7 @@ __global__ __launch_bounds__(256) void k_grad_redo_batched(const DescPtrs* __res
     const int s = blockIdx.y;
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const AdamLane ahead(st + s, opts[s]);
-    const FlagWalk walk(flags + flag_off[s], (set_n[s] + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64,
+    const FlagWalk<> walk(flags + flag_off[s], (set_n[s] + 63) >> 6, ((int64_t)blockIdx.x * 4 + wid) * 64,
                         (int64_t)gridDim.x * 256);
     const int64_t stride = (int64_t)n_sets * kAcc;   // between a set's rows
     column_parts<false, 4>(rows1 + (int64_t)s * kAcc, nrows1, (int)blockIdx.x, (int)gridDim.x, stride, part);

@@ -676,7 +676,7 @@ __global__ __launch_bounds__(256) void k_apps_grad_redo(DescPtrs d, SegPtrs sg, 
         }
     }
     if (b >= r0)
-        for_flagged(FlagWalk(rflags, (n_seg + 63) >> 6, ((int64_t)(b - r0) * 4 + wid) * 64, (int64_t)(nb - r0) * 256),
+        for_flagged(FlagWalk<>(rflags, (n_seg + 63) >> 6, ((int64_t)(b - r0) * 4 + wid) * 64, (int64_t)(nb - r0) * 256),
                     queue[wid], [&](int64_t j) {
                         const Set& Sx = uniform_const(sc);
                         Eval<double> E;

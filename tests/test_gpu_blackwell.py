@@ -216,3 +216,21 @@ def test_bw_calibration_sweep_keeps_seven_waves_per_simd(wmb):
     say("untouched words", untouched, "of rows", untouched / 26)
     # a ticket's row but its first word, and the ends of 256-byte fields, stay untouched too
     assert 0 <= untouched - 26 * (8192 + 64 - rows) < 26 * 16
+
+
+@pytest.mark.parametrize("n", [65, 257, 5000, 16321, 16385])
+def test_bw_float64_pass_of_one_block_shares_its_words(wmb, orc, n):
+    """Every descriptor flagged (measured = the float64 time rounded to float32),
+    up to and past the 256 flag words that a single block's waves share.  All terms
+    are float64: a slot's sum of n terms, cancelling by at most n, to 1e-15 n^2 of
+    the largest slot, below 1e-6 here."""
+    p = synth.bw_param_set(1)
+    d = synth.bw_descriptors(n, 237)
+    T, _ = orc.bw_predict(p, d)
+    m = np.where(np.isfinite(T), T, 1.0).astype(np.float32)
+    loss, cnt, g = orc.bw_loss_grad(p, d, m)
+    out = wmb.bw_loss_grad(wmb.DeviceBwDescriptors.from_host(d), torch.from_numpy(m).cuda(), p).cpu().numpy()
+    assert int(out[1]) == cnt
+    assert abs(out[0] - loss) <= 1e-13
+    x = np.abs(np.asarray(p.theta))
+    assert np.all(np.abs(out[2:] - g) * x <= 1e-6 * np.max(x * np.abs(g)))

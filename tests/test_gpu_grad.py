@@ -232,3 +232,19 @@ def test_vjp_sweep_keeps_seven_waves_per_simd(wmb):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     say("rows written", rows)
     assert rows == 7 * cus + words // 256 + 1
+
+
+@pytest.mark.parametrize("n", [63, 65, 129, 257, 5000, 16321, 16385])
+def test_float64_pass_of_one_block_shares_its_words(wmb, orc, n):
+    """Every descriptor flagged, up to and past the 256 flag words that the four
+    waves of a single block share: 1 to 5 words, shares that do not divide, the
+    last word not full.  Tolerances as in the test of flags and row slots."""
+    p = synth.param_set(6)
+    d = synth.descriptors(n, 107)
+    T, _ = orc.predict(p, d)
+    m = np.where(np.isfinite(T), T, 1.0).astype(np.float32)
+    loss, cnt, g = orc.loss_grad(p, d, m)
+    out = wmb.loss_grad(wmb.DeviceDescriptors.from_host(d), torch.from_numpy(m).cuda(), p).cpu().numpy()
+    assert int(out[1]) == cnt
+    assert abs(out[0] - loss) <= 1e-13
+    assert np.all(np.abs(out[2:] - g) * np.abs(p.theta) <= 1e-11 * loss_grad_absum(orc, p, d, m) + 1e-300)
