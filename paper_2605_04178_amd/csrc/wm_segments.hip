@@ -11,6 +11,7 @@
 // loads in pieces staged in LDS, and each application's owner thread adds its
 // rows in float64, in row order.
 #include "wm_device.hpp"
+#include "wm_shares.hpp"
 
 namespace wm {
 
@@ -751,16 +752,18 @@ static hipError_t apps_grad_t(const DescPtrs& d, const SegPtrs& sg, int64_t n_se
     // and the pass's count of finished blocks in the first row past them (one
     // block less where every row is taken)
     constexpr int kRows = kAppsMaxBlocks + kAppsLongBlocks + kRedoMaxBlocks;
-    // A launch is 2 to 3 us of a small call: a single block clears the flags
+    // A launch is 2 to 3 us of a small call: a single block clears few flags
     // itself, and with no more rows than a piece holds no application is long
     // (loss and gradient over 31 applications 18.7 us with both launches, 12.4
     // without).
     const bool any_long = n_seg > c.block;
     int nb1 = 1, nrows1 = 0, nb2 = 1;
     uint32_t* ticket = nullptr;
+    bool alone = false;
     const auto place = [&] {
+        alone = sweep_clears_flags(nb1, rwords, c.block);
         nrows1 = nb1 + (any_long ? kAppsLongBlocks : 0);
-        if (nb1 > 1 && rwords > 0) {
+        if (!alone && rwords > 0) {
             const int64_t zb = (rwords + 255) / 256;
             k_zero_words<<<(int)(zb < 1024 ? zb : 1024), 256, 0, s>>>(rflags, rwords);
         }
@@ -772,7 +775,7 @@ static hipError_t apps_grad_t(const DescPtrs& d, const SegPtrs& sg, int64_t n_se
     case B:                                                                                           \
         nb1 = apps_grid<B, MODE>(n_apps, c.grid_mult);                                               \
         place();                                                                                      \
-        if (nb1 == 1)                                                                                \
+        if (alone)                                                                                   \
             k_apps_grad<B, MODE, true><<<1, B, 0, s>>>(d, sg, n_seg, n_apps, S, Q, meas, rows, aflags, \
                                                        lflags, rflags, wrow, ticket);                \
         else                                                                                         \

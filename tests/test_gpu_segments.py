@@ -244,3 +244,27 @@ def test_apps_float64_pass_splits(wmb, orc, n_apps, smin, smax):
     w = torch.ones(n_apps, dtype=torch.float32, device="cuda")
     g = [wmb.apps_vjp(dd, ds, w, p, q, ws=ws).cpu().numpy() for _ in range(2)]
     assert np.array_equal(g[0], g[1]) and np.isfinite(g[0]).all()
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+def test_apps_row_flags_cleared_on_both_sides(wmb, orc, extra):
+    """The most rows whose flags a single block of 64 clears itself (64 words per
+    thread), and one more, which a launch of its own clears: in a workspace of
+    ones, rows of a word past the last flagged one included."""
+    p = synth.param_set(8)
+    q = synth.seg_params(18)
+    rows = 64 * 64 * 64 + extra
+    sg, d = synth.segments(1, 153, rows, rows)
+    sg.app_off = np.array([0, rows - 70, rows - 50, rows], np.int32)
+    Ta, _ = orc.predict_apps(p, q, d, sg)
+    m = Ta * np.array([1.03, 1.0, 0.96])
+    dd, ds = _dev(wmb, sg, d)
+    default = wmb.get_launch(wmb.OP_APPS_LOSS_GRAD, 3)
+    wmb.set_launch(wmb.OP_APPS_LOSS_GRAD, 3, 64, 1, 1)
+    try:
+        first = _grad_check(wmb, orc, p, q, sg, d, m, f"{rows} rows")
+        ws = torch.full((wmb.apps_workspace_bytes(dd.n, 3),), 255, dtype=torch.uint8, device="cuda")
+        again = wmb.apps_loss_grad(dd, ds, torch.from_numpy(m.astype(np.float32)).cuda(), p, q, ws=ws)
+        assert np.array_equal(again.cpu().numpy(), first)
+    finally:
+        wmb.set_launch(wmb.OP_APPS_LOSS_GRAD, 3, default["block"], default["per_thread"], default["grid_mult"])

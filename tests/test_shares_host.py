@@ -30,3 +30,12 @@ def test_tile_runs(tmp_path, n, avg):
         assert 1 <= per <= one
         # no shorter than three rounds of 64 candidates unless the runs of gm = 1 are
         assert per >= min(one, 192 // avg if avg else one)
+
+
+def test_sweep_clears_flags(tmp_path):
+    f = _build(tmp_path, "clears", 'std::printf("%d", (int)sweep_clears_flags(std::atoi(v[1]), std::atoll(v[2]), '
+                                   "std::atoi(v[3])));")
+    for block in (64, 128, 256, 512):
+        assert f(1, 0, block) == [1] and f(1, 64 * block, block) == [1]
+        assert f(1, 64 * block + 1, block) == [0] and f(1, 1 << 25, block) == [0]
+        assert f(2, 1, block) == [0]
