@@ -135,6 +135,44 @@ def test_multipliers_sorted_keys(wmb, orc, kind):
     _check_mult(wmb, orc, T, m, off, train, f"sorted keys, {kind}")
 
 
+@pytest.mark.parametrize("sizes", [(31, 31), (29, 1), (63, 0), (33, 31), (61, 3), (45, 45, 7)])
+def test_multipliers_runs_of_ratios_that_agree_in_the_kept_bits(wmb, orc, sizes):
+    # m/T = (k + 1)/k for distinct k next to 2^24: neighbouring ratios differ by 16
+    # units in the last place, so the sort key, which gives its last six bits to
+    # the lane, holds some four of them to be equal and leaves them in row order.
+    # Rows shuffled, all of them training rows, an odd number per group: the
+    # median lies inside such a run and is one row's ratio, not a rounding tie
+    # (weights agree to 2^-24, half the total lies half a weight from either sum).
+    rng = np.random.default_rng(29)
+    off = np.concatenate([[0], np.cumsum(list(sizes) * 40)]).astype(np.int32)
+    n = int(off[-1])
+    k = np.zeros(n)
+    for a, b in zip(off[:-1], off[1:]):
+        k[a:b] = 2 ** 24 - 1 - rng.permutation(64)[:b - a]
+    T, m = k.astype(np.float32), (k + 1).astype(np.float32)
+    assert np.array_equal(T.astype(float), k) and np.array_equal(m.astype(float), k + 1)
+    train = np.ones(n, np.uint8)
+    # without putting the runs in order, a good part of the groups would differ
+    x = (k + 1) / k
+    kept = x.view(np.uint64) & ~np.uint64(63)
+    wrong = 0
+    for a, b in zip(off[:-1], off[1:]):
+        w = (k / (k + 1))[a:b]
+        def median(order):
+            c = np.cumsum(w[order])
+            return x[a:b][order][np.argmax(c >= 0.5 * c[-1])] if b > a else 1.0
+        wrong += median(np.argsort(kept[a:b], kind="stable")) != median(np.argsort(x[a:b], kind="stable"))
+    say("groups a sort by the kept bits alone would get wrong:", wrong, "of", len(off) - 1)
+    assert wrong >= 20
+    # (the training errors, |mu T - m| / m, cancel to the rounding of mu T in either
+    # evaluation: not compared)
+    mult, Ts, st = wmb.fit_multipliers(*(torch.from_numpy(v).cuda() for v in (T, m, off, train)))
+    om, oTs, _ = orc.fit_multipliers(T.astype(np.float64), m.astype(np.float64), off, train)
+    assert np.array_equal(mult.cpu().numpy(), om)
+    assert np.array_equal(Ts.cpu().numpy(), oTs.astype(np.float32))
+    assert st[1].item() == n and st[3].item() == 0
+
+
 # plan totals and all-singles sums: float32 run costs (the model's prediction
 # tolerance), summed in float64
 PLAN_RTOL = 1e-5
