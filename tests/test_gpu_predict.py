@@ -248,3 +248,30 @@ def test_occupancy_and_rounds_at_the_edges(wmb, orc, part):
     d.grid = np.clip(G, 1, 2 ** 31 - 1).astype(np.int32)
     _, occ, _ = _parity(wmb, orc, p, d, str(part))
     say(part, "feasible", int((occ > 0).sum()), "distinct", np.unique(occ).size)
+
+
+@pytest.mark.parametrize("per_thread", [1, 2, 4, 8])
+@pytest.mark.parametrize("n", [1, 3, 5, 1023, 1025, 4097, 10001])
+def test_predict_ragged_and_misaligned_in_every_form(wmb, orc, n, per_thread):
+    """Each number of descriptors per thread, at sizes that are no multiple of it
+    (the wide forms' tails), and with every array one, two and three elements off
+    the 16 bytes that the wide loads need: the same bytes, from the narrow form."""
+    p = synth.param_set(0)
+    d = synth.descriptors(n + 3, 31 + n)
+    dd = wmb.DeviceDescriptors.from_host(d)
+    To, occo = orc.predict(p, d)
+    T0, o0 = wmb.predict(dd, p)   # the default form, aligned
+    T0, o0 = T0.cpu().numpy(), o0.cpu().numpy()
+    assert np.array_equal(o0, occo) and rel_err(T0, To).max() <= TOL
+    wmb.set_launch(wmb.OP_PREDICT, n, 256, per_thread)
+    assert wmb.get_launch(wmb.OP_PREDICT, n)["per_thread"] == per_thread
+    for k in range(4):
+        T, o = wmb.predict(dd.slice(k, k + n), p)
+        assert np.array_equal(o.cpu().numpy(), o0[k:k + n]), k
+        assert np.array_equal(np.nan_to_num(T.cpu().numpy(), nan=-1.0), np.nan_to_num(T0[k:k + n], nan=-1.0)), k
+    # outputs off the alignment too
+    out_T, out_o = torch.zeros(n + 1, device="cuda"), torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    wmb.predict(dd.slice(0, n), p, out_T=out_T[1:], out_occ=out_o[1:])
+    assert out_T[0].item() == 0.0 and out_o[0].item() == 0
+    assert np.array_equal(out_o[1:].cpu().numpy(), o0[:n])
+    assert np.array_equal(np.nan_to_num(out_T[1:].cpu().numpy(), nan=-1.0), np.nan_to_num(T0[:n], nan=-1.0))

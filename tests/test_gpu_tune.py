@@ -162,3 +162,17 @@ def test_autotuners_install_valid_configs_and_cache_roundtrip(wmb, orc, tmp_path
         _restore(wmb, wmb.OP_PREDICT, 1 << 20)
         _restore(wmb, wmb.OP_VJP, 1 << 20)
         _restore(wmb, wmb.OP_SELECT_TILE, 20000)
+
+
+@pytest.mark.parametrize("turn", [0, 1])
+def test_launches_end_with_the_test(wmb, turn):
+    # the same test twice: what the first sets and tunes, the second does not see
+    n = 777_777
+    default = {"block": 256, "per_thread": 1, "grid_mult": 1, "chunk": 0}
+    assert wmb.get_launch(wmb.OP_PREDICT, n) == default
+    assert wmb.get_launch(wmb.OP_PREDICT_APPS, n) == {**default, "grid_mult": 4}
+    assert wmb.get_launch(wmb.OP_CALIBRATE_BATCHED, n) == {**default, "chunk": 2048}
+    wmb.set_launch(wmb.OP_PREDICT, n, 512, 4)
+    wmb.set_launch(wmb.OP_PREDICT_APPS, n, 128, 1, 1)
+    wmb.set_launch(wmb.OP_CALIBRATE_BATCHED, n, 256, 1, 1, 4096)
+    assert wmb.get_launch(wmb.OP_PREDICT, n)["per_thread"] == 4
