@@ -111,7 +111,8 @@ __device__ inline void bw_grad_exact(const BwSet& S, const BwDesc& x, float wi, 
 
 // Phase 1: wave-aligned groups of 64 descriptors, one ballot word of redo
 // flags per group (written exactly once).
-// Bound: vector instructions (225 per 64 descriptors, reciprocals counted once)
+// Bound: vector instructions (244 per 64 descriptors, 251 with the grid doubled;
+// 0.95 to 1.0 per CU-cycle)
 // and the 36 B of each descriptor, both near their rates.  At 2^24 descriptors
 // the sweep took 168 us with the dtype's tensor rate an indexed load from the
 // kernel arguments (its latency inside the evaluation) and a 64-bit vector add

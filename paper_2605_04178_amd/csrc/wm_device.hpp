@@ -194,7 +194,8 @@ __device__ inline double load_shared(const double* p)
 // count shows the block as finished, so the last block's load_shared see
 // every row.  An agent-scope release and acquire around the count would write
 // back and invalidate whole L2 caches for the same guarantee: measured slower
-// than a separate launch for the final reduction.
+// than a separate launch for the final reduction.  Only what goes by store_shared
+// and load_shared is ordered so: a plain store read by the last block would race.
 __device__ inline bool last_block(uint32_t* ticket, uint32_t nblocks)
 {
     __shared__ uint32_t last;

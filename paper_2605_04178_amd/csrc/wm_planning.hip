@@ -342,10 +342,13 @@ __device__ inline double prefix_lanes(double c)
 // in the last bits; where that moves the choice, the two ratios' objectives
 // are equal to rounding (the objective is flat between them when C equals
 // half the total).
-// Bound: VALU issue (0.8 per CU-cycle).  At 2^16 groups of 1-40 rows / 1.34 M
-// rows k_fit_mult takes 28.6 us; with (x, row) pairs exchanged by ds_bpermute
-// (45 per wave) it was held by the LDS pipe and took 53.3.  DPP moves and
-// lane-row swaps leave five VALU instructions per step.
+// Bound: latency.  Counted over the launch the kernel issues 0.42 vector
+// instructions per CU-cycle with 11 waves per CU on average (of 28): the sort is
+// 21 dependent steps, and a pair with a group beyond 32 rows (36 % of them at 1-40
+// rows per group) waits for its rows, which are not loaded ahead.  At 2^16 groups /
+// 1.34 M rows k_fit_mult takes 28.6 us; with (x, row) pairs exchanged by
+// ds_bpermute (45 per wave) it was held by the LDS pipe and took 53.3.  DPP moves
+// and lane-row swaps leave five VALU instructions per step.
 template <int W>
 __device__ inline void fit_pair_sorted(int64_t g0, bool has1, int n0, bool in, uint32_t at, float t, float m,
                                        bool tr, double* __restrict__ mult, float* __restrict__ T_scaled,
@@ -752,9 +755,11 @@ constexpr uint8_t kPlanUncertain = 0x80;
 // The chains of the block's rows are bracketed by two 64-way searches of the
 // offsets (three dependent loads for 2^16 chains; a binary search per row has
 // sixteen).
-// Bound: VALU issue (0.86 per CU-cycle; lanes wait for their wave's longest start,
-// 5.1 of 8 steps used -- ordering the block's starts by run count saved the
-// steps and lost as much to the uneven waves).  At 2^16 chains / 589 K rows, R =
+// Bound: VALU issue while the chip is full, uneven waves at the end (over the
+// launch 0.66 vector instructions per CU-cycle with 14 waves per CU on average, of
+// 24; lanes wait for their wave's longest start, 5.1 of 8 steps used -- ordering
+// the block's starts by run count saved the steps and lost as much to the uneven
+// waves).  At 2^16 chains / 589 K rows, R =
 // 8: 46.2 us; 51.4 with the model's quotients on integers and its selects as
 // branches, 68.0 with the rows loaded, converted and tested per run as well.
 struct FuseArgs {   // k_fuse_costs's parameters, in order
@@ -1229,7 +1234,7 @@ __device__ inline void plan_starts(const PlanGroup<G>& g, bool live, const PlanS
 // that are not non-decreasing) gets NaN totals and no start flags; a chain
 // holding an uncertain run or a close decision is queued for the float64
 // redo; the rest get their totals and start flags.
-constexpr int kPlanBlock = 256;    // threads per block of the planning pass (5 blocks per CU)
+constexpr int kPlanBlock = 256;    // threads per block of the planning pass (4 blocks per CU)
 
 template <int G>
 __global__ __launch_bounds__(kPlanBlock) void k_plan(const int32_t* __restrict__ off,

@@ -68,9 +68,9 @@ __device__ inline double exact_cost(const Set& S, int32_t M, int32_t N, int32_t 
 
 // ---------------------------------------------------------------------------
 // float32 cost of one candidate: the same terms in the form that costs the
-// fewest vector instructions, which bound the selection: 2^16 shapes with 3.4e6
-// candidates took 16.5e6 of them and 33.2 us with the descriptor formed and
-// evaluated as any other, and take 9.8e6 and 27.4 us.
+// fewest vector instructions: 2^16 shapes with 3.4e6 candidates took 16.5e6 of them
+// and 33.2 us with the descriptor formed and evaluated as any other, and take 9.7e6
+// and 28.2 us.
 //   - Tile sizes and everything that follows from them alone are powers of two:
 //     their float forms are built from their exponents.
 //   - What only the shape decides (compulsory traffic, the dtype's peak) sits in
@@ -413,8 +413,11 @@ __device__ inline void direct_shape(const TileArgs& C, int64_t i, int lane)
 // A run per wave, cut where the LDS is full, takes short calls and long lists
 // where fixed batches of eight shapes left waves idle or went without the queue:
 // 1000 shapes of up to 96 candidates 16.1 -> 7.0 us, 2^14 of up to 384 87.4 -> 30.7.
-// Bound by vector instructions.  The LDS of a wave leaves room for 24 waves per
-// CU, so the kernel asks for 6 waves per SIMD (at most 80 VGPRs).
+// Bound: vector instructions and latency.  Over a launch of 2^16 shapes it issues
+// 0.45 to 0.53 of them per CU-cycle: each wave has one batch, so that all load at
+// their start and evaluate the queues at their end together.  The LDS of a wave
+// leaves room for 24 waves per CU, so the kernel asks for 6 waves per SIMD (at most
+// 80 VGPRs).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void k_select_tile(const TileArgs A)
 {
